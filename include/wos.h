@@ -326,8 +326,9 @@ wos_status wos_finalize_grad(const double* grad_sum, const double* grad_sum_sq, 
  * walks (eight per resident lane; the per-walk buffers of the plan's workspace only, the
  * caller's outputs are not touched), keeps the fastest for that variant, and builds with
  * it. Later plans and wos_solve of the same variant reuse it. Jobs with fewer walks than
- * the prefix keep 256 / 256. Explicit values are used as given. Synchronous; the caller's
- * stream is used for the timing runs. */
+ * the prefix are not timed: they take tiles of 64 to 256 walks, shorter for smaller jobs.
+ * Explicit values are used as given. Synchronous; the caller's stream is used for the
+ * timing runs. */
 typedef struct wos_plan wos_plan;
 wos_status wos_plan_create(const wos_batch_item* items, int32_t n_items, const wos_options* opt,
                            void* stream, wos_plan** out);

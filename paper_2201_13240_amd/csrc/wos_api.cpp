@@ -1006,9 +1006,23 @@ uint64_t slots_for(uint64_t total_points, uint64_t chunk, uint32_t tile) {
   return total_points * std::max<uint64_t>(1, (chunk + tile - 1) / tile);
 }
 
-// Block size and tile length: the caller's, else the tuned shape of this walker, else
-// 256 / 256. Walks per point are split into launches only when the slots of one launch
-// would exceed the workspace cap.
+// Walks of a job from which its walker variant is autotuned, and below which the tuned
+// tile length is cut to the job (eight per resident lane).
+uint64_t tune_walks(uint64_t lanes) { return 8 * lanes; }
+
+// Longest tile, 64 to 256 walks, that leaves every resident wave about eight of them: a wave
+// that takes the last tile of a job holds up its end, and with 256 walks it does so for four
+// rounds of its lanes (square of 65,536 points x 64 walks: 31.0 ms at 256, 29.0 at 64; disk of
+// 804 points x 128: 680 and 545 us).
+uint32_t tile_for(uint64_t walks, uint64_t lanes) {
+  uint32_t tile = 256;
+  while (tile > 64 && walks < 8 * (lanes / 64) * tile) tile /= 2;
+  return tile;
+}
+
+// Block size and tile length: the caller's, else the tuned shape of this walker where the
+// job is large enough to have been tuned on, else by the job's size. Walks per point are split
+// into launches only when the slots of one launch would exceed the workspace cap.
 wos_status pick_shape(const wos_options* opt, Schedule& s) {
   unsigned block = 256u;
   uint32_t tile = 256u;
@@ -1021,15 +1035,15 @@ wos_status pick_shape(const wos_options* opt, Schedule& s) {
     }
   }
   if (opt->block_size) block = (unsigned)opt->block_size;
-  if (opt->tile_walks > 0) tile = (uint32_t)opt->tile_walks;
-  s.tile_walks = tile;
   wos_status r = grid_for_block(s, block);
+  bool tuned = false;
   if (r != WOS_OK) return r;
   const uint64_t cap = opt->workspace_bytes ? opt->workspace_bytes : (4ull << 30);
   const uint64_t slot_bytes = (uint64_t)s.slot_words * 8u;
   const uint64_t N = opt->walks_per_point;
   uint64_t nc = N;
   if (s.total_points > 0 && slots_for(s.total_points, N, tile) * slot_bytes > cap) {
+      tuned = true;
     const uint64_t tiles_per_point = std::max<uint64_t>(1, cap / slot_bytes / s.total_points);
     nc = std::min<uint64_t>(N, tiles_per_point * tile);
   }
@@ -1037,6 +1051,10 @@ wos_status pick_shape(const wos_options* opt, Schedule& s) {
   s.n_launches = (int)((N + nc - 1) / nc);
   return WOS_OK;
 }
+  const uint64_t lanes = (uint64_t)s.grid * s.block, walks = s.total_points * opt->walks_per_point;
+  if (opt->tile_walks > 0) tile = (uint32_t)opt->tile_walks;
+  else if (!tuned || walks < tune_walks(lanes)) tile = std::min(tile, tile_for(walks, lanes));
+  s.tile_walks = tile;
 
 // Cuts each item's walks of one launch into point-major tiles of `tile` walks and numbers
 // their slots (DevItem); returns the launch's tiles and slots.
@@ -1142,7 +1160,7 @@ WsLayout ws_layout(const Schedule& s, int n_items, uint64_t max_slots, int cus) 
   L.inside = take(std::max<uint64_t>(s.total_points, 1));
   L.gamma0 = take(std::max<uint64_t>(s.total_points, 1) * (s.fp64 ? 8 : 4));
   L.items = take(sizeof(DevItem) * (size_t)n_items * s.n_launches);
-  L.counter = take(sizeof(uint32_t) * 64);
+  L.counter = take(sizeof(uint32_t) * kTileQueues * kTileQueueStride);
   L.lp = take(sizeof(LaunchParams));
   L.slots = take((size_t)std::max<uint64_t>(max_slots, 1) * s.slot_words * sizeof(uint64_t));
   L.grad = take(s.grad ? grad_record_bytes(s) * max_grid_lanes(cus) : 0);
@@ -1206,7 +1224,11 @@ WalkerLaunch walker_launch(const wos_options* opt, const Schedule& s, const Work
   L.fp64 = s.fp64;
   L.dim = s.dim;
   L.geom = s.geom;
-  L.grid = s.grid;
+  // no more waves than tiles, and in a launch of several items as many for every queue
+  L.n_queues = n_items > 1 ? kTileQueues : 1;
+  const uint64_t per_block = s.block / 64;
+  const uint64_t need = (n_tiles + per_block - 1) / per_block;
+  L.grid = (unsigned)std::min<uint64_t>(s.grid, (need + L.n_queues - 1) / L.n_queues * L.n_queues);
   L.block = s.block;
   L.items = items;
   L.n_items = n_items;
@@ -1529,7 +1551,7 @@ wos_status autotune(wos_plan* P, hipStream_t st, unsigned* block, uint32_t* tile
     if (r != WOS_OK) return r;
     lanes = std::max<uint64_t>(lanes, (uint64_t)s.grid * b);
   }
-  const uint64_t walks = 8 * lanes;
+  const uint64_t walks = tune_walks(lanes);
   if (launch0 < walks) return WOS_OK;
   // A shape is scored by the marginal time of 4W more walks, T(5W) - T(W): in samples
   // this small the launch's drain (lanes idle while the last walks finish) is a large part

@@ -111,16 +111,13 @@ __global__ void reduce_kernel(DevItem it, const uint64_t* __restrict__ slots, in
   }
 }
 
-// Zeroes the slots (and the tile counter) before a walker launch; a kernel rather than a
+// Zeroes the slots (and the tile counters) before a walker launch; a kernel rather than a
 // memset node, so that it can be captured in the plan's graph.
-__global__ void clear_kernel(uint64_t* __restrict__ p, uint64_t n, uint32_t* counter) {
+static_assert(kTileQueues * kTileQueueStride <= 256, "one thread of block 0 per counter word");
+__global__ void clear_kernel(uint64_t* __restrict__ p, uint64_t n, uint32_t* counters) {
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = 0;
-  if (blockIdx.x == 0 && threadIdx.x == 0) *counter = 0;
-}
-
-__global__ void reset_kernel(uint32_t* counter) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *counter = 0;
+  if (blockIdx.x == 0 && threadIdx.x < kTileQueues * kTileQueueStride) counters[threadIdx.x] = 0;
 }
 
 __global__ void set_params_kernel(LaunchParams* lp, uint64_t seed, uint64_t add) {
@@ -439,19 +436,14 @@ hipError_t launch_reduce(int grad_dim, const DevItem& it, const uint64_t* slots,
   return hipGetLastError();
 }
 
-hipError_t launch_clear(uint64_t* p, uint64_t n, uint32_t* counter, hipStream_t st) {
+hipError_t launch_clear(uint64_t* p, uint64_t n, uint32_t* counters, hipStream_t st) {
   const unsigned blocks = (unsigned)std::min<uint64_t>(std::max<uint64_t>((n + 255) / 256, 1), 4096);
-  hipLaunchKernelGGL(clear_kernel, dim3(blocks), dim3(256), 0, st, p, n, counter);
+  hipLaunchKernelGGL(clear_kernel, dim3(blocks), dim3(256), 0, st, p, n, counters);
   return hipGetLastError();
 }
 
 hipError_t launch_set_params(LaunchParams* lp, uint64_t seed, uint64_t walk_offset_add, hipStream_t st) {
   hipLaunchKernelGGL(set_params_kernel, dim3(1), dim3(64), 0, st, lp, seed, walk_offset_add);
-  return hipGetLastError();
-}
-
-hipError_t launch_reset(uint32_t* counter, hipStream_t st) {
-  hipLaunchKernelGGL(reset_kernel, dim3(1), dim3(64), 0, st, counter);
   return hipGetLastError();
 }
 

@@ -18,7 +18,8 @@ struct WalkerLaunch {
   const DevItem* items;
   int n_items;
   uint32_t n_tiles;   // tiles of all items
-  uint32_t* tile_counter;
+  uint32_t n_queues;  // 1 or kTileQueues: queues the tiles are cut into
+  uint32_t* tile_counter;   // [kTileQueues * kTileQueueStride], zeroed before the launch
   uint64_t* slots;    // accumulation slots, slot_words(grad dim) words each, zeroed before the launch
   int slot_words;
   const LaunchParams* lp;
@@ -53,11 +54,10 @@ int walker_mode(int variant, bool grad, bool split);
 const void* walker_symbol(int fp64, int dim, int geom, int mode);
 // Per-point sums of one item from its slots, added into the item's outputs.
 hipError_t launch_reduce(int grad_dim, const DevItem& it, const uint64_t* slots, int slot_words, hipStream_t st);
-// Zeroes n words at p and the tile counter (a kernel, so that it can sit in a captured graph).
-hipError_t launch_clear(uint64_t* p, uint64_t n, uint32_t* counter, hipStream_t st);
+// Zeroes n words at p and the tile counters (a kernel, so that it can sit in a captured graph).
+hipError_t launch_clear(uint64_t* p, uint64_t n, uint32_t* counters, hipStream_t st);
 hipError_t launch_finalize_components(const double* sum, const double* sum_sq, const uint64_t* nw, int64_t n, int dim,
                                       double* mean, double* se, hipStream_t st);
-hipError_t launch_reset(uint32_t* counter, hipStream_t st);
 hipError_t launch_set_params(LaunchParams* lp, uint64_t seed, uint64_t walk_offset_add, hipStream_t st);
 hipError_t launch_classify(int dim, int geom, const void* P64, const double* pts, int64_t n, int8_t* inside,
                            uint64_t* counters, hipStream_t st);

@@ -74,6 +74,7 @@ struct WalkerArgs {
   T ww_hi;               // > 0: expected-value splitting above this weight (delta tracking)
   T* grad;               // [grid lane][GradRecord<DIM>::kStride] or null: gradient records
   uint64_t* events;      // event-counting build only: [kEvents]
+  uint32_t n_queues;     // queues they are cut into (TileQueues)
 };
 
 // Events counted by the event-counting build of the walker (algorithmic work per step).
@@ -88,6 +89,52 @@ constexpr uint32_t kFlagRR = 1u << 30;
 constexpr uint32_t kStepMask = (1u << 30) - 1;
 
 __device__ __forceinline__ const void* uniform_ptr(const void* p) { return (const void*)uniform_u64((uint64_t)p); }
+
+// The launch's tiles in one queue, or in kTileQueues equal runs, one for each XCD. A wave
+// takes its first tile of its own queue by its place in the grid, so that a launch does not
+// open with every wave on one counter (5120 atomics on one address take about 50 us, the
+// time of a small job's walks), and a launch with no more tiles than waves uses no counter
+// at all; the next ones come from the queue's counter. A wave whose queue is empty goes on
+// with the others. Block b runs on XCD b mod 8 (dispatch order; only speed depends on it):
+// with several problems in a launch the waves of an XCD then share one problem's tables in
+// their L2 and meet an eighth of the problem switches, each of which drains a wave.
+struct TileQueues {
+  uint32_t n_tiles, n_queues;
+  uint32_t q;         // current queue
+  uint32_t left;      // queues not yet found empty, the current one included
+  bool first;
+
+  __device__ __forceinline__ void init(uint32_t n, uint32_t nq) {
+    n_tiles = n;
+    n_queues = nq;
+    q = blockIdx.x % nq;
+    left = nq;
+    first = true;
+  }
+  __device__ __forceinline__ uint32_t base(uint32_t k) const { return (uint32_t)((uint64_t)n_tiles * k / n_queues); }
+  // Next tile of this wave, or -1 when none is left. Called with every lane active.
+  __device__ __forceinline__ int64_t next(uint32_t* counter, uint32_t lane) {
+    const uint32_t wpb = blockDim.x >> 6;
+    if (first) {
+      first = false;
+      const uint32_t b = base(q), place = blockIdx.x / n_queues * wpb + (uint32_t)uniform_int((int)(threadIdx.x >> 6));
+      if (place < base(q + 1) - b) return (int64_t)(b + place);
+    }
+    while (left) {
+      const uint32_t b = base(q), size = base(q + 1) - b;
+      const uint32_t waves = (gridDim.x - q + n_queues - 1) / n_queues * wpb;   // that took a first tile by place
+      if (size > waves) {
+        uint32_t t = 0;
+        if (lane == 0) t = atomicAdd(counter + q * kTileQueueStride, 1u);
+        t = (uint32_t)uniform_int((int)t);
+        if (t < size - waves) return (int64_t)(b + waves + t);
+      }
+      --left;
+      q = q + 1 == n_queues ? 0 : q + 1;
+    }
+    return -1;
+  }
+};
 
 // A walk split by the weight window resumes its pending sibling branches from this state.
 constexpr int kSplitDepth = 4;
@@ -363,7 +410,7 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
   const WOS_GLOBAL DevItem* items = gptr(a.items);
   // ---- wave-uniform scheduling state: the current item, the tile being handed out
   // (walks res_next .. res_end - 1 of it: point tl_p0 + (tl_j0 + r) / walks), the next
-  // claimed tile, and the item searched for it (tiles are claimed in increasing order)
+  // claimed tile, and the item searched for it (a queue's tiles come in increasing order)
   int cur_item = -1, search_item = 0;
   uint32_t res_next = 0, res_end = 0;
   uint32_t tl_p0 = 0, tl_j0 = 0, tl_slot0 = 0, tl_walks = 1, tl_single = 1;
@@ -411,6 +458,8 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
     // ---------------------------------------------------------------- finished walks
     // A walk that ended in the last iteration adds its estimate A + Ac, its square, its
     // distance queries and flags (in nsteps) to its slot here, where little else is live.
+  TileQueues tiles;
+  tiles.init(a.n_tiles, a.n_queues);
     if constexpr (kQueue) {
       const uint64_t fin = __ballot(phase == 4);
       if (fin) {
@@ -440,15 +489,12 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
       if (res_next >= res_end) {
         if (pend_tile < 0) {
           if (queue_done) break;
-          // every lane is active here, so the first active lane is lane 0
-          uint32_t t = 0;
-          if (lane == 0) t = atomicAdd(tile_counter, 1u);
-          t = __builtin_amdgcn_readfirstlane(t);
-          if (t >= a.n_tiles) {
+          pend_tile = tiles.next(tile_counter, lane);
+          if (pend_tile < 0) {
             queue_done = true;
             break;
           }
-          pend_tile = (int64_t)t;
+          if (pend_tile < (int64_t)items[search_item].tile_base) search_item = 0;   // from another queue
           while (pend_tile >= (int64_t)(items[search_item].tile_base + items[search_item].n_tiles))
             search_item = uniform_int(search_item + 1);
         }
@@ -1011,3 +1057,4 @@ static const void* walker_symbol_td(int geom, int mode) {
 }
 
 }  // namespace wos
+  a.n_queues = L.n_queues;
