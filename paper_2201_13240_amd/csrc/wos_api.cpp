@@ -129,9 +129,21 @@ wos_status check_field(const wos_field_desc& f, int dim, const char* name, bool 
   return WOS_OK;
 }
 
+// Number of terms of a field on the device: whole groups.
+int padded_terms(const wos_field_desc& f) {
+  if (f.base != WOS_FIELD_FOURIER && f.base != WOS_FIELD_BUMPS) return 0;
+  const int g = f.base == WOS_FIELD_FOURIER ? kFourierGroup : kBumpGroup;
+  return (std::max(f.n_terms, 0) + g - 1) / g * g;
+}
+
 template <typename T>
 std::vector<T> field_terms(const wos_field_desc& f, int dim) {
-  std::vector<T> out((size_t)std::max(f.n_terms, 0) * kTermStride, (T)0);
+  // zeros: a wave of amplitude and wave vector 0; a bump of amplitude 0 also takes a width,
+  // so that its exponent is -inf, not NaN, where the square of the distance overflows
+  const int n = padded_terms(f);
+  std::vector<T> out((size_t)n * kTermStride, (T)0);
+  if (f.base == WOS_FIELD_BUMPS)
+    for (int j = std::max(f.n_terms, 0); j < n; ++j) out[(size_t)j * kTermStride + 3] = (T)1;
   for (int j = 0; j < f.n_terms; ++j) {
     const double* t = f.terms + j * (dim + 2);
     T* o = out.data() + (size_t)j * kTermStride;
@@ -168,7 +180,7 @@ DevField<T> field_header(const wos_field_desc& f) {
   std::memset(&d, 0, sizeof(d));
   d.base = f.base;
   d.transform = f.transform;
-  d.n = (f.base == WOS_FIELD_FOURIER || f.base == WOS_FIELD_BUMPS) ? f.n_terms : 0;
+  d.n = padded_terms(f);
   d.sol = f.solution_id;
   d.c0 = (T)f.c0;
   d.c1 = (T)f.c1;

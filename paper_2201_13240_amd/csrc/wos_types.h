@@ -19,12 +19,15 @@ enum SolutionId : int32_t { SOL_EXPCOS = 1, SOL_QUADRATIC = 2 };
 //            (one cosine) for the value alone
 //   bumps:   c0, c1, c2, log2(e)/(2 w^2) (for exp2), amp, 1/w^2 (the last two unused)
 constexpr int kTermStride = 8;
+// Terms are evaluated in groups; the last one is filled up with terms that add zero.
+constexpr int kFourierGroup = 2;
+constexpr int kBumpGroup = 4;
 
 template <typename T>
 struct DevField {
   int32_t base;
   int32_t transform;
-  int32_t n;         // number of terms
+  int32_t n;         // number of terms, a multiple of the group
   int32_t sol;       // manufactured solution id
   T c0, c1;          // value = c0 + c1 B  or  exp(c0 + c1 B)
   const T* terms;    // [n][kTermStride]
