@@ -1038,24 +1038,28 @@ uint32_t tile_for(uint64_t walks, uint64_t lanes) {
 wos_status pick_shape(const wos_options* opt, Schedule& s) {
   unsigned block = 256u;
   uint32_t tile = 256u;
+  bool tuned = false;
   {
     std::lock_guard<std::mutex> lk(g_occ_mutex);
     auto t = g_tuned.find(tune_key(s));
     if (t != g_tuned.end()) {
       block = t->second.first;
       tile = t->second.second;
+      tuned = true;
     }
   }
   if (opt->block_size) block = (unsigned)opt->block_size;
   wos_status r = grid_for_block(s, block);
-  bool tuned = false;
   if (r != WOS_OK) return r;
+  const uint64_t lanes = (uint64_t)s.grid * s.block, walks = s.total_points * opt->walks_per_point;
+  if (opt->tile_walks > 0) tile = (uint32_t)opt->tile_walks;
+  else if (!tuned || walks < tune_walks(lanes)) tile = std::min(tile, tile_for(walks, lanes));
+  s.tile_walks = tile;
   const uint64_t cap = opt->workspace_bytes ? opt->workspace_bytes : (4ull << 30);
   const uint64_t slot_bytes = (uint64_t)s.slot_words * 8u;
   const uint64_t N = opt->walks_per_point;
   uint64_t nc = N;
   if (s.total_points > 0 && slots_for(s.total_points, N, tile) * slot_bytes > cap) {
-      tuned = true;
     const uint64_t tiles_per_point = std::max<uint64_t>(1, cap / slot_bytes / s.total_points);
     nc = std::min<uint64_t>(N, tiles_per_point * tile);
   }
@@ -1063,10 +1067,6 @@ wos_status pick_shape(const wos_options* opt, Schedule& s) {
   s.n_launches = (int)((N + nc - 1) / nc);
   return WOS_OK;
 }
-  const uint64_t lanes = (uint64_t)s.grid * s.block, walks = s.total_points * opt->walks_per_point;
-  if (opt->tile_walks > 0) tile = (uint32_t)opt->tile_walks;
-  else if (!tuned || walks < tune_walks(lanes)) tile = std::min(tile, tile_for(walks, lanes));
-  s.tile_walks = tile;
 
 // Cuts each item's walks of one launch into point-major tiles of `tile` walks and numbers
 // their slots (DevItem); returns the launch's tiles and slots.

@@ -136,9 +136,13 @@ struct Rng {
 
   __device__ __forceinline__ void set_key(uint64_t seed) { key = make_uint2((uint32_t)seed, (uint32_t)(seed >> 32)); }
   __device__ __forceinline__ void init(uint32_t wk, uint32_t p, uint32_t prob) {
+    problem = prob;
+    start(wk, p);
+  }
+  // a walk of the problem set before
+  __device__ __forceinline__ void start(uint32_t wk, uint32_t p) {
     walk = wk;
     point = p;
-    problem = prob;
     block = 0;
   }
   template <int NB>
@@ -854,12 +858,32 @@ struct FV {
   T lap;
 };
 
+// x[ax] by selects. The empty asm statements keep each x[i] a value of its own: in 3D the
+// compiler would otherwise select an address instead, and with it keep every point of the
+// walker (its position, the sampled point) in LDS or scratch memory throughout.
 template <typename T, int DIM>
 __device__ __forceinline__ T axis_component(const T* x, int ax) {
   T v = x[0];
 #pragma unroll
-  for (int i = 1; i < DIM; ++i) v = ax == i ? x[i] : v;
+  for (int i = 1; i < DIM; ++i) {
+    T xi = x[i];
+    asm("" : "+v"(xi));
+    v = ax == i ? xi : v;
+  }
   return v;
+}
+
+// Calls fn with each term of a field, U at a time: their scalar loads are issued together, so
+// that a group waits for one (at one walk per wave, as at the end of a launch, a wait at
+// every term is most of the time of a loop). The host pads the terms to whole groups.
+template <typename T, int U, typename F>
+__device__ __forceinline__ void for_terms(G<DevField<T>>& f, F&& fn) {
+  const WOS_GLOBAL T* p = gptr(f.terms);
+#pragma unroll 1
+  for (int j = 0; j < f.n; j += U, p += U * kTermStride) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) fn(p + u * kTermStride);
+  }
 }
 
 // Base function B of a field at x, with gradient and Laplacian when D is true.
@@ -872,14 +896,13 @@ __device__ __forceinline__ FV<T, DIM> field_base(G<DevField<T>>& f, const T* x) 
   for (int i = 0; i < DIM; ++i) r.g[i] = 0;
   const int base = f.base;
   if (base == FB_FOURIER) {
-    const WOS_GLOBAL T* p = gptr(f.terms);
-    for (int j = 0; j < f.n; ++j, p += kTermStride) {
+    for_terms<T, kFourierGroup>(f, [&](const WOS_GLOBAL T* p) {
       if (!D) {
         // value alone: a cos(2 pi (k.x + phi / 2 pi)), one cosine
         T th = m_fma(p[0], x[0], m_fma(p[1], x[1], p[7]));
         if (DIM == 3) th = m_fma(p[2], x[2], th);
         r.v = m_fma(p[6], m_cospi2(th), r.v);
-        continue;
+        return;
       }
       // phase k.x in revolutions (k in cycles per unit length)
       T th = p[0] * x[0] + p[1] * x[1];
@@ -896,25 +919,25 @@ __device__ __forceinline__ FV<T, DIM> field_base(G<DevField<T>>& f, const T* x) 
         for (int i = 0; i < DIM; ++i) r.g[i] = m_fma(dval, p[i], r.g[i]);
         r.lap = m_fma(-val, p[5], r.lap);                // Laplacian: -|2 pi k|^2 B_j
       }
-    }
+    });
   } else if (base == FB_BUMPS) {
-    const WOS_GLOBAL T* p = gptr(f.terms);
-    for (int j = 0; j < f.n; ++j, p += kTermStride) {
+    for_terms<T, kBumpGroup>(f, [&](const WOS_GLOBAL T* p) {
       T d[DIM], r2 = 0;
 #pragma unroll
       for (int i = 0; i < DIM; ++i) {
         d[i] = x[i] - p[i];
         r2 = m_fma(d[i], d[i], r2);
       }
-      const T e = p[4] * m_exp2(-r2 * p[3]);   // p[3] = log2(e) / (2 w^2)
-      r.v += e;
+      const T g = m_exp2(-r2 * p[3]);   // p[3] = log2(e) / (2 w^2)
+      r.v = m_fma(p[4], g, r.v);
       if (D) {
+        const T e = p[4] * g;
         const T iw2 = p[5];
 #pragma unroll
         for (int i = 0; i < DIM; ++i) r.g[i] = m_fma(-e * iw2, d[i], r.g[i]);
         r.lap = m_fma(e, iw2 * (r2 * iw2 - (T)DIM), r.lap);
       }
-    }
+    });
   } else if (base == FB_TANH) {
     // the axis is a run-time value: select with compile-time indices so that x and r
     // stay in registers (a dynamic index would place them in scratch memory)
@@ -1021,18 +1044,44 @@ __device__ __forceinline__ void spectral2d_first_slot(G<Spectral2D<T>>& sp, cons
   out[0].lap = kFourPi2 * (lx + lyy);
 }
 
-template <typename T, bool D, int ND = 2>
-__device__ __forceinline__ void spectral2d(G<Spectral2D<T>>& sp, const T* x, FV<T, 2>* out) {
-  // phi(y) = 1, cos 2 pi y, sin 2 pi y, cos 4 pi y, sin 4 pi y, cos 6 pi y, sin 6 pi y
-  T phi[kSpecRow];
+// phi(y) = 1, cos 2 pi y, sin 2 pi y, cos 4 pi y, sin 4 pi y, cos 6 pi y, sin 6 pi y
+template <typename T>
+__device__ __forceinline__ void spectral_basis(T y, T* phi) {
   phi[0] = 1;
-  m_sincospi2(x[1], &phi[2], &phi[1]);
+  m_sincospi2(y, &phi[2], &phi[1]);
 #pragma unroll
   for (int n = 2; n <= kSpecK; ++n) {
     const T pc = phi[2 * n - 3], ps = phi[2 * n - 2];
     phi[2 * n - 1] = m_fma(pc, phi[1], -ps * phi[2]);
     phi[2 * n] = m_fma(ps, phi[1], pc * phi[2]);
   }
+}
+
+// The value of one slot alone.
+template <typename T, int SLOT>
+__device__ __forceinline__ T spectral2d_value(G<Spectral2D<T>>& sp, const T* x) {
+  T phi[kSpecRow];
+  spectral_basis<T>(x[1], phi);
+  T v = spectral_dot<T>(sp.m[0][SLOT][0], phi);
+  T cx1, sx1;
+  m_sincospi2(x[0], &sx1, &cx1);
+  T c = cx1, sn = sx1;
+#pragma unroll
+  for (int n = 1; n <= kSpecK; ++n) {
+    const T vc = spectral_dot<T>(sp.m[2 * n - 1][SLOT][0], phi);
+    const T vs = spectral_dot<T>(sp.m[2 * n][SLOT][0], phi);
+    v += m_fma(vc, c, vs * sn);
+    const T t = m_fma(c, cx1, -sn * sx1);
+    sn = m_fma(sn, cx1, c * sx1);
+    c = t;
+  }
+  return v;
+}
+
+template <typename T, bool D, int ND = 2>
+__device__ __forceinline__ void spectral2d(G<Spectral2D<T>>& sp, const T* x, FV<T, 2>* out) {
+  T phi[kSpecRow];
+  spectral_basis<T>(x[1], phi);
   if constexpr (D && ND == 1) {
     spectral2d_first_slot<T>(sp, x, phi, out);
     return;
@@ -1170,7 +1219,10 @@ template <typename T, int DIM, bool D>
 __device__ __forceinline__ void coefficient_bases(G<DevProblem<T>>& P, const T* x, FV<T, DIM>* b) {
   const int sp = DIM == 2 ? P.spectral : 0;
   if constexpr (DIM == 2) {
-    if (sp) spectral2d<T, D>(P.spec, x, b);
+    // a table that holds sigma alone gives its value alone, without the other slots and their
+    // derivatives
+    if (sp == 4) b[2].v = spectral2d_value<T, 2>(P.spec, x);
+    else if (sp) spectral2d<T, D>(P.spec, x, b);
   }
   if (!(sp & 1)) b[0] = field_base<T, DIM, D>(P.alpha, x);
   if (!(sp & 2)) b[1] = field_base<T, DIM, D>(P.psi, x);
@@ -1270,10 +1322,12 @@ template <typename T, int DIM>
 __device__ __forceinline__ T point_gamma(G<DevProblem<T>>& P, const T* x) {
   T lnal, ps = P.psi.c0;
   const bool has_psi = !(P.psi.base == FB_NONE && P.psi.transform == FT_AFFINE);
-  if (DIM == 2 && P.spectral) {
+  if (DIM == 2 && (P.spectral & 3)) {
     FV<T, DIM> base[3];
-    if constexpr (DIM == 2) spectral2d<T, false>(P.spec, x, base);
-    if (P.spectral & kSpecGammaMerged) return base[0].v;
+    if constexpr (DIM == 2) {
+      if (P.spectral & kSpecGammaMerged) return spectral2d_value<T, 0>(P.spec, x);
+      spectral2d<T, false>(P.spec, x, base);
+    }
     if (!(P.spectral & 1)) base[0] = field_base<T, DIM, false>(P.alpha, x);
     if (has_psi && !(P.spectral & 2)) base[1] = field_base<T, DIM, false>(P.psi, x);
     const FV<T, DIM> al = field_transform<T, DIM, false>(P.alpha, base[0], &lnal);
@@ -1384,10 +1438,10 @@ constexpr int kPrimStride3 = 12;   // triangle: a, b, c, (pad)
 constexpr int kStackDepth = 48;     // private (scratch) stack: any tree the host accepts
 // LDS stack depths of the walker. The walker's LDS must leave room for five 256-thread
 // blocks per CU: the mesh walker takes trees of depth <= 15 (30 KB in FP32), the polygon
-// walker, whose candidate grid answers most queries, trees of depth <= 12 (24 KB; up to
-// about 8000 edges). Deeper trees use the private stack.
+// walker, whose candidate grid answers most queries, trees of depth <= 11 (22 KB; up to
+// 8192 edges). Deeper trees use the private stack.
 constexpr int kLdsStackDepth = 15;
-constexpr int kLdsStackDepthPolygon = 12;
+constexpr int kLdsStackDepthPolygon = 11;
 
 // Traversal stack of far children with their box distances, either in LDS (one column
 // per lane: entry k of lane t at k * stride + t, conflict-free) for trees of depth <= depth,

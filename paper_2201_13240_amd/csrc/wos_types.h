@@ -208,14 +208,14 @@ struct GradRecord {
   static constexpr int kStride = 1 + 3 * DIM;
 };
 
-struct LaunchParams {
-  uint64_t seed;
-  uint64_t walk_offset_add;  // added to every item's walk_offset (plan relaunches)
 // Tile queues of a launch of several items (one per XCD), and the distance of their
 // counters in 32-bit words (a cache line each).
 constexpr uint32_t kTileQueues = 8;
 constexpr uint32_t kTileQueueStride = 32;
 
+struct LaunchParams {
+  uint64_t seed;
+  uint64_t walk_offset_add;  // added to every item's walk_offset (plan relaunches)
 };
 
 }  // namespace wos

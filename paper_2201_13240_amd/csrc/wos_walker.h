@@ -34,10 +34,23 @@ __device__ __forceinline__ uint64_t uniform_u64(uint64_t v) {
   return ((uint64_t)hi << 32) | lo;
 }
 
+__device__ __forceinline__ float uniform_val(float v) { return __int_as_float(uniform_int(__float_as_int(v))); }
+__device__ __forceinline__ double uniform_val(double v) {
+  return __longlong_as_double((long long)uniform_u64((uint64_t)__double_as_longlong(v)));
+}
+
+// The lane's index formed where it is used: hoisted out of the walker's loop, it and the
+// addresses made from it would hold registers for the whole loop.
+__device__ __forceinline__ uint32_t lane_here() {
+  uint32_t m = ~0u;
+  asm volatile("" : "+s"(m));
+  return __builtin_amdgcn_mbcnt_hi(m, __builtin_amdgcn_mbcnt_lo(m, 0u));
+}
+
 // ------------------------------------------------------------------ walker
 //
 // Persistent kernel. Work is a sequence of tiles (a run of walks of one point, or whole
-// points; see DevItem); a wavefront takes one tile at a time with a single atomic and hands
+// points; see DevItem); a wavefront takes one tile at a time (TileQueues) and hands
 // its walks to idle lanes (ballot + mbcnt), so lanes whose walk ends pick up a new walk at
 // the next step instead of idling until the longest walk of the wave finishes. A wave only
 // switches to a tile of another item (another problem) once all its lanes are idle, so the
@@ -61,6 +74,7 @@ struct WalkerArgs {
   const DevItem* items;
   int32_t n_items;
   uint32_t n_tiles;      // tiles of all items
+  uint32_t n_queues;     // queues they are cut into (TileQueues)
   uint32_t* tile_counter;
   uint64_t* slots;       // accumulation slots (slot_words words each)
   int32_t slot_words;
@@ -74,21 +88,7 @@ struct WalkerArgs {
   T ww_hi;               // > 0: expected-value splitting above this weight (delta tracking)
   T* grad;               // [grid lane][GradRecord<DIM>::kStride] or null: gradient records
   uint64_t* events;      // event-counting build only: [kEvents]
-  uint32_t n_queues;     // queues they are cut into (TileQueues)
 };
-
-// Events counted by the event-counting build of the walker (algorithmic work per step).
-enum Event {
-  EV_STEPS = 0, EV_NODES, EV_PRIMS, EV_TRIALS, EV_TRIALS_FREE, EV_VOLUME, EV_EXIT, EV_TERMINAL,
-  EV_GAMMA, EV_WALKS, EV_RR_TESTS, EV_BALL_LARGE_S, EV_CELLS, EV_LANE_ITERS, EV_ACTIVE_LANES, EV_COEF_LANES,
-  kEvents
-};
-
-constexpr uint32_t kFlagCapped = 1u << 31;
-constexpr uint32_t kFlagRR = 1u << 30;
-constexpr uint32_t kStepMask = (1u << 30) - 1;
-
-__device__ __forceinline__ const void* uniform_ptr(const void* p) { return (const void*)uniform_u64((uint64_t)p); }
 
 // The launch's tiles in one queue, or in kTileQueues equal runs, one for each XCD. A wave
 // takes its first tile of its own queue by its place in the grid, so that a launch does not
@@ -135,6 +135,19 @@ struct TileQueues {
     return -1;
   }
 };
+
+// Events counted by the event-counting build of the walker (algorithmic work per step).
+enum Event {
+  EV_STEPS = 0, EV_NODES, EV_PRIMS, EV_TRIALS, EV_TRIALS_FREE, EV_VOLUME, EV_EXIT, EV_TERMINAL,
+  EV_GAMMA, EV_WALKS, EV_RR_TESTS, EV_BALL_LARGE_S, EV_CELLS, EV_LANE_ITERS, EV_ACTIVE_LANES, EV_COEF_LANES,
+  kEvents
+};
+
+constexpr uint32_t kFlagCapped = 1u << 31;
+constexpr uint32_t kFlagRR = 1u << 30;
+constexpr uint32_t kStepMask = (1u << 30) - 1;
+
+__device__ __forceinline__ const void* uniform_ptr(const void* p) { return (const void*)uniform_u64((uint64_t)p); }
 
 // A walk split by the weight window resumes its pending sibling branches from this state.
 constexpr int kSplitDepth = 4;
@@ -263,8 +276,9 @@ struct SlotCache {
     for (int w = (int)lane; w < ENTRIES * WORDS; w += 64) lds[w] = 0;
   }
   // Adds entry e (wave-uniform) into its global slot t and clears it.
-  __device__ __forceinline__ void flush(int e, uint32_t t, uint64_t* slots, int slot_words, uint32_t lane) {
+  __device__ __forceinline__ void flush(int e, uint32_t t, uint64_t* slots, int slot_words) {
     if (t == ~0u) return;
+    const uint32_t lane = lane_here();
     for (int w = (int)lane; w < slot_words; w += 64) {
       const uint64_t v = lds[e * WORDS + w];
       if (v) GlobalAdd::add(slots + (size_t)t * slot_words + w, v);
@@ -273,25 +287,26 @@ struct SlotCache {
   }
   // Entry for a new single-point tile with global slot `slot`; returns the reference its
   // walks carry. `ref` is the calling lane's current reference, rewritten if it pointed
-  // into the entry taken over.
-  __device__ __forceinline__ uint32_t take(uint32_t slot, uint64_t* slots, int slot_words, uint32_t lane,
-                                           uint32_t& ref) {
+  // into the entry taken over; *held receives the global slot that the entry held.
+  __device__ __forceinline__ uint32_t take(uint32_t slot, uint64_t* slots, int slot_words, uint32_t& ref,
+                                           uint32_t* held) {
     const int e = (int)next;
     uint32_t t = ~0u;
 #pragma unroll
     for (int c = 0; c < ENTRIES; ++c)
       if (c == e) t = tag[c];
-    flush(e, t, slots, slot_words, lane);
+    flush(e, t, slots, slot_words);
     if (ref == (kCachedSlot | (uint32_t)e)) ref = t;
 #pragma unroll
     for (int c = 0; c < ENTRIES; ++c)
       if (c == e) tag[c] = slot;
     next = next + 1 == (uint32_t)ENTRIES ? 0u : next + 1;
+    *held = t;
     return kCachedSlot | (uint32_t)e;
   }
-  __device__ __forceinline__ void flush_all(uint64_t* slots, int slot_words, uint32_t lane) {
+  __device__ __forceinline__ void flush_all(uint64_t* slots, int slot_words) {
 #pragma unroll
-    for (int e = 0; e < ENTRIES; ++e) flush(e, tag[e], slots, slot_words, lane);
+    for (int e = 0; e < ENTRIES; ++e) flush(e, tag[e], slots, slot_words);
   }
   // Adds a finished walk into the slot it references.
   template <int GD>
@@ -303,54 +318,83 @@ struct SlotCache {
   }
 };
 
-// A wavefront's queue of finished walks in LDS: estimate, distance queries with flags, and
-// slot reference. Lanes whose walk ended append their result (ballot + mbcnt, one LDS
-// store each); the whole wave adds the queued results into their slots, one per lane,
-// when the queue cannot take an iteration's walks, before a new single-point tile takes
-// over a slot-cache entry (queued references must still be valid), and at the end. The
-// integer adds then run on up to 64 lanes at once instead of inside the divergent branch
-// of the few lanes that ended, which would hold up the whole wave at almost every
-// iteration. Called with every lane active.
-template <int CAP>
+// A wavefront's queue of finished walks in LDS: estimate, distance queries with flags, slot
+// reference, and for a walk that ended in the epsilon shell its last point with the
+// primitive nearest to it and the weight of its boundary term. Lanes whose walk ended
+// append an entry (ballot + mbcnt); the whole wave finishes the queued walks, one per lane,
+// when the queue is full or no lane runs a walk (before the wave turns to another item, and
+// at its end): boundary point, boundary value, and the integer adds into their slots. About
+// three lanes of a wave end a walk in each iteration, so work done where they end holds up
+// the other 61: with the boundary terms evaluated there, they took 3600 of an iteration's
+// 26,800 cycles on the star polygon. The terms are the same, in the same order, so the
+// estimates are too. Called with every lane active.
+constexpr int32_t kNoBoundary = -1;   // `prim` of a walk without a boundary term
+
+template <typename T, int DIM, int CAP>
 struct EmitQueue {
-  double* v;       // [CAP] estimates
+  static constexpr bool kComp = sizeof(T) == 4;   // only the FP32 walk carries a compensation
+  static constexpr int kBytes = CAP * (int)(8 + 4 + sizeof(T) * (DIM + 2 + (kComp ? 1 : 0)));
   uint2* meta;     // [CAP] (steps | flags, slot reference)
+  T* val;          // [DIM + 2 or 3][CAP]: last point, weight, estimate, its compensation
+  int32_t* prim;   // [CAP]
   uint32_t n;      // queued entries; wave-uniform
 
-  __device__ __forceinline__ void init(double* vb, uint2* mb) {
-    v = vb;
-    meta = mb;
+  __device__ __forceinline__ void init(unsigned char* base) {
+    meta = (uint2*)base;
+    val = (T*)(meta + CAP);
+    prim = (int32_t*)(val + CAP * (DIM + 2 + (kComp ? 1 : 0)));
     n = 0;
   }
-  template <int WORDS, int ENTRIES>
-  __device__ __forceinline__ void drain(SlotCache<WORDS, ENTRIES>& cache, uint64_t* slots, int slot_words,
-                                        uint32_t lane) {
-    if (n == 0) return;
+  // Appends the calling lane's walk if it ended and fits; returns whether it was taken.
+  __device__ __forceinline__ bool push(bool ended, bool boundary, const T* x, int p, T w, T A, T Ac,
+                                       uint32_t steps_flags, uint32_t ref) {
+    const uint64_t fin = __ballot(ended);
+    const uint32_t r = n + lanes_below(fin);
+    const bool taken = ended && r < (uint32_t)CAP;
+    if (taken) {
+      meta[r] = make_uint2(steps_flags, ref);
+      prim[r] = boundary ? p : kNoBoundary;
+#pragma unroll
+      for (int i = 0; i < DIM; ++i) val[i * CAP + r] = x[i];
+      val[DIM * CAP + r] = w;
+      val[(DIM + 1) * CAP + r] = A;
+      if constexpr (kComp) val[(DIM + 2) * CAP + r] = Ac;
+    }
+    n = (uint32_t)uniform_int((int)min(n + (uint32_t)__popcll(fin), (uint32_t)CAP));
+    return taken;
+  }
+  // A slot-cache entry was taken over: queued references to it become references to the
+  // global slot it held.
+  __device__ __forceinline__ void retarget(uint32_t from, uint32_t to) {
+    const uint32_t lane = lane_here();
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    if (lane < n && meta[lane].y == from) meta[lane].y = to;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  }
+  template <int GEOM, int WORDS, int ENTRIES>
+  __device__ __forceinline__ void drain(G<DevProblem<T>>& P, int compensated, SlotCache<WORDS, ENTRIES>& cache,
+                                        uint64_t* slots, int slot_words) {
+    const uint32_t lane = lane_here();
     // entries were written by other lanes of this wave: keep the compiler from moving
     // the reads above those LDS stores (the wave's LDS operations run in order)
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     if (lane < n) {
-      const double val = v[lane];
       const uint2 m = meta[lane];
-      cache.template emit<0>(m.y, slots, slot_words, val, m.x, kStepMask, kFlagCapped, kFlagRR, nullptr);
+      const int32_t p = prim[lane];
+      T A = val[(DIM + 1) * CAP + lane], Ac = 0;
+      if constexpr (kComp) Ac = val[(DIM + 2) * CAP + lane];
+      if (p != kNoBoundary) {
+        T x[DIM], xb[DIM];
+#pragma unroll
+        for (int i = 0; i < DIM; ++i) x[i] = val[i * CAP + lane];
+        closest_point<T, DIM, GEOM>(P.geom, x, p, xb);
+        add_estimate(A, Ac, val[DIM * CAP + lane] * boundary_value<T, DIM>(P, xb), compensated);
+      }
+      cache.template emit<0>(m.y, slots, slot_words, (double)A + (double)Ac, m.x, kStepMask, kFlagCapped, kFlagRR,
+                             nullptr);
     }
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     n = 0;
-  }
-  // Appends the results of the lanes in `fin` (the calling lane's if `mine`), draining
-  // first if they do not fit.
-  template <int WORDS, int ENTRIES>
-  __device__ __forceinline__ void push(uint64_t fin, bool mine, double val, uint32_t steps_flags, uint32_t ref,
-                                       SlotCache<WORDS, ENTRIES>& cache, uint64_t* slots, int slot_words,
-                                       uint32_t lane) {
-    const uint32_t nf = (uint32_t)__popcll(fin);
-    if (n + nf > (uint32_t)CAP) drain(cache, slots, slot_words, lane);
-    if (mine) {
-      const uint32_t r = n + lanes_below(fin);
-      v[r] = val;
-      meta[r] = make_uint2(steps_flags, ref);
-    }
-    n += nf;
   }
 };
 
@@ -377,29 +421,31 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
   constexpr bool EXTRA = MODE == 1;
   const uint32_t lane = __lane_id();
   constexpr int kStack = GEOM == GK_POLYGON ? kLdsStackDepthPolygon : kLdsStackDepth;
-  LdsStack<T> lds_stack{nullptr, nullptr, 0, 0};
-  if constexpr (GEOM == GK_POLYGON || GEOM == GK_TRIMESH) {
-    __shared__ int32_t s_node[kStack * 256];
-    __shared__ T s_dist[kStack * 256];
-    lds_stack = LdsStack<T>{s_node + threadIdx.x, s_dist + threadIdx.x, (int)blockDim.x, kStack};
-  }
+  constexpr bool kHasStack = GEOM == GK_POLYGON || GEOM == GK_TRIMESH;
+  __shared__ int32_t s_node[kHasStack ? kStack * 256 : 1];
+  __shared__ T s_dist[kHasStack ? kStack * 256 : 1];
+  const int wave = uniform_int((int)(threadIdx.x >> 6));
+  // the lane's column of the stack
+  auto lds_stack = [&]() {
+    if constexpr (!kHasStack) return LdsStack<T>{nullptr, nullptr, 0, 0};
+    const uint32_t c = (uint32_t)wave * 64u + lane_here();
+    return LdsStack<T>{s_node + c, s_dist + c, (int)blockDim.x, kStack};
+  };
   // LDS cache of accumulation slots: gradient slots are larger, so fewer entries
   constexpr int kCacheWords = EXTRA ? 64 : 16;
   constexpr int kCacheEntries = EXTRA ? 2 : 4;
   __shared__ uint64_t s_slot_cache[4 * kCacheEntries * kCacheWords];
   SlotCache<kCacheWords, kCacheEntries> cache;
-  cache.init(s_slot_cache + uniform_int((int)(threadIdx.x >> 6)) * (kCacheEntries * kCacheWords), lane);
+  cache.init(s_slot_cache + wave * (kCacheEntries * kCacheWords), lane);
   // queue of finished walks (not with gradient records, whose results come from a
-  // per-lane record; not for meshes, whose LDS stacks leave no room at five blocks per CU)
+  // per-lane record; not for meshes, whose LDS stacks leave no room at five blocks per CU;
+  // 56 entries are what five blocks of the FP32 polygon walker leave room for)
   constexpr bool kQueue = MODE != 1 && GEOM != GK_TRIMESH;
-  constexpr int kQueueCap = 64;
-  __shared__ double s_queue_v[kQueue ? 4 * kQueueCap : 1];
-  __shared__ uint2 s_queue_m[kQueue ? 4 * kQueueCap : 1];
-  EmitQueue<kQueueCap> queue;
-  if constexpr (kQueue) {
-    const int w = uniform_int((int)(threadIdx.x >> 6));
-    queue.init(s_queue_v + w * kQueueCap, s_queue_m + w * kQueueCap);
-  }
+  constexpr int kQueueCap = (sizeof(T) == 4 && GEOM == GK_POLYGON) ? 56 : 64;
+  using Queue = EmitQueue<T, DIM, kQueueCap>;
+  __shared__ __align__(16) unsigned char s_queue[kQueue ? 4 * Queue::kBytes : 16];
+  Queue queue;
+  if constexpr (kQueue) queue.init(s_queue + wave * Queue::kBytes);
   Tally tally = {0, 0, 0, 0};
   uint32_t ev[kEvents];
   if constexpr (COUNT) {
@@ -412,14 +458,20 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
   // (walks res_next .. res_end - 1 of it: point tl_p0 + (tl_j0 + r) / walks), the next
   // claimed tile, and the item searched for it (a queue's tiles come in increasing order)
   int cur_item = -1, search_item = 0;
+  TileQueues tiles;
+  tiles.init(a.n_tiles, a.n_queues);
   uint32_t res_next = 0, res_end = 0;
   uint32_t tl_p0 = 0, tl_j0 = 0, tl_slot0 = 0, tl_walks = 1, tl_single = 1;
+  T tl_x[DIM], tl_gamma0 = 0;   // start of the walks of a single-point tile
+#pragma unroll
+  for (int i = 0; i < DIM; ++i) tl_x[i] = 0;
   int64_t pend_tile = -1;
   bool queue_done = false;
   const WOS_GLOBAL DevProblem<T>* Pp = nullptr;
   // ---- lane state: phase 0 = idle, 1 = new walk whose gamma(x0) and its gradient are still
   // to be evaluated (gradient records only), 2 = walking (3: next flight inside a ball),
-  // 4 = ended, its result still to be added; slot: accumulation slot of the walk
+  // 4 = ended, its result still to be added, 5 = the same with a boundary term at x, nearest
+  // to last_prim, of weight Pi; slot: accumulation slot of the walk
   int phase = 0;
   uint32_t slot = 0;
   T* const grad_rec = EXTRA && a.grad ? a.grad + ((size_t)blockIdx.x * blockDim.x + threadIdx.x) * GradRecord<DIM>::kStride
@@ -432,6 +484,7 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
   int last_prim = -1;   // closest primitive of the previous step (bounds the next query)
   Rng rng;
   rng.set_key(seed);
+  rng.problem = 0;
   // next flight (phase 3 = inside the unrolled series of a ball): exit point z and current
   // inner point, both relative to the ball centre x; the series T and S of the ball, the
   // throughput, the ball radius and its 2D kernel constant. Pi holds prod_k T_k.
@@ -458,13 +511,12 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
     // ---------------------------------------------------------------- finished walks
     // A walk that ended in the last iteration adds its estimate A + Ac, its square, its
     // distance queries and flags (in nsteps) to its slot here, where little else is live.
-  TileQueues tiles;
-  tiles.init(a.n_tiles, a.n_queues);
     if constexpr (kQueue) {
-      const uint64_t fin = __ballot(phase == 4);
-      if (fin) {
-        queue.push(fin, phase == 4, (double)A + (double)Ac, nsteps, slot, cache, slots, a.slot_words, lane);
-        if (phase == 4) phase = 0;
+      for (;;) {
+        if (queue.push(phase >= 4, phase == 5, x, last_prim, Pi, A, Ac, nsteps, slot)) phase = 0;
+        if (queue.n == 0u || (queue.n < (uint32_t)kQueueCap && __ballot(phase != 0) != 0)) break;
+        queue.template drain<GEOM>(*Pp, a.compensated, cache, slots, a.slot_words);
+        if (__ballot(phase >= 4) == 0) break;
       }
     } else if (phase == 4) {
       const double v = (double)A + (double)Ac;
@@ -503,6 +555,7 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
           if (cur_item >= 0) flush_trials(items[cur_item].counters, ntrials, COUNT ? &ev[EV_TRIALS] : nullptr);
           cur_item = uniform_int(search_item);
           Pp = (const WOS_GLOBAL DevProblem<T>*)uniform_ptr(items[cur_item].problem);
+          if constexpr (!EXTRA) rng.problem = (uint32_t)uniform_int((int)items[cur_item].problem_index);
         }
         // the tile's walks, from the item's regular cut (DevItem)
         G<DevItem>& it = items[cur_item];
@@ -527,8 +580,21 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
         tl_slot0 = uniform_int((int)(it.slot_base + (it.tiles_per_point > 0u ? tl : (uint64_t)tl_p0)));
         tl_walks = uniform_int((int)walks);
         if (tl_single) {
-          if constexpr (kQueue) queue.drain(cache, slots, a.slot_words, lane);
-          tl_slot0 = uniform_int((int)cache.take(tl_slot0, slots, a.slot_words, lane, slot));
+          // every walk of the tile starts at one point, read here once (scalar loads); a
+          // point outside the domain runs no walk: the reduction marks its sums
+          const uint64_t in = (uint64_t)it.inside + tl_p0;
+          const uint32_t word = *(const WOS_GLOBAL uint32_t*)(in & ~3ull);
+          if ((word >> (8u * ((uint32_t)in & 3u)) & 0xFFu) == 0u) {
+            res_end = 0;
+          } else {
+            uint32_t held;
+            const uint32_t ref = cache.take(tl_slot0, slots, a.slot_words, slot, &held);
+            if constexpr (kQueue) queue.retarget(ref, held);
+            tl_slot0 = uniform_int((int)ref);
+#pragma unroll
+            for (int i = 0; i < DIM; ++i) tl_x[i] = uniform_val((T)gptr(it.points)[(size_t)tl_p0 * DIM + i]);
+            tl_gamma0 = uniform_val(gptr((const WOS_GLOBAL T*)it.gamma0)[tl_p0]);
+          }
         }
         res_next = 0;
         pend_tile = -1;
@@ -554,10 +620,19 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
           slot = tl_slot0 + dq;
         }
         nsteps = 0;
-        if (gptr(it.inside)[p]) {
+        T g0 = tl_gamma0;
+#pragma unroll
+        for (int i = 0; i < DIM; ++i) x[i] = tl_x[i];
+        bool in = true;
+        if (!tl_single) {
+          in = gptr(it.inside)[p] != 0;
+          g0 = gptr((const WOS_GLOBAL T*)it.gamma0)[p];
 #pragma unroll
           for (int i = 0; i < DIM; ++i) x[i] = (T)gptr(it.points)[(size_t)p * DIM + i];
-          rng.init((uint32_t)(it.walk_offset + offset_add + j), p, it.problem_index);
+        }
+        if (in) {
+          rng.start((uint32_t)(it.walk_offset + offset_add + j), p);
+          if constexpr (EXTRA) rng.problem = it.problem_index;   // split branches change it
           Pi = 1;
           A = 0;
           Ac = 0;
@@ -568,7 +643,7 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
             phase = 1;   // gamma(x0) with its gradient, for the gradient record
             if constexpr (COUNT) ++ev[EV_GAMMA];
           } else {
-            gamma0 = gptr((const WOS_GLOBAL T*)it.gamma0)[p];
+            gamma0 = g0;
             gx = gamma0;
             gx_known = true;
             phase = 2;
@@ -635,16 +710,18 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
             flag = kFlagCapped;
           } else {
             int prim;
-            const T d = boundary_distance<T, DIM, GEOM, COUNT, true>(P.geom, x, &prim, &tally, lds_stack, last_prim);
+            const T d = boundary_distance<T, DIM, GEOM, COUNT, true>(P.geom, x, &prim, &tally, lds_stack(), last_prim);
             last_prim = prim;
             ++nsteps;
             if (!(d == d)) {
               done = true;
               flag = kFlagCapped;
             } else if (d < P.epsilon) {
-              T xb[DIM];
-              closest_point<T, DIM, GEOM>(P.geom, x, prim, xb);
-              gb = boundary_value<T, DIM>(P, xb);
+              if constexpr (!kQueue) {
+                T xb[DIM];
+                closest_point<T, DIM, GEOM>(P.geom, x, prim, xb);
+                gb = boundary_value<T, DIM>(P, xb);
+              }
               terminal = true;
               if constexpr (COUNT) {
                 ++ev[EV_TERMINAL];
@@ -687,7 +764,8 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
           gamma0 = cq.gamma;
           phase = 2;
         } else if (terminal) {
-          add_estimate(A, Ac, Pi * m_exp(cq.gamma - gamma0) * gb, a.compensated);
+          Pi *= m_exp(cq.gamma - gamma0);
+          if constexpr (!kQueue) add_estimate(A, Ac, Pi * gb, a.compensated);
           done = true;
         } else if (sample) {
           const NfBall<T, DIM> nb = nf_ball<T, DIM>(nf_R, P.sqrt_sigma_bar, nf_c);
@@ -701,7 +779,7 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
         }
         if (done) {
           nsteps = (nsteps & kStepMask) | flag;
-          phase = 4;   // added to its slot at the top of the next iteration
+          phase = kQueue && terminal ? 5 : 4;   // added to its slot at the top of the next iteration
         }
       } else {
         bool done = false, terminal = false, sampled = false;
@@ -728,7 +806,7 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
             flag = kFlagCapped;
           } else {
             int prim;
-            const T d = boundary_distance<T, DIM, GEOM, COUNT, true>(P.geom, x, &prim, &tally, lds_stack, last_prim);
+            const T d = boundary_distance<T, DIM, GEOM, COUNT, true>(P.geom, x, &prim, &tally, lds_stack(), last_prim);
             last_prim = prim;
             ++nsteps;
             if (!(d == d)) {
@@ -737,10 +815,12 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
               flag = kFlagCapped;
             } else if (d < P.epsilon) {
               // epsilon shell: the walk returns g(xbar) (Alg. 1) times its weight, which
-              // needs gamma at the current point
-              T xb[DIM];
-              closest_point<T, DIM, GEOM>(P.geom, x, prim, xb);
-              gb = boundary_value<T, DIM>(P, xb);
+              // needs gamma at the current point (g(xbar) itself is taken from the queue)
+              if constexpr (!kQueue) {
+                T xb[DIM];
+                closest_point<T, DIM, GEOM>(P.geom, x, prim, xb);
+                gb = boundary_value<T, DIM>(P, xb);
+              }
               terminal = true;
               if constexpr (COUNT) {
                 ++ev[EV_TERMINAL];
@@ -811,7 +891,8 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
             }
           }
         } else if (terminal) {
-          add_estimate(A, Ac, pe * gb, a.compensated);
+          if constexpr (kQueue) Pi = pe;
+          else add_estimate(A, Ac, pe * gb, a.compensated);
           done = true;
         } else if (sampled) {
           const T mu = uniform01<T, SL::kMu>(rng);
@@ -922,15 +1003,14 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
             rng.init(rng.walk, rng.point, (rng.problem & 0xFFFFu) | ((split_state >> 8) << 16));
             pending = false;
           } else {
-            phase = 4;   // added to its slot at the top of the next iteration
+            phase = kQueue && terminal ? 5 : 4;   // added to its slot at the top of the next iteration
           }
         }
       }
     }
   }
   if (cur_item >= 0) flush_trials(items[cur_item].counters, ntrials, COUNT ? &ev[EV_TRIALS] : nullptr);
-  if constexpr (kQueue) queue.drain(cache, slots, a.slot_words, lane);
-  cache.flush_all(slots, a.slot_words, lane);
+  cache.flush_all(slots, a.slot_words);
   if constexpr (COUNT) {
     ev[EV_NODES] = tally.nodes;
     ev[EV_PRIMS] = tally.prims;
@@ -984,6 +1064,7 @@ static hipError_t launch_walker_t(const WalkerLaunch& L, hipStream_t st) {
   a.items = L.items;
   a.n_items = L.n_items;
   a.n_tiles = L.n_tiles;
+  a.n_queues = L.n_queues;
   a.tile_counter = L.tile_counter;
   a.slots = L.slots;
   a.slot_words = L.slot_words;
@@ -1057,4 +1138,3 @@ static const void* walker_symbol_td(int geom, int mode) {
 }
 
 }  // namespace wos
-  a.n_queues = L.n_queues;
