@@ -70,8 +70,8 @@ int wos_version(void);
  *           x - f(x) grad f(x) with the gradient of the row that decides f. Components
  *           beyond dim are ignored. lo[dim], hi[dim]: a box that holds the (bounded)
  *           domain, used to sample sigma'.
- * Polygons and meshes get an axis-aligned BVH (Sec. 7.1) and a candidate grid in front
- * of it, built on the host (for meshes with up to 16 threads). Where a grid cell's
+ * Polygons and meshes get an axis-aligned BVH (Sec. 7.1), built on the host, and a
+ * candidate grid in front of it, built on the device. Where a grid cell's
  * truncated list cannot decide the nearest primitive (mostly deep inside a mesh or a
  * large polygon), the walk's ball radius may be a certified lower bound of the distance,
  * at least 2 epsilon and a quarter of the cell size: every ball stays inside the

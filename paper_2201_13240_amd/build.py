@@ -15,7 +15,7 @@ ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 # The walker is instantiated per precision and dimension in four translation units, which
 # compile in parallel with the rest.
 SOURCES = ["wos_walker_f64_3d.hip", "wos_walker_f64_2d.hip", "wos_walker_f32_3d.hip", "wos_walker_f32_2d.hip",
-           "wos_kernels.hip", "wos_api.cpp", "bvh.cpp"]
+           "wos_kernels.hip", "wos_grid.hip", "wos_api.cpp", "bvh.cpp"]
 HEADERS = ["wos_walker.h", "wos_device.h", "wos_types.h", "wos_launch.h", "bvh.h", "bessel_tables.h",
            "proposal_bound.h"]
 

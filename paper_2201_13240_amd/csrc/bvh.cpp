@@ -218,10 +218,8 @@ struct TriQuery {
 
 }  // namespace
 
-SegmentGrid build_segment_grid(const std::vector<double>& segs, int64_t n, const BvhTopology& topo,
-                               const std::vector<double>& bounds, int64_t target_cells, double margin,
-                               int max_candidates, int deep_list) {
-  SegmentGrid g;
+GridShape segment_grid_shape(const std::vector<double>& segs, int64_t n, int64_t target_cells) {
+  GridShape g;
   double lo[2] = {1e300, 1e300}, hi[2] = {-1e300, -1e300};
   for (int64_t i = 0; i < n; ++i)
     for (int v = 0; v < 2; ++v)
@@ -244,7 +242,77 @@ SegmentGrid build_segment_grid(const std::vector<double>& segs, int64_t n, const
   g.lo[0] = lo[0];
   g.lo[1] = lo[1];
   g.h = h;
-  const double halfdiag = 0.5 * h * std::sqrt(2.0);
+  return g;
+}
+
+GridShape triangle_grid_shape(const std::vector<double>& tris, int64_t n, int64_t target_cells) {
+  GridShape g;
+  double lo[3] = {1e300, 1e300, 1e300}, hi[3] = {-1e300, -1e300, -1e300};
+  for (int64_t i = 0; i < n; ++i)
+    for (int v = 0; v < 3; ++v)
+      for (int k = 0; k < 3; ++k) {
+        lo[k] = std::min(lo[k], tris[12 * i + 3 * v + k]);
+        hi[k] = std::max(hi[k], tris[12 * i + 3 * v + k]);
+      }
+  double ext = 0, vol = 1;
+  for (int k = 0; k < 3; ++k) ext = std::max(ext, hi[k] - lo[k]);
+  const double pad = 1e-6 * ext + 1e-12;
+  for (int k = 0; k < 3; ++k) {
+    lo[k] -= pad;
+    vol *= hi[k] - lo[k] + pad;
+  }
+  // a nearly flat set (degenerate input) would make the cells tiny: coarsen until the
+  // grid holds at most twice the target
+  double h = std::cbrt(vol / (double)target_cells);
+  auto n_cells = [&](double hh) {
+    double c = 1;
+    for (int k = 0; k < 3; ++k) c *= std::max(1.0, std::ceil((hi[k] - lo[k] + pad) / hh));
+    return c;
+  };
+  while (n_cells(h) > 2.0 * (double)target_cells) h *= 1.25;
+  int32_t nn[3];
+  for (int k = 0; k < 3; ++k) {
+    nn[k] = std::max(1, (int32_t)std::ceil((hi[k] - lo[k] + pad) / h));
+    g.lo[k] = lo[k];
+  }
+  g.nx = nn[0];
+  g.ny = nn[1];
+  g.nz = nn[2];
+  g.h = h;
+  return g;
+}
+
+double cell_halfdiag(const GridShape& s, int dim) { return 0.5 * s.h * std::sqrt((double)dim); }
+
+double deep_distance(const GridShape& s) { return 8 * s.h; }
+
+bool closed_mesh(const int32_t* triangles, int64_t n) {
+  auto mix = [](uint64_t z) {   // splitmix64
+    z += 0x9E3779B97F4A7C15ull;
+    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+    return z ^ (z >> 31);
+  };
+  uint64_t s0 = 0, s1 = 0;
+  for (int64_t j = 0; j < n; ++j)
+    for (int e = 0; e < 3; ++e) {
+      const uint32_t a = (uint32_t)triangles[3 * j + e], b = (uint32_t)triangles[3 * j + (e + 1) % 3];
+      if (a == b) continue;
+      const uint64_t key = (uint64_t)std::min(a, b) << 32 | std::max(a, b);
+      const uint64_t h0 = mix(key), h1 = mix(h0 ^ 0xD1B54A32D192ED03ull);
+      s0 += a < b ? h0 : 0 - h0;
+      s1 += a < b ? h1 : 0 - h1;
+    }
+  return s0 == 0 && s1 == 0;
+}
+
+SegmentGrid build_segment_grid(const std::vector<double>& segs, int64_t n, const BvhTopology& topo,
+                               const std::vector<double>& bounds, int64_t target_cells, double margin,
+                               int max_candidates, int deep_list) {
+  SegmentGrid g;
+  static_cast<GridShape&>(g) = segment_grid_shape(segs, n, target_cells);
+  const double *lo = g.lo, h = g.h;
+  const double halfdiag = cell_halfdiag(g, 2);
   SegQuery q{segs, topo, bounds};
   const int64_t ncell = (int64_t)g.nx * g.ny;
   g.start.resize(ncell + 1);
@@ -278,40 +346,9 @@ SegmentGrid build_triangle_grid(const std::vector<double>& tris, int64_t n, cons
                                 const std::vector<double>& bounds, int64_t target_cells, double margin,
                                 int max_candidates, int threads) {
   SegmentGrid g;
-  double lo[3] = {1e300, 1e300, 1e300}, hi[3] = {-1e300, -1e300, -1e300};
-  for (int64_t i = 0; i < n; ++i)
-    for (int v = 0; v < 3; ++v)
-      for (int k = 0; k < 3; ++k) {
-        lo[k] = std::min(lo[k], tris[12 * i + 3 * v + k]);
-        hi[k] = std::max(hi[k], tris[12 * i + 3 * v + k]);
-      }
-  double ext = 0, vol = 1;
-  for (int k = 0; k < 3; ++k) ext = std::max(ext, hi[k] - lo[k]);
-  const double pad = 1e-6 * ext + 1e-12;
-  for (int k = 0; k < 3; ++k) {
-    lo[k] -= pad;
-    vol *= hi[k] - lo[k] + pad;
-  }
-  // a nearly flat set (degenerate input) would make the cells tiny: coarsen until the
-  // grid holds at most twice the target
-  double h = std::cbrt(vol / (double)target_cells);
-  auto n_cells = [&](double hh) {
-    double c = 1;
-    for (int k = 0; k < 3; ++k) c *= std::max(1.0, std::ceil((hi[k] - lo[k] + pad) / hh));
-    return c;
-  };
-  while (n_cells(h) > 2.0 * (double)target_cells) h *= 1.25;
-  int32_t nn[3];
-  for (int k = 0; k < 3; ++k) {
-    nn[k] = std::max(1, (int32_t)std::ceil((hi[k] - lo[k] + pad) / h));
-    g.lo[k] = lo[k];
-  }
-  g.nx = nn[0];
-  g.ny = nn[1];
-  g.nz = nn[2];
-  g.h = h;
-  const double halfdiag = 0.5 * h * std::sqrt(3.0);
-  const double deep = 8 * h;
+  static_cast<GridShape&>(g) = triangle_grid_shape(tris, n, target_cells);
+  const double *lo = g.lo, h = g.h;
+  const double halfdiag = cell_halfdiag(g, 3), deep = deep_distance(g);
   const TriQuery q{tris, topo, bounds};
   const int64_t ncell = (int64_t)g.nx * g.ny * g.nz;
   threads = (int)std::max<int64_t>(1, std::min<int64_t>(threads, (ncell + 4095) / 4096));

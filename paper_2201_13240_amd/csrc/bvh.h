@@ -1,7 +1,10 @@
-// Host construction of the axis-aligned BVH used for closest-point queries (Sec. 7.1).
+// Host construction of the axis-aligned BVH used for closest-point queries (Sec. 7.1), the
+// shapes of the candidate grids in front of it, and the reference construction of the grids.
 #pragma once
 #include <cstdint>
 #include <vector>
+
+#include "wos_types.h"
 
 namespace wos {
 
@@ -32,10 +35,7 @@ namespace wos {
 // superset of the primitives that can be nearest to any point of the cell (or within
 // `margin` of it): for p in the cell and s* nearest to p,
 // |c - s*| <= |p - s*| + halfdiag <= d(c) + 2 halfdiag.
-struct SegmentGrid {
-  int32_t nx = 0, ny = 0, nz = 1;
-  double lo[3] = {0, 0, 0};
-  double h = 0;
+struct SegmentGrid : GridShape {
   std::vector<uint32_t> start;   // [nx * ny * nz + 1], cell (i, j, k) at (k * ny + j) * nx + i
   std::vector<int32_t> prim;     // candidate indices (leaf order), nearest to the cell centre first
   std::vector<double> dc;        // distance from the cell centre to each candidate (ascending per cell)
@@ -43,6 +43,23 @@ struct SegmentGrid {
                                  // off its list (+inf: the list is complete)
 };
 
+// Cells of the grid over n segments ([n][4]) or triangles ([n][12]): about target_cells, at
+// most twice as many.
+GridShape segment_grid_shape(const std::vector<double>& segs, int64_t n, int64_t target_cells);
+GridShape triangle_grid_shape(const std::vector<double>& tris, int64_t n, int64_t target_cells);
+
+// Half diagonal of a cell, and the centre distance from which a mesh cell keeps one triangle.
+double cell_halfdiag(const GridShape& s, int dim);
+double deep_distance(const GridShape& s);
+
+// Whether a triangle set is closed: every edge is run through as often in one direction as
+// in the other, so that the winding number is constant off the surface. By a 128-bit
+// fingerprint of the signed edges, which is zero for a closed set.
+bool closed_mesh(const int32_t* triangles, int64_t n);
+
+// Reference construction of the grids on the host: what the device builds (grid_count_kernel,
+// grid_fill_kernel) is held against it.
+//
 // segs: [n][4] in leaf order; topo/bounds: the BVH over them (child bounds as produced
 // by bvh_child_bounds<double>). target_cells bounds the grid size. Each list is sorted by
 // distance from the cell centre, so a query at p can stop once dc - |p - centre| exceeds

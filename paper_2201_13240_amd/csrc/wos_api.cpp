@@ -12,7 +12,6 @@
 #include <map>
 #include <mutex>
 #include <string>
-#include <thread>
 #include <tuple>
 #include <vector>
 
@@ -76,13 +75,13 @@ struct wos_problem {
   double epsilon = 0;
   double sigma_bar = 0;
   double sp_min = NAN, sp_max = NAN;
-  void* dmem = nullptr;
+  void* dmem = nullptr;         // headers, field terms, BVH and primitives in both precisions
+  void* grid_mem = nullptr;     // candidate grid in both precisions, cell classes
   size_t off32 = 0, off64 = 0;
   int64_t n_nodes = 0, n_prims = 0;
   int32_t depth = 0;
   int32_t grid_nx = 0, grid_ny = 0, grid_nz = 0;
   int64_t grid_candidates = 0;
-  std::vector<unsigned char> staging;  // host copy of the device blob
   double geometry_ms = 0, sigma_bar_ms = 0, upload_ms = 0;   // set-up time (host wall clock)
   const void* d32() const { return (const unsigned char*)dmem + off32; }
   const void* d64() const { return (const unsigned char*)dmem + off64; }
@@ -213,8 +212,9 @@ struct HostGeometry {
   BvhTopology topo;
   std::vector<double> bounds64;      // node child bounds
   std::vector<float> bounds32;
-  SegmentGrid grid;                  // polygons and triangle meshes
-  double grid_margin = 0;            // rounding margin of the candidate lists
+  GridShape grid;                    // polygons and triangle meshes
+  GridRule rule;
+  bool closed = false;               // cells off the boundary have one class each
 };
 
 wos_status build_geometry(const wos_problem_desc& d, HostGeometry& g) {
@@ -370,9 +370,9 @@ wos_status build_geometry(const wos_problem_desc& d, HostGeometry& g) {
     double scale = 0;
     for (double c : g.prims64) scale = std::max(scale, std::fabs(c));
     const int64_t target = std::min<int64_t>(1 << 20, std::max<int64_t>(4096, 64 * n));
-    g.grid_margin = 4e-6 * (scale + 1.0);
-    g.grid = build_segment_grid(g.prims64, n, g.topo, g.bounds64, target, g.grid_margin, kPolygonCellMax,
-                                kPolygonDeepList);
+    g.grid = segment_grid_shape(g.prims64, n, target);
+    g.rule = GridRule{cell_halfdiag(g.grid, 2), 4e-6 * (scale + 1.0), HUGE_VAL, kPolygonCellMax, kPolygonDeepList};
+    g.closed = true;
   } else {
     // meshes: about 128 cells per triangle, between 32^3 and 2^21 cells, lists of the 6
     // candidates nearest to the cell centre (on the perturbed icosphere these walks ran
@@ -381,9 +381,9 @@ wos_status build_geometry(const wos_problem_desc& d, HostGeometry& g) {
     double scale = 0;
     for (double c : g.prims64) scale = std::max(scale, std::fabs(c));
     const int64_t target = std::min<int64_t>(1 << 21, std::max<int64_t>(32768, 128 * n));
-    g.grid_margin = 4e-6 * (scale + 1.0);
-    const int threads = (int)std::min<unsigned>(16, std::max<unsigned>(1, std::thread::hardware_concurrency()));
-    g.grid = build_triangle_grid(g.prims64, n, g.topo, g.bounds64, target, g.grid_margin, kMeshCellList, threads);
+    g.grid = triangle_grid_shape(g.prims64, n, target);
+    g.rule = GridRule{cell_halfdiag(g.grid, 3), 4e-6 * (scale + 1.0), deep_distance(g.grid), kMeshCellList, kMeshCellList};
+    g.closed = closed_mesh(G.triangles, n);
   }
   return WOS_OK;
 }
@@ -414,8 +414,9 @@ void write_nodes(const HostGeometry& g, const std::vector<T>& bounds, BvhNode<T,
   }
 }
 
-// Lays out DevProblem<T> and everything it points to inside the blob; pointers are
-// device addresses (dbase + offset), patched once the device allocation exists.
+// Lays out DevProblem<T> and everything it points to, except the candidate grid, inside the
+// blob; pointers are device addresses (dbase + offset), patched once the device allocation
+// exists.
 template <typename T>
 size_t layout_problem(Blob& blob, const wos_problem_desc& d, const HostGeometry& g, std::vector<std::pair<size_t, size_t>>& ptr_fixups) {
   const size_t off_struct = blob.alloc(sizeof(DevProblem<T>));
@@ -551,7 +552,7 @@ size_t layout_problem(Blob& blob, const wos_problem_desc& d, const HostGeometry&
     G.hi[i] = (T)d.geometry.hi[i];
   }
   G.radius = (T)d.geometry.radius;
-  size_t node_off = 0, prim_off = 0, grid_start_off = 0, grid_prim_off = 0, grid_seg_off = 0, grid_dc_off = 0;
+  size_t node_off = 0, prim_off = 0;
   if (g.n_prims > 0) {
     G.n_prims = (int32_t)g.n_prims;
     G.n_nodes = (int32_t)(g.topo.child.size() / 2);
@@ -564,79 +565,20 @@ size_t layout_problem(Blob& blob, const wos_problem_desc& d, const HostGeometry&
     if (d.dim == 2) {
       node_off = blob.alloc(std::max<size_t>(1, G.n_nodes) * sizeof(BvhNode<T, 2>));
       write_nodes<T, 2>(g, bounds, (BvhNode<T, 2>*)(blob.host.data() + node_off));
-      if (g.grid.nx > 0) {
-        G.grid_nx = g.grid.nx;
-        G.grid_ny = g.grid.ny;
-        G.grid_lo[0] = (T)g.grid.lo[0];
-        G.grid_lo[1] = (T)g.grid.lo[1];
-        G.grid_inv_h = (T)(1.0 / g.grid.h);
-        G.grid_h = (T)g.grid.h;
-        G.grid_lb_min = (T)std::max(0.25 * g.grid.h, 2.0 * d.epsilon);
-        const size_t nc = g.grid.prim.size();
-        const size_t ncell = g.grid.start.size() - 1;
-        grid_start_off = blob.alloc(ncell * sizeof(CellRec<T>));
-        CellRec<T>* cells = (CellRec<T>*)(blob.host.data() + grid_start_off);
-        for (size_t c = 0; c < ncell; ++c) {
-          CellRec<T> r;
-          std::memset(&r, 0, sizeof(r));
-          r.start = g.grid.start[c];
-          r.count = g.grid.start[c + 1] - g.grid.start[c];
-          r.tail = std::isfinite(g.grid.tail[c]) ? (T)(g.grid.tail[c] - g.grid_margin)
-                                                 : std::numeric_limits<T>::infinity();
-          // inline entries beyond the list repeat its last candidate: their distance equals
-          // that candidate's, so they never replace it as the nearest (strict comparison)
-          for (uint32_t k = 0; r.count > 0 && k < (uint32_t)kCellInline; ++k) {
-            const uint32_t kk = std::min<uint32_t>(k, r.count - 1);
-            const double* sg = g.prims64.data() + (size_t)g.grid.prim[r.start + kk] * 4;
-            r.seg[k][0] = (T)sg[0];
-            r.seg[k][1] = (T)sg[1];
-            r.seg[k][2] = (T)(sg[2] - sg[0]);
-            r.seg[k][3] = (T)(sg[3] - sg[1]);
-            const double ex = (double)r.seg[k][2], ey = (double)r.seg[k][3], l2 = ex * ex + ey * ey;
-            r.inv_len2[k] = l2 > 0 ? (T)(1.0 / l2) : (T)0;
-          }
-          cells[c] = r;
-        }
-        grid_prim_off = blob.alloc(std::max<size_t>(nc, 1) * sizeof(int32_t));
-        std::memcpy(blob.host.data() + grid_prim_off, g.grid.prim.data(), nc * sizeof(int32_t));
-        grid_seg_off = blob.alloc(std::max<size_t>(nc, 1) * 4 * sizeof(T));
-        T* cs = (T*)(blob.host.data() + grid_seg_off);
-        for (size_t k = 0; k < nc; ++k)
-          for (int c = 0; c < 4; ++c) cs[4 * k + c] = prims[(size_t)g.grid.prim[k] * 4 + c];
-        grid_dc_off = blob.alloc(std::max<size_t>(nc, 1) * sizeof(T));
-        T* dc = (T*)(blob.host.data() + grid_dc_off);
-        for (size_t k = 0; k < nc; ++k) dc[k] = (T)(g.grid.dc[k] - g.grid_margin);
-      }
     } else {
       node_off = blob.alloc(std::max<size_t>(1, G.n_nodes) * sizeof(BvhNode<T, 3>));
       write_nodes<T, 3>(g, bounds, (BvhNode<T, 3>*)(blob.host.data() + node_off));
-      if (g.grid.nx > 0) {
-        G.grid_nx = g.grid.nx;
-        G.grid_ny = g.grid.ny;
-        G.grid_nz = g.grid.nz;
-        for (int k = 0; k < 3; ++k) G.grid_lo[k] = (T)g.grid.lo[k];
-        G.grid_inv_h = (T)(1.0 / g.grid.h);
-        G.grid_h = (T)g.grid.h;
-        // a quarter cell: lower, the walks make more steps; higher, more queries take the
-        // BVH, which a whole wave then waits for (h: 11% slower on the perturbed icosphere)
-        G.grid_lb_min = (T)std::max(0.25 * g.grid.h, 2.0 * d.epsilon);
-        const size_t nc = g.grid.prim.size();
-        const size_t ncell = g.grid.start.size() - 1;
-        grid_start_off = blob.alloc(ncell * sizeof(MeshCell<T>));
-        MeshCell<T>* cells = (MeshCell<T>*)(blob.host.data() + grid_start_off);
-        for (size_t c = 0; c < ncell; ++c) {
-          std::memset(&cells[c], 0, sizeof(MeshCell<T>));
-          cells[c].start = g.grid.start[c];
-          cells[c].count = g.grid.start[c + 1] - g.grid.start[c];
-          cells[c].tail = std::isfinite(g.grid.tail[c]) ? (T)(g.grid.tail[c] - g.grid_margin)
-                                                        : std::numeric_limits<T>::infinity();
-        }
-        grid_prim_off = blob.alloc(std::max<size_t>(nc, 1) * sizeof(int32_t));
-        std::memcpy(blob.host.data() + grid_prim_off, g.grid.prim.data(), nc * sizeof(int32_t));
-        grid_dc_off = blob.alloc(std::max<size_t>(nc, 1) * sizeof(T));
-        T* dc = (T*)(blob.host.data() + grid_dc_off);
-        for (size_t k = 0; k < nc; ++k) dc[k] = (T)(g.grid.dc[k] - g.grid_margin);
-      }
+    }
+    if (g.grid.nx > 0) {
+      G.grid_nx = g.grid.nx;
+      G.grid_ny = g.grid.ny;
+      G.grid_nz = d.dim == 3 ? g.grid.nz : 0;
+      for (int k = 0; k < d.dim; ++k) G.grid_lo[k] = (T)g.grid.lo[k];
+      G.grid_inv_h = (T)(1.0 / g.grid.h);
+      G.grid_h = (T)g.grid.h;
+      // a quarter cell: lower, the walks make more steps; higher, more queries take the
+      // BVH, which a whole wave then waits for (h: 11% slower on the perturbed icosphere)
+      G.grid_lb_min = (T)std::max(0.25 * g.grid.h, 2.0 * d.epsilon);
     }
   }
   std::memcpy(blob.host.data() + off_struct, &P, sizeof(P));
@@ -651,22 +593,80 @@ size_t layout_problem(Blob& blob, const wos_problem_desc& d, const HostGeometry&
     const size_t gbase = off_struct + offsetof(DevProblem<T>, geom);
     ptr_fixups.push_back({gbase + offsetof(DevGeometry<T>, nodes), node_off});
     ptr_fixups.push_back({gbase + offsetof(DevGeometry<T>, prims), prim_off});
-    if (g.grid.nx > 0) {
-      ptr_fixups.push_back({gbase + offsetof(DevGeometry<T>, cells), grid_start_off});
-      ptr_fixups.push_back({gbase + offsetof(DevGeometry<T>, cell_prim), grid_prim_off});
-      if (grid_seg_off) ptr_fixups.push_back({gbase + offsetof(DevGeometry<T>, cell_segs), grid_seg_off});
-      ptr_fixups.push_back({gbase + offsetof(DevGeometry<T>, cell_dc), grid_dc_off});
-    }
   }
   return off_struct;
 }
 
 template <typename T>
-void set_sigma_bar(unsigned char* host_struct, double sb) {
-  DevProblem<T>* P = (DevProblem<T>*)host_struct;
-  P->sigma_bar = (T)sb;
-  P->inv_sigma_bar = sb > 0 ? (T)(1.0 / sb) : (T)0;
-  P->sqrt_sigma_bar = (T)std::sqrt(std::max(sb, 0.0));
+void set_sigma_bar(DevProblem<T>& P, double sb) {
+  P.sigma_bar = (T)sb;
+  P.inv_sigma_bar = sb > 0 ? (T)(1.0 / sb) : (T)0;
+  P.sqrt_sigma_bar = (T)std::sqrt(std::max(sb, 0.0));
+}
+
+// Device memory of one call, freed when it goes out of scope.
+struct DeviceScratch {
+  void* p = nullptr;
+  ~DeviceScratch() {
+    if (p) (void)hipFree(p);
+  }
+};
+
+// Builds the candidate grid of a polygon or mesh on the device (its BVH is there already):
+// list lengths, their prefix sum, one allocation of the exact size, the lists. Sets the
+// grid pointers of both headers on the host.
+hipError_t build_grid(wos_problem* p, const HostGeometry& g, DevProblem<float>& h32, DevProblem<double>& h64) {
+  const int64_t nc = g.grid.cells();
+  size_t off = 0;
+  auto take = [&off](size_t bytes) {
+    const size_t o = off;
+    off = (off + bytes + 255) / 256 * 256;
+    return o;
+  };
+  const size_t o_best = take(nc * sizeof(double)), o_near = take(nc * 4), o_count = take(nc * 4), o_start = take(nc * 4),
+               o_sums = take(scan_sum_words(nc) * 4), o_total = take(8);
+  DeviceScratch scratch;
+  hipError_t e = hipMalloc(&scratch.p, off);
+  if (e != hipSuccess) return e;
+  unsigned char* b = (unsigned char*)scratch.p;
+  double* best = (double*)(b + o_best);
+  int32_t* near = (int32_t*)(b + o_near);
+  uint32_t *count = (uint32_t*)(b + o_count), *start = (uint32_t*)(b + o_start), *total = (uint32_t*)(b + o_total);
+  e = launch_grid_count(p->dim, p->depth, p->d64(), g.grid, g.rule, best, near, count, (uint32_t*)(b + o_sums), start,
+                        total, 0);
+  uint32_t n = 0;
+  if (e == hipSuccess) e = hipMemcpy(&n, total, sizeof(n), hipMemcpyDeviceToHost);
+  if (e != hipSuccess) return e;
+  p->grid_candidates = n;
+  const bool seg = p->dim == 2;
+  const size_t r32 = seg ? sizeof(CellRec<float>) : sizeof(MeshCell<float>);
+  const size_t r64 = seg ? sizeof(CellRec<double>) : sizeof(MeshCell<double>);
+  off = 0;
+  const size_t o_c32 = take(nc * r32), o_c64 = take(nc * r64), o_prim = take((size_t)n * 4),
+               o_s32 = take(seg ? (size_t)n * 16 : 0), o_s64 = take(seg ? (size_t)n * 32 : 0), o_d32 = take((size_t)n * 4),
+               o_d64 = take((size_t)n * 8), o_cls = take(nc);
+  if ((e = hipMalloc(&p->grid_mem, off)) != hipSuccess) return e;
+  b = (unsigned char*)p->grid_mem;
+  const GridOut o{b + o_c32,           b + o_c64,           (int32_t*)(b + o_prim),
+                  (float*)(b + o_s32), (float*)(b + o_d32), (double*)(b + o_s64), (double*)(b + o_d64)};
+  if ((e = launch_grid_fill(p->dim, p->depth, p->d64(), g.grid, g.rule, best, near, start, o, 0)) != hipSuccess) return e;
+  uint8_t* cls = nullptr;
+  if (g.closed) {
+    // the counts and starts are done with: their memory takes the labels and roots
+    cls = b + o_cls;
+    e = launch_cell_classes(p->dim, p->d64(), g.grid, g.rule.halfdiag + g.rule.margin, best, count, start, total, cls, 0);
+    if (e != hipSuccess) return e;
+  }
+  auto point = [&](auto& h, const void* cells, auto* segs, auto* dc) {
+    h.geom.cells = cells;
+    h.geom.cell_prim = o.prim;
+    h.geom.cell_segs = seg ? segs : nullptr;
+    h.geom.cell_dc = dc;
+    h.geom.cell_class = cls;
+  };
+  point(h32, o.cells32, o.segs32, o.dc32);
+  point(h64, o.cells64, o.segs64, o.dc64);
+  return hipSuccess;
 }
 
 }  // namespace
@@ -701,7 +701,7 @@ static wos_status problem_create_impl(const wos_problem_desc* desc, int device, 
     const wos_status s = build_geometry(d, g);
     if (s != WOS_OK) return s;
   }
-  const double geometry_ms = ms_since(t0);
+  double geometry_ms = ms_since(t0);
   t0 = clock::now();
   int n_dev = 0;
   WOS_HIP(hipGetDeviceCount(&n_dev));
@@ -719,7 +719,11 @@ static wos_status problem_create_impl(const wos_problem_desc* desc, int device, 
   p->grid_nx = g.grid.nx;
   p->grid_ny = g.grid.ny;
   p->grid_nz = g.grid.nx > 0 ? g.grid.nz : 0;
-  p->grid_candidates = (int64_t)g.grid.prim.size();
+  auto cleanup = [&]() {
+    if (p->grid_mem) (void)hipFree(p->grid_mem);
+    if (p->dmem) (void)hipFree(p->dmem);
+    delete p;
+  };
   Blob blob;
   std::vector<std::pair<size_t, size_t>> fix;
   p->off32 = layout_problem<float>(blob, d, g, fix);
@@ -733,14 +737,27 @@ static wos_status problem_create_impl(const wos_problem_desc* desc, int device, 
     const uint64_t addr = (uint64_t)p->dmem + f.second;
     std::memcpy(blob.host.data() + f.first, &addr, sizeof(addr));
   }
-  p->staging = blob.host;
-  auto upload = [&]() { return hipMemcpy(p->dmem, p->staging.data(), p->staging.size(), hipMemcpyHostToDevice); };
-  if ((e = upload()) != hipSuccess) {
-    (void)hipFree(p->dmem);
-    delete p;
+  if ((e = hipMemcpy(p->dmem, blob.host.data(), blob.host.size(), hipMemcpyHostToDevice)) != hipSuccess) {
+    cleanup();
     return fail(WOS_ERR_DEVICE, "upload of problem data failed");
   }
+  DevProblem<float>& h32 = *(DevProblem<float>*)(blob.host.data() + p->off32);
+  DevProblem<double>& h64 = *(DevProblem<double>*)(blob.host.data() + p->off64);
+  auto upload_headers = [&]() {
+    const hipError_t e32 = hipMemcpy((void*)p->d32(), &h32, sizeof(h32), hipMemcpyHostToDevice);
+    return e32 != hipSuccess ? e32 : hipMemcpy((void*)p->d64(), &h64, sizeof(h64), hipMemcpyHostToDevice);
+  };
   const double upload_ms = ms_since(t0);
+  t0 = clock::now();
+  if (g.grid.nx > 0) {
+    if ((e = build_grid(p, g, h32, h64)) == hipSuccess) e = upload_headers();
+    if (e != hipSuccess) {
+      cleanup();
+      return fail(e == hipErrorOutOfMemory ? WOS_ERR_OUT_OF_MEMORY : WOS_ERR_DEVICE,
+                  std::string("candidate grid failed: ") + hipGetErrorString(e));
+    }
+  }
+  geometry_ms += ms_since(t0);
   t0 = clock::now();
   // sample alpha, sigma and sigma' in FP64 over a grid of the bounding box (interior points)
   double lo[3] = {0, 0, 0}, hi[3] = {0, 0, 0};
@@ -769,29 +786,32 @@ static wos_status problem_create_impl(const wos_problem_desc* desc, int device, 
   double h[3] = {0, 0, 0};
   for (int i = 0; i < d.dim; ++i) h[i] = (hi[i] - lo[i]) / grid;
   const int nblocks = 1024;
-  double* dout = nullptr;
   std::vector<double> hout((size_t)nblocks * 6);
-  auto cleanup = [&]() {
-    if (dout) (void)hipFree(dout);
-    (void)hipFree(p->dmem);
-    delete p;
-  };
-  if ((e = hipMalloc(&dout, hout.size() * sizeof(double))) != hipSuccess ||
-      (e = launch_sigma_sample(d.dim, g.kind, p->d64(), lo, h, grid, nblocks, dout, 0)) != hipSuccess ||
-      (e = hipMemcpy(hout.data(), dout, hout.size() * sizeof(double), hipMemcpyDeviceToHost)) != hipSuccess) {
-    cleanup();
-    return fail(WOS_ERR_DEVICE, std::string("sigma' sampling failed: ") + hipGetErrorString(e));
-  }
-  (void)hipFree(dout);
-  dout = nullptr;
   double mn = INFINITY, mx = -INFINITY, amin = INFINITY, smin = INFINITY, bad = 0, cnt = 0;
-  for (int b = 0; b < nblocks; ++b) {
-    mn = std::min(mn, hout[6 * b]);
-    mx = std::max(mx, hout[6 * b + 1]);
-    amin = std::min(amin, hout[6 * b + 2]);
-    smin = std::min(smin, hout[6 * b + 3]);
-    bad += hout[6 * b + 4];
-    cnt += hout[6 * b + 5];
+  {
+    const int64_t samples = d.dim == 2 ? (int64_t)grid * grid : (int64_t)grid * grid * grid;
+    const int64_t most = std::min<int64_t>(samples, 1 << 26);   // per launch: a byte of scratch each
+    DeviceScratch scratch;
+    e = hipMalloc(&scratch.p, hout.size() * sizeof(double) + (size_t)most);
+    double* dout = (double*)scratch.p;
+    for (int64_t first = 0; first < samples && e == hipSuccess; first += most) {
+      e = launch_sigma_sample(d.dim, g.kind, p->d64(), lo, h, grid, first, std::min(most, samples - first), nblocks,
+                              (int8_t*)(dout + hout.size()), dout, 0);
+      if (e == hipSuccess) e = hipMemcpy(hout.data(), dout, hout.size() * sizeof(double), hipMemcpyDeviceToHost);
+      if (e != hipSuccess) break;
+      for (int b = 0; b < nblocks; ++b) {
+        mn = std::min(mn, hout[6 * b]);
+        mx = std::max(mx, hout[6 * b + 1]);
+        amin = std::min(amin, hout[6 * b + 2]);
+        smin = std::min(smin, hout[6 * b + 3]);
+        bad += hout[6 * b + 4];
+        cnt += hout[6 * b + 5];
+      }
+    }
+    if (e != hipSuccess) {
+      cleanup();
+      return fail(WOS_ERR_DEVICE, std::string("sigma' sampling failed: ") + hipGetErrorString(e));
+    }
   }
   wos_status st = WOS_OK;
   std::string msg;
@@ -826,9 +846,9 @@ static wos_status problem_create_impl(const wos_problem_desc* desc, int device, 
     return fail(st, msg);
   }
   p->sigma_bar = sb;
-  set_sigma_bar<float>(p->staging.data() + p->off32, sb);
-  set_sigma_bar<double>(p->staging.data() + p->off64, sb);
-  if ((e = upload()) != hipSuccess) {
+  set_sigma_bar(h32, sb);
+  set_sigma_bar(h64, sb);
+  if ((e = upload_headers()) != hipSuccess) {
     cleanup();
     return fail(WOS_ERR_DEVICE, "upload of sigma_bar failed");
   }
@@ -880,6 +900,7 @@ wos_status wos_problem_grid_info(const wos_problem* p, int32_t* nx, int32_t* ny,
 wos_status wos_problem_destroy(wos_problem* p) {
   if (!p) return WOS_OK;
   (void)hipSetDevice(p->device);
+  if (p->grid_mem) (void)hipFree(p->grid_mem);
   if (p->dmem) (void)hipFree(p->dmem);
   delete p;
   return WOS_OK;

@@ -1,0 +1,820 @@
+// Geometry on the device: inside tests of query points and of the sigma' sample, the sample
+// itself, and the construction of the candidate grids of polygons and triangle meshes.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cmath>
+#include <cstdint>
+#include <type_traits>
+
+#include "wos_device.h"
+#include "wos_launch.h"
+
+namespace wos {
+
+// ------------------------------------------------------------------ inside tests (FP64)
+
+template <int DIM>
+__device__ __forceinline__ bool finite_point(const double* x) {
+  bool f = true;
+#pragma unroll
+  for (int i = 0; i < DIM; ++i) f = f && isfinite(x[i]);
+  return f;
+}
+
+template <int DIM, int GEOM>
+__device__ __forceinline__ bool inside_analytic(G<DevGeometry<double>>& g, const double* x) {
+  if (!finite_point<DIM>(x)) return false;
+  if (GEOM == GK_BALL) {
+    double r2 = 0;
+    for (int i = 0; i < DIM; ++i) r2 += (x[i] - g.center[i]) * (x[i] - g.center[i]);
+    return r2 < g.radius * g.radius;
+  } else if (GEOM == GK_BOX) {
+    for (int i = 0; i < DIM; ++i)
+      if (!(x[i] > g.lo[i] && x[i] < g.hi[i])) return false;
+    return true;
+  } else {
+    int act;
+    return sdf_value<double, DIM>(g, x, &act) < 0.0;
+  }
+}
+
+// What primitive j adds to the inside test at x: polygons count the crossings of a horizontal
+// ray (even-odd), meshes sum signed solid angles (generalized winding number; Van Oosterom
+// and Strackee: tan(Omega/2) = det[a b c] / (|a||b||c| + (a.b)|c| + (a.c)|b| + (b.c)|a|)).
+template <int GEOM>
+__device__ __forceinline__ double inside_term(G<DevGeometry<double>>& g, const double* x, int j) {
+  if (GEOM == GK_POLYGON) {
+    const WOS_GLOBAL double* s = gptr(g.prims) + (size_t)j * kPrimStride2;
+    const double ay = s[1], by = s[3];
+    if ((ay > x[1]) != (by > x[1])) {
+      const double xi = s[0] + (x[1] - ay) * (s[2] - s[0]) / (by - ay);
+      if (x[0] < xi) return 1.0;
+    }
+    return 0.0;
+  }
+  const WOS_GLOBAL double* t = gptr(g.prims) + (size_t)j * kPrimStride3;
+  double a[3], b[3], c[3];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    a[i] = t[i] - x[i];
+    b[i] = t[3 + i] - x[i];
+    c[i] = t[6 + i] - x[i];
+  }
+  const double la = sqrt(a[0] * a[0] + a[1] * a[1] + a[2] * a[2]);
+  const double lb = sqrt(b[0] * b[0] + b[1] * b[1] + b[2] * b[2]);
+  const double lc = sqrt(c[0] * c[0] + c[1] * c[1] + c[2] * c[2]);
+  const double det = a[0] * (b[1] * c[2] - b[2] * c[1]) - a[1] * (b[0] * c[2] - b[2] * c[0]) +
+                     a[2] * (b[0] * c[1] - b[1] * c[0]);
+  const double ab = a[0] * b[0] + a[1] * b[1] + a[2] * b[2];
+  const double ac = a[0] * c[0] + a[1] * c[1] + a[2] * c[2];
+  const double bc = b[0] * c[0] + b[1] * c[1] + b[2] * c[2];
+  return 2.0 * atan2(det, la * lb * lc + ab * lc + ac * lb + bc * la);
+}
+
+template <int GEOM>
+__device__ __forceinline__ bool inside_sum(double w) {
+  return GEOM == GK_POLYGON ? ((int64_t)w & 1) != 0 : fabs(w) > 2.0 * M_PI;
+}
+
+// Inside test of one finite point by a whole wave, over every primitive.
+template <int GEOM>
+__device__ __forceinline__ bool inside_wave(G<DevGeometry<double>>& g, const double* x) {
+  double w = 0;
+  for (int j = (int)__lane_id(); j < g.n_prims; j += 64) w += inside_term<GEOM>(g, x, j);
+  for (int off = 32; off > 0; off >>= 1) w += __shfl_xor(w, off);
+  return inside_sum<GEOM>(w);
+}
+
+// Class of a point from its grid cell: 0 outside, 1 inside, kCellMixed undecided. Points
+// outside the grid lie outside the domain; a mesh that is not closed has no classes.
+template <int DIM>
+__device__ __forceinline__ int cell_class_of(G<DevGeometry<double>>& g, const double* x) {
+  if (!finite_point<DIM>(x)) return 0;
+  if (!g.cell_class) return kCellMixed;
+  const int nn[3] = {g.grid_nx, g.grid_ny, g.grid_nz};
+  int64_t c = 0;
+  bool in = true;
+#pragma unroll
+  for (int i = DIM - 1; i >= 0; --i) {
+    const double f = (x[i] - g.grid_lo[i]) * g.grid_inv_h;
+    in = in && f >= 0.0 && f < (double)nn[i];
+    c = c * nn[i] + (in ? (int64_t)f : 0);
+  }
+  return in ? (int)gptr(g.cell_class)[c] : 0;
+}
+
+// Points to classify: an array, or the cell centres of a sampling grid.
+template <int DIM>
+struct ArrayPoints {
+  const double* pts;
+  __device__ __forceinline__ void get(int64_t k, double* x) const {
+    for (int i = 0; i < DIM; ++i) x[i] = pts[k * DIM + i];
+  }
+};
+
+template <int DIM>
+struct SamplePoints {
+  double lo[3], h[3];
+  int grid;
+  int64_t first;   // sample of k = 0
+  __device__ __forceinline__ void get(int64_t k, double* x) const {
+    k += first;
+#pragma unroll
+    for (int i = 0; i < DIM; ++i) {
+      x[i] = __builtin_fma(h[i], (double)(k % grid) + 0.5, lo[i]);
+      k /= grid;
+    }
+  }
+};
+
+// Analytic and SDF domains: one point per thread.
+template <int DIM, int GEOM, typename SRC>
+__global__ void classify_analytic_kernel(const DevProblem<double>* P, SRC src, int64_t n, int8_t* inside,
+                                         uint64_t* counters) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  bool bad = false;
+  if (i < n) {
+    double x[DIM];
+    src.get(i, x);
+    const bool in = inside_analytic<DIM, GEOM>(gptr(P)->geom, x);
+    inside[i] = in ? 1 : 0;
+    bad = !in;
+  }
+  if (counters) {
+    const uint64_t m = __ballot(bad);
+    if (__lane_id() == 0 && m) atomicAdd((unsigned long long*)&counters[0], (unsigned long long)__popcll(m));
+  }
+}
+
+// Polygons and meshes: 64 points per block. The first wave looks up their cells; the points
+// that lie in a cell of the boundary (2-10% of a slice) go through every primitive, a wave
+// each. One point per thread over every primitive, as before, is a serial chain of n_prims
+// terms: 15.7 ms for 131,000 points of a 20,480-triangle mesh, 156 us on average for the
+// polygons of a batch.
+constexpr int kClassifyPoints = 64;
+
+template <int DIM, int GEOM, typename SRC>
+__global__ void __launch_bounds__(256) classify_cells_kernel(const DevProblem<double>* P, SRC src, int64_t n,
+                                                             int8_t* inside, uint64_t* counters) {
+  __shared__ double s_x[kClassifyPoints][DIM];
+  __shared__ int s_todo[kClassifyPoints];
+  __shared__ int s_n;
+  __shared__ int s_in[kClassifyPoints];
+  G<DevGeometry<double>>& g = gptr(P)->geom;
+  const int t = (int)threadIdx.x, wave = t >> 6;
+  const int64_t i = (int64_t)blockIdx.x * kClassifyPoints + t;
+  if (wave == 0) {
+    int c = 0;
+    if (i < n) {
+      double x[DIM];
+      src.get(i, x);
+      c = cell_class_of<DIM>(g, x);
+#pragma unroll
+      for (int k = 0; k < DIM; ++k) s_x[t][k] = x[k];
+    }
+    s_in[t] = c == 1;
+    const uint64_t todo = __ballot(c == kCellMixed);
+    if (c == kCellMixed) s_todo[__popcll(todo & ((1ull << t) - 1ull))] = t;
+    if (t == 0) s_n = __popcll(todo);
+  }
+  __syncthreads();
+  for (int k = wave; k < s_n; k += (int)(blockDim.x >> 6)) {
+    const int p = s_todo[k];
+    double x[DIM];
+#pragma unroll
+    for (int c = 0; c < DIM; ++c) x[c] = s_x[p][c];
+    const bool in = inside_wave<GEOM>(g, x);
+    if (__lane_id() == 0) s_in[p] = in;
+  }
+  __syncthreads();
+  if (wave == 0) {
+    const bool in = s_in[t] != 0;
+    if (i < n) inside[i] = in ? 1 : 0;
+    if (counters) {
+      const uint64_t m = __ballot(i < n && !in);
+      if (t == 0 && m) atomicAdd((unsigned long long*)&counters[0], (unsigned long long)__popcll(m));
+    }
+  }
+}
+
+// ------------------------------------------------------------------ sigma' sampling (FP64)
+// out per block: [min sigma', max sigma', min alpha, min sigma, #non-finite, #samples]
+
+template <int DIM>
+__global__ void sigma_sample_kernel(const DevProblem<double>* P, SamplePoints<DIM> src, int64_t n, const int8_t* inside,
+                                    double* out) {
+  double mn = __builtin_huge_val(), mx = -__builtin_huge_val(), amin = __builtin_huge_val(),
+         smin = __builtin_huge_val(), bad = 0, cnt = 0;
+  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x) {
+    if (!inside[k]) continue;
+    double x[DIM];
+    src.get(k, x);
+    G<DevProblem<double>>& PR = *gptr(P);
+    const PointCoef<double> c = point_coef<double, DIM, false>(PR, x);
+    const double sig = field_eval<double, DIM, false>(PR.sigma, x).v;
+    cnt += 1;
+    if (!isfinite(c.sigma_prime) || !isfinite(c.alpha)) {
+      bad += 1;
+      continue;
+    }
+    mn = fmin(mn, c.sigma_prime);
+    mx = fmax(mx, c.sigma_prime);
+    amin = fmin(amin, c.alpha);
+    smin = fmin(smin, sig);
+  }
+  __shared__ double red[6][256];
+  const int t = threadIdx.x;
+  red[0][t] = mn; red[1][t] = mx; red[2][t] = amin; red[3][t] = smin; red[4][t] = bad; red[5][t] = cnt;
+  __syncthreads();
+  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
+    if (t < s) {
+      red[0][t] = fmin(red[0][t], red[0][t + s]);
+      red[1][t] = fmax(red[1][t], red[1][t + s]);
+      red[2][t] = fmin(red[2][t], red[2][t + s]);
+      red[3][t] = fmin(red[3][t], red[3][t + s]);
+      red[4][t] += red[4][t + s];
+      red[5][t] += red[5][t + s];
+    }
+    __syncthreads();
+  }
+  if (t == 0)
+    for (int k = 0; k < 6; ++k) out[blockIdx.x * 6 + k] = red[k][0];
+}
+
+// ------------------------------------------------------------------ cell classes
+//
+// A cell that no primitive touches lies wholly inside or wholly outside a closed boundary,
+// and so do two such cells that share a face. Cells are joined into components (union-find
+// over faces, labels only ever shrink), the lowest cell of each component is tested against
+// every primitive, and the others take its class.
+
+__device__ __forceinline__ uint32_t load_label(const uint32_t* label, uint32_t c) {
+  return __hip_atomic_load(label + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ uint32_t find_root(const uint32_t* label, uint32_t c) {
+  for (;;) {
+    const uint32_t up = load_label(label, c);
+    if (up == c) return c;
+    c = up;   // up < c
+  }
+}
+
+// Each turn either ends or replaces a by a smaller label, so the loop ends.
+__device__ __forceinline__ void join(uint32_t* label, uint32_t a, uint32_t b) {
+  for (;;) {
+    a = find_root(label, a);
+    b = find_root(label, b);
+    if (a == b) return;
+    if (a < b) {
+      const uint32_t t = a;
+      a = b;
+      b = t;
+    }
+    const uint32_t old = atomicMin(label + a, b);
+    if (old == a) return;
+    a = old;
+  }
+}
+
+// A cell's first label: the start of its run of untouched cells in x, as far as its wave
+// reaches, so that a row is not one chain of labels (one cell per link: 3.2 ms of joins for
+// 655,000 cells).
+__global__ void __launch_bounds__(256) label_init_kernel(const double* best, double reach, int64_t ncell, int nx,
+                                                         uint32_t* label, uint32_t* n_roots) {
+  const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (c == 0) *n_roots = 0;
+  const int lane = (int)__lane_id();
+  const bool open = c < ncell && sqrt(best[c]) > reach;
+  const uint64_t all = __ballot(open);
+  const bool left = lane > 0 && (all >> (lane - 1) & 1ull) && c % nx != 0;
+  const uint64_t starts = __ballot(open && !left) & (~0ull >> (63 - lane));
+  if (c < ncell) label[c] = open ? (uint32_t)(c - (lane - (63 - __clzll(starts)))) : kNoLabel;
+}
+
+// Joins across the ends of those runs and to the next row and layer; of two rows' common
+// stretch only the first pair is joined, the runs hold the others together.
+__global__ void __launch_bounds__(256) label_join_kernel(uint32_t* label, int nx, int ny, int nz) {
+  const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  auto open = [&](int64_t u) { return load_label(label, (uint32_t)u) != kNoLabel; };
+  if (c >= (int64_t)nx * ny * nz || !open(c)) return;
+  const int64_t layer = (int64_t)nx * ny;
+  const int i = (int)(c % nx), j = (int)(c / nx % ny), k = (int)(c / layer);
+  const bool left = i > 0 && open(c - 1);
+  if (left && (c & 63) == 0) join(label, (uint32_t)c, (uint32_t)(c - 1));
+  if (j + 1 < ny && open(c + nx) && !(left && open(c + nx - 1))) join(label, (uint32_t)c, (uint32_t)(c + nx));
+  if (k + 1 < nz && open(c + layer) && !(left && open(c + layer - 1)))
+    join(label, (uint32_t)c, (uint32_t)(c + layer));
+}
+
+__global__ void label_roots_kernel(const uint32_t* label, int64_t ncell, uint32_t* roots, uint32_t* n_roots) {
+  const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (c < ncell && label[c] == (uint32_t)c) roots[atomicAdd(n_roots, 1u)] = (uint32_t)c;
+}
+
+template <int GEOM>
+__global__ void __launch_bounds__(256) root_class_kernel(const DevProblem<double>* P, GridShape s, const uint32_t* roots,
+                                                         const uint32_t* n_roots, uint8_t* cls) {
+  __shared__ double s_w[4];
+  G<DevGeometry<double>>& g = gptr(P)->geom;
+  const uint32_t n = *n_roots;
+  for (uint32_t r = blockIdx.x; r < n; r += gridDim.x) {
+    const uint32_t c = roots[r];
+    const double x[3] = {s.lo[0] + ((double)(c % (uint32_t)s.nx) + 0.5) * s.h,
+                         s.lo[1] + ((double)(c / (uint32_t)s.nx % (uint32_t)s.ny) + 0.5) * s.h,
+                         s.lo[2] + ((double)(c / ((uint32_t)s.nx * (uint32_t)s.ny)) + 0.5) * s.h};
+    double w = 0;
+    for (int j = (int)threadIdx.x; j < g.n_prims; j += (int)blockDim.x) w += inside_term<GEOM>(g, x, j);
+    for (int off = 32; off > 0; off >>= 1) w += __shfl_xor(w, off);
+    if (__lane_id() == 0) s_w[threadIdx.x >> 6] = w;
+    __syncthreads();
+    if (threadIdx.x == 0) cls[c] = inside_sum<GEOM>(s_w[0] + s_w[1] + s_w[2] + s_w[3]) ? 1 : 0;
+    __syncthreads();
+  }
+}
+
+__global__ void cell_class_kernel(const uint32_t* label, int64_t ncell, uint8_t* cls) {
+  const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (c >= ncell) return;
+  const uint32_t l = label[c];
+  if (l == kNoLabel) {
+    cls[c] = kCellMixed;
+  } else if (l != (uint32_t)c) {
+    cls[c] = cls[find_root(label, l)];   // roots are written already
+  }
+}
+
+// ------------------------------------------------------------------ candidate grids
+//
+// The construction of build_segment_grid and build_triangle_grid (bvh.h), one cell per
+// thread, in their arithmetic: contraction is off from here on, so that distances, and with
+// them the lists, come out as the host's. The host builds took 170 ms for 5120 triangles and
+// 440 ms for 20,480 (16 threads), more than the solves that followed.
+#pragma clang fp contract(off)
+
+__device__ __forceinline__ double build_seg_dist2(const WOS_GLOBAL double* s, const double* p) {
+  const double ex = s[2] - s[0], ey = s[3] - s[1];
+  const double qx = p[0] - s[0], qy = p[1] - s[1];
+  const double l2 = ex * ex + ey * ey;
+  double t = l2 > 0 ? (qx * ex + qy * ey) / l2 : 0.0;
+  t = fmin(1.0, fmax(0.0, t));
+  const double dx = qx - t * ex, dy = qy - t * ey;
+  return dx * dx + dy * dy;
+}
+
+__device__ __forceinline__ double build_dot3(const double* a, const double* b) {
+  return a[0] * b[0] + a[1] * b[1] + a[2] * b[2];
+}
+
+__device__ __forceinline__ double build_edge_dist2(const double* a, const double* b, const double* p) {
+  double e[3], q[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    e[k] = b[k] - a[k];
+    q[k] = p[k] - a[k];
+  }
+  const double l2 = build_dot3(e, e);
+  double t = l2 > 0 ? build_dot3(q, e) / l2 : 0.0;
+  t = fmin(1.0, fmax(0.0, t));
+#pragma unroll
+  for (int k = 0; k < 3; ++k) q[k] -= t * e[k];
+  return build_dot3(q, q);
+}
+
+__device__ __forceinline__ double build_tri_dist2(const WOS_GLOBAL double* t, const double* p) {
+  double a[3], b[3], c[3], e0[3], e1[3], ap[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    a[k] = t[k];
+    b[k] = t[3 + k];
+    c[k] = t[6 + k];
+    e0[k] = b[k] - a[k];
+    e1[k] = c[k] - a[k];
+    ap[k] = p[k] - a[k];
+  }
+  const double d00 = build_dot3(e0, e0), d01 = build_dot3(e0, e1), d11 = build_dot3(e1, e1);
+  const double den = d00 * d11 - d01 * d01;
+  if (den > 0) {
+    const double d20 = build_dot3(ap, e0), d21 = build_dot3(ap, e1);
+    const double v = (d11 * d20 - d01 * d21) / den, w = (d00 * d21 - d01 * d20) / den;
+    if (v >= 0 && w >= 0 && v + w <= 1) {
+      double q[3];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) q[k] = ap[k] - v * e0[k] - w * e1[k];
+      return build_dot3(q, q);
+    }
+  }
+  return fmin(build_edge_dist2(a, b, p), fmin(build_edge_dist2(b, c, p), build_edge_dist2(c, a, p)));
+}
+
+template <int DIM>
+__device__ __forceinline__ double build_box_dist2(const WOS_GLOBAL double* lo, const WOS_GLOBAL double* hi,
+                                                  const double* p) {
+  double s = 0;
+#pragma unroll
+  for (int k = 0; k < DIM; ++k) {
+    const double e = fmax(fmax(lo[k] - p[k], p[k] - hi[k]), 0.0);
+    s += e * e;
+  }
+  return s;
+}
+
+// Blocks of one wave. Far children wait on a stack in LDS (a column per lane) in trees of
+// depth kBuildStack or less, else in private memory.
+constexpr int kBuildStack = 20;
+constexpr int kBuildStackDeep = 48;   // any tree the host accepts
+
+// Visits every leaf primitive whose subtree box lies within sqrt(bound) of p, nearer boxes
+// first; f(primitive, squared distance) may lower the bound.
+template <int DIM, bool DEEP, typename F>
+__device__ __forceinline__ void build_traverse(G<DevGeometry<double>>& g, const double* p, const double& bound,
+                                               int32_t* s_node, double* s_dist, F&& f) {
+  const WOS_GLOBAL BvhNode<double, DIM>* nodes = (const WOS_GLOBAL BvhNode<double, DIM>*)g.nodes;
+  const WOS_GLOBAL double* prims = gptr(g.prims);
+  int32_t d_node[DEEP ? kBuildStackDeep : 1];
+  double d_dist[DEEP ? kBuildStackDeep : 1];
+  int sp = 0;
+  int32_t cur = g.root;
+  for (;;) {
+    if (cur < 0) {
+      const int32_t code = -1 - cur, first = code >> 3, cnt = code & 7;
+      for (int32_t i = first; i < first + cnt; ++i)
+        f(i, DIM == 2 ? build_seg_dist2(prims + (size_t)i * kPrimStride2, p)
+                      : build_tri_dist2(prims + (size_t)i * kPrimStride3, p));
+    } else {
+      G<BvhNode<double, DIM>>& n = nodes[cur];
+      const double da = build_box_dist2<DIM>(n.lo[0], n.hi[0], p), db = build_box_dist2<DIM>(n.lo[1], n.hi[1], p);
+      const int32_t ca = n.child[0], cb = n.child[1];
+      const bool a_first = da <= db;
+      const double near_d = a_first ? da : db, far_d = a_first ? db : da;
+      if (far_d <= bound) {   // at most one entry per level above the current node
+        if constexpr (DEEP) {
+          d_node[sp] = a_first ? cb : ca;
+          d_dist[sp] = far_d;
+        } else {
+          s_node[sp * 64] = a_first ? cb : ca;
+          s_dist[sp * 64] = far_d;
+        }
+        ++sp;
+      }
+      if (near_d <= bound) {
+        cur = a_first ? ca : cb;
+        continue;
+      }
+    }
+    double d;
+    do {
+      if (sp == 0) return;
+      --sp;
+      cur = DEEP ? d_node[DEEP ? sp : 0] : s_node[sp * 64];
+      d = DEEP ? d_dist[DEEP ? sp : 0] : s_dist[sp * 64];
+    } while (!(d <= bound));
+  }
+}
+
+// Cell of this thread and its centre, or -1: a wave takes a block of 8 x 8 (3D: 4 x 4 x 4)
+// cells, whose searches visit nearly the same nodes (64 cells of a row reach across the
+// domain).
+template <int DIM>
+struct CellBlocks {
+  static constexpr int kSide = DIM == 2 ? 8 : 4;
+  static int64_t blocks(const GridShape& s) {
+    const auto n = [](int64_t v) { return (v + kSide - 1) / kSide; };
+    return n(s.nx) * n(s.ny) * (DIM == 2 ? 1 : n(s.nz));
+  }
+};
+
+template <int DIM>
+__device__ __forceinline__ int64_t block_cell(const GridShape& s, double* p) {
+  constexpr int S = CellBlocks<DIM>::kSide;
+  const int bx = (s.nx + S - 1) / S, by = (s.ny + S - 1) / S, b = (int)blockIdx.x, t = (int)threadIdx.x;
+  const int i = b % bx * S + t % S, j = b / bx % by * S + t / S % S, k = DIM == 2 ? 0 : b / (bx * by) * S + t / (S * S);
+  p[0] = s.lo[0] + ((double)i + 0.5) * s.h;
+  p[1] = s.lo[1] + ((double)j + 0.5) * s.h;
+  p[2] = s.lo[2] + ((double)k + 0.5) * s.h;
+  return i < s.nx && j < s.ny && k < s.nz ? ((int64_t)k * s.ny + j) * s.nx + i : -1;
+}
+
+// Squared distance of each cell's centre (best), the nearest primitive and the length of its
+// list.
+template <int DIM, bool DEEP>
+__global__ void __launch_bounds__(64) grid_count_kernel(const DevProblem<double>* P, GridShape s, GridRule rule,
+                                                        double* best_out, int32_t* near_out, uint32_t* count) {
+  __shared__ int32_t s_node[DEEP ? 1 : kBuildStack * 64];
+  __shared__ double s_dist[DEEP ? 1 : kBuildStack * 64];
+  double p[3];
+  const int64_t c = block_cell<DIM>(s, p);
+  if (c < 0) return;
+  int32_t* sn = s_node + (DEEP ? 0 : threadIdx.x);
+  double* sd = s_dist + (DEEP ? 0 : threadIdx.x);
+  G<DevGeometry<double>>& g = gptr(P)->geom;
+  double best = 1e300;
+  int32_t nearest = 0;
+  build_traverse<DIM, DEEP>(g, p, best, sn, sd, [&](int32_t i, double d2) {
+    if (d2 < best) {
+      best = d2;
+      nearest = i;
+    }
+  });
+  best_out[c] = best;
+  near_out[c] = nearest;
+  const double d = sqrt(best);
+  if (DIM == 3 && d >= rule.deep) {
+    count[c] = 1;
+    return;
+  }
+  const double r = d + 2 * rule.halfdiag + rule.margin, r2 = r * r;
+  const uint32_t most = (uint32_t)(DIM == 2 ? rule.max_list + 1 : rule.max_list);
+  uint32_t n = 0;
+  double bound = r2;
+  build_traverse<DIM, DEEP>(g, p, bound, sn, sd, [&](int32_t, double d2) {
+    if (d2 <= r2 && ++n >= most) bound = -1.0;   // enough is known
+  });
+  count[c] = DIM == 2 && n >= most ? (uint32_t)rule.deep_list : min(n, most);
+}
+
+// Writes every cell's list: primitives in leaf order of (distance, index), the distances in
+// both precisions less the rounding margin, and the records the walkers read.
+template <int DIM, bool DEEP>
+__global__ void __launch_bounds__(64) grid_fill_kernel(const DevProblem<double>* P, GridShape s, GridRule rule,
+                                                       const double* best_in, const int32_t* near_in,
+                                                       const uint32_t* start, GridOut o) {
+  // the nearest candidates found so far, in order; a polygon list over the limit keeps its
+  // deep_list nearest and the next one's distance
+  constexpr int kKeep = DIM == 2 ? kPolygonCellMax + 1 : kMeshCellList + 1;
+  __shared__ int32_t s_node[DEEP ? 1 : kBuildStack * 64];
+  __shared__ double s_dist[DEEP ? 1 : kBuildStack * 64];
+  __shared__ double s_d2[kKeep * 64];
+  __shared__ int32_t s_id[kKeep * 64];
+  double p[3];
+  const int64_t c = block_cell<DIM>(s, p);
+  if (c < 0) return;
+  int32_t* sn = s_node + (DEEP ? 0 : threadIdx.x);
+  double* sd = s_dist + (DEEP ? 0 : threadIdx.x);
+  double* ld = s_d2 + threadIdx.x;
+  int32_t* li = s_id + threadIdx.x;
+  G<DevGeometry<double>>& g = gptr(P)->geom;
+  const double best = best_in[c], d = sqrt(best);
+  const uint32_t st = start[c];
+  int n = 0, keep = 0;
+  double tail = __builtin_huge_val();
+  if (DIM == 3 && d >= rule.deep) {
+    ld[0] = best;
+    li[0] = near_in[c];
+    keep = 1;
+    tail = d;
+  } else {
+    const double r = d + 2 * rule.halfdiag + rule.margin, r2 = r * r;
+    double bound = r2;
+    int cap = rule.max_list + 1;
+    bool over = false;
+    build_traverse<DIM, DEEP>(g, p, bound, sn, sd, [&](int32_t i, double d2) {
+      if (!(d2 <= bound)) return;
+      if (n == cap) {
+        const double ed = ld[(n - 1) * 64];
+        if (d2 > ed || (d2 == ed && i > li[(n - 1) * 64])) return;
+        --n;
+      }
+      int k = n++;
+      for (; k > 0; --k) {
+        const double ed = ld[(k - 1) * 64];
+        const int32_t ei = li[(k - 1) * 64];
+        if (ed < d2 || (ed == d2 && ei < i)) break;
+        ld[k * 64] = ed;
+        li[k * 64] = ei;
+      }
+      ld[k * 64] = d2;
+      li[k * 64] = i;
+      if (n == cap) {
+        if (DIM == 2 && !over) {
+          over = true;
+          cap = n = rule.deep_list + 1;
+        }
+        bound = ld[(n - 1) * 64];
+      }
+    });
+    keep = DIM == 2 ? (over ? rule.deep_list : n) : min(n, rule.max_list);
+    if (n > keep) tail = sqrt(ld[keep * 64]);
+  }
+  const double t = tail < __builtin_huge_val() ? tail - rule.margin : tail;
+  const WOS_GLOBAL double* prims = gptr(g.prims);
+  for (int k = 0; k < keep; ++k) {
+    const int32_t id = li[k * 64];
+    const double dc = sqrt(ld[k * 64]) - rule.margin;
+    o.prim[st + k] = id;
+    o.dc32[st + k] = (float)dc;
+    o.dc64[st + k] = dc;
+    if (DIM == 2) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const double v = prims[(size_t)id * kPrimStride2 + e];
+        o.segs32[(size_t)(st + k) * 4 + e] = (float)v;
+        o.segs64[(size_t)(st + k) * 4 + e] = v;
+      }
+    }
+  }
+  auto record = [&](auto* rec) {
+    using R = typename std::remove_reference<decltype(*rec)>::type;
+    using T = typename std::remove_reference<decltype(rec->tail)>::type;
+    rec->count = (uint32_t)keep;
+    rec->start = st;
+    rec->tail = (T)t;
+    if constexpr (std::is_same<R, CellRec<T>>::value) {
+      // inline entries beyond the list repeat its last candidate: their distance equals
+      // that candidate's, so they never replace it as the nearest (strict comparison)
+      for (int k = 0; k < kCellInline; ++k) {
+        T sg[4] = {0, 0, 0, 0}, inv = 0;
+        if (keep > 0) {
+          const WOS_GLOBAL double* q = prims + (size_t)li[min(k, keep - 1) * 64] * kPrimStride2;
+          sg[0] = (T)q[0];
+          sg[1] = (T)q[1];
+          sg[2] = (T)(q[2] - q[0]);
+          sg[3] = (T)(q[3] - q[1]);
+          const double ex = (double)sg[2], ey = (double)sg[3], l2 = ex * ex + ey * ey;
+          inv = l2 > 0 ? (T)(1.0 / l2) : (T)0;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) rec->seg[k][e] = sg[e];
+        rec->inv_len2[k] = inv;
+      }
+    }
+  };
+  if (DIM == 2) {
+    record((CellRec<float>*)o.cells32 + c);
+    record((CellRec<double>*)o.cells64 + c);
+  } else {
+    record((MeshCell<float>*)o.cells32 + c);
+    record((MeshCell<double>*)o.cells64 + c);
+  }
+}
+
+// ------------------------------------------------------------------ prefix sum
+// start[c] = count[0] + ... + count[c - 1] over n cells, and the total: sums of 4096 counts,
+// their running sums, then the counts of each block again.
+constexpr int kScanItems = 16;
+
+__device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t* s_wave, uint32_t* total) {
+  uint32_t run = v;
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t u = __shfl_up(run, off);
+    if ((int)__lane_id() >= off) run += u;
+  }
+  const int wave = threadIdx.x >> 6;
+  if (__lane_id() == 63) s_wave[wave] = run;
+  __syncthreads();
+  uint32_t before = 0, all = 0;
+  for (int w = 0; w < 4; ++w) {
+    if (w < wave) before += s_wave[w];
+    all += s_wave[w];
+  }
+  __syncthreads();
+  *total = all;
+  return before + run - v;
+}
+
+__global__ void __launch_bounds__(256) scan_sums_kernel(const uint32_t* count, int64_t n, uint32_t* sums) {
+  __shared__ uint32_t s_wave[4];
+  const int64_t b = ((int64_t)blockIdx.x * 256 + threadIdx.x) * kScanItems;
+  uint32_t v = 0, total;
+  for (int k = 0; k < kScanItems; ++k) v += b + k < n ? count[b + k] : 0u;
+  block_scan(v, s_wave, &total);
+  if (threadIdx.x == 0) sums[blockIdx.x] = total;
+}
+
+__global__ void __launch_bounds__(256) scan_blocks_kernel(uint32_t* sums, int n_blocks, uint32_t* total_out) {
+  __shared__ uint32_t s_wave[4];
+  uint32_t carry = 0;
+  for (int b = 0; b < n_blocks; b += 256) {
+    const int i = b + (int)threadIdx.x;
+    const uint32_t v = i < n_blocks ? sums[i] : 0u;
+    uint32_t total;
+    const uint32_t e = block_scan(v, s_wave, &total);
+    if (i < n_blocks) sums[i] = carry + e;
+    carry += total;
+  }
+  if (threadIdx.x == 0) *total_out = carry;
+}
+
+__global__ void __launch_bounds__(256) scan_write_kernel(const uint32_t* count, int64_t n, const uint32_t* sums,
+                                                         uint32_t* start) {
+  __shared__ uint32_t s_wave[4];
+  const int64_t b = ((int64_t)blockIdx.x * 256 + threadIdx.x) * kScanItems;
+  uint32_t v = 0, total;
+  for (int k = 0; k < kScanItems; ++k) v += b + k < n ? count[b + k] : 0u;
+  uint32_t e = sums[blockIdx.x] + block_scan(v, s_wave, &total);
+  for (int k = 0; k < kScanItems && b + k < n; ++k) {
+    start[b + k] = e;
+    e += count[b + k];
+  }
+}
+
+// ====================================================================== launchers
+
+static inline unsigned blocks_for(int64_t n, int bs) { return (unsigned)((n + bs - 1) / bs); }
+
+template <int DIM, typename SRC>
+static hipError_t classify_t(int geom, const void* P64, const SRC& src, int64_t n, int8_t* inside, uint64_t* counters,
+                             hipStream_t st) {
+  const DevProblem<double>* P = (const DevProblem<double>*)P64;
+  const dim3 b(256), ga(blocks_for(n, 256)), gc(blocks_for(n, kClassifyPoints));
+  if (geom == GK_BALL)
+    hipLaunchKernelGGL((classify_analytic_kernel<DIM, GK_BALL, SRC>), ga, b, 0, st, P, src, n, inside, counters);
+  else if (geom == GK_BOX)
+    hipLaunchKernelGGL((classify_analytic_kernel<DIM, GK_BOX, SRC>), ga, b, 0, st, P, src, n, inside, counters);
+  else if (geom == GK_SDF)
+    hipLaunchKernelGGL((classify_analytic_kernel<DIM, GK_SDF, SRC>), ga, b, 0, st, P, src, n, inside, counters);
+  else if (geom == (DIM == 2 ? GK_POLYGON : GK_TRIMESH))
+    hipLaunchKernelGGL((classify_cells_kernel<DIM, DIM == 2 ? GK_POLYGON : GK_TRIMESH, SRC>), gc, b, 0, st, P, src, n,
+                       inside, counters);
+  else
+    return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
+hipError_t launch_classify(int dim, int geom, const void* P64, const double* pts, int64_t n, int8_t* inside,
+                           uint64_t* counters, hipStream_t st) {
+  if (n == 0) return hipSuccess;
+  return dim == 2 ? classify_t<2>(geom, P64, ArrayPoints<2>{pts}, n, inside, counters, st)
+                  : classify_t<3>(geom, P64, ArrayPoints<3>{pts}, n, inside, counters, st);
+}
+
+template <int DIM>
+static hipError_t sigma_t(int geom, const void* P64, const double* lo, const double* h, int grid, int64_t first,
+                          int64_t n, int nblocks, int8_t* inside, double* out, hipStream_t st) {
+  SamplePoints<DIM> src;
+  for (int i = 0; i < 3; ++i) {
+    src.lo[i] = lo[i];
+    src.h[i] = h[i];
+  }
+  src.grid = grid;
+  src.first = first;
+  const hipError_t e = classify_t<DIM>(geom, P64, src, n, inside, nullptr, st);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((sigma_sample_kernel<DIM>), dim3(nblocks), dim3(256), 0, st, (const DevProblem<double>*)P64, src,
+                     n, inside, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_sigma_sample(int dim, int geom, const void* P64, const double* lo, const double* h, int grid,
+                               int64_t first, int64_t n, int nblocks, int8_t* inside, double* out, hipStream_t st) {
+  return dim == 2 ? sigma_t<2>(geom, P64, lo, h, grid, first, n, nblocks, inside, out, st)
+                  : sigma_t<3>(geom, P64, lo, h, grid, first, n, nblocks, inside, out, st);
+}
+
+hipError_t launch_grid_count(int dim, int depth, const void* P64, const GridShape& s, const GridRule& rule, double* best,
+                             int32_t* near, uint32_t* count, uint32_t* sums, uint32_t* start, uint32_t* total,
+                             hipStream_t st) {
+  const int64_t n = s.cells();
+  const DevProblem<double>* P = (const DevProblem<double>*)P64;
+  const dim3 g((unsigned)(dim == 2 ? CellBlocks<2>::blocks(s) : CellBlocks<3>::blocks(s))), b(64);
+  const bool deep = depth > kBuildStack;
+  if (dim == 2) {
+    if (deep) hipLaunchKernelGGL((grid_count_kernel<2, true>), g, b, 0, st, P, s, rule, best, near, count);
+    else hipLaunchKernelGGL((grid_count_kernel<2, false>), g, b, 0, st, P, s, rule, best, near, count);
+  } else {
+    if (deep) hipLaunchKernelGGL((grid_count_kernel<3, true>), g, b, 0, st, P, s, rule, best, near, count);
+    else hipLaunchKernelGGL((grid_count_kernel<3, false>), g, b, 0, st, P, s, rule, best, near, count);
+  }
+  const unsigned nb = blocks_for(n, 256 * kScanItems);
+  hipLaunchKernelGGL(scan_sums_kernel, dim3(nb), dim3(256), 0, st, count, n, sums);
+  hipLaunchKernelGGL(scan_blocks_kernel, dim3(1), dim3(256), 0, st, sums, (int)nb, total);
+  hipLaunchKernelGGL(scan_write_kernel, dim3(nb), dim3(256), 0, st, count, n, sums, start);
+  return hipGetLastError();
+}
+
+hipError_t launch_grid_fill(int dim, int depth, const void* P64, const GridShape& s, const GridRule& rule,
+                            const double* best, const int32_t* near, const uint32_t* start, const GridOut& out,
+                            hipStream_t st) {
+  const DevProblem<double>* P = (const DevProblem<double>*)P64;
+  const dim3 g((unsigned)(dim == 2 ? CellBlocks<2>::blocks(s) : CellBlocks<3>::blocks(s))), b(64);
+  const bool deep = depth > kBuildStack;
+  if (dim == 2) {
+    if (deep) hipLaunchKernelGGL((grid_fill_kernel<2, true>), g, b, 0, st, P, s, rule, best, near, start, out);
+    else hipLaunchKernelGGL((grid_fill_kernel<2, false>), g, b, 0, st, P, s, rule, best, near, start, out);
+  } else {
+    if (deep) hipLaunchKernelGGL((grid_fill_kernel<3, true>), g, b, 0, st, P, s, rule, best, near, start, out);
+    else hipLaunchKernelGGL((grid_fill_kernel<3, false>), g, b, 0, st, P, s, rule, best, near, start, out);
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_cell_classes(int dim, const void* P64, const GridShape& s, double reach, const double* best,
+                               uint32_t* label, uint32_t* roots, uint32_t* n_roots, uint8_t* cls, hipStream_t st) {
+  const int64_t n = s.cells();
+  const DevProblem<double>* P = (const DevProblem<double>*)P64;
+  const dim3 g(blocks_for(n, 256)), b(256);
+  hipLaunchKernelGGL(label_init_kernel, g, b, 0, st, best, reach, n, s.nx, label, n_roots);
+  hipLaunchKernelGGL(label_join_kernel, g, b, 0, st, label, s.nx, s.ny, s.nz);
+  hipLaunchKernelGGL(label_roots_kernel, g, b, 0, st, label, n, roots, n_roots);
+  if (dim == 2)
+    hipLaunchKernelGGL((root_class_kernel<GK_POLYGON>), dim3(512), b, 0, st, P, s, roots, n_roots, cls);
+  else
+    hipLaunchKernelGGL((root_class_kernel<GK_TRIMESH>), dim3(512), b, 0, st, P, s, roots, n_roots, cls);
+  hipLaunchKernelGGL(cell_class_kernel, g, b, 0, st, label, n, cls);
+  return hipGetLastError();
+}
+
+size_t scan_sum_words(int64_t cells) { return blocks_for(cells, 256 * kScanItems); }
+
+}  // namespace wos

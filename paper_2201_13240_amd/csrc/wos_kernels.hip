@@ -1,5 +1,5 @@
-// Kernels around the walker (exact per-point sums, classification, sigma' sampling,
-// diagnostics) and the host-side launchers; the walker itself is in wos_walker.h.
+// Kernels around the walker (exact per-point sums, diagnostics) and their host-side
+// launchers; the walker itself is in wos_walker.h, inside tests and grids in wos_grid.hip.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -125,128 +125,6 @@ __global__ void set_params_kernel(LaunchParams* lp, uint64_t seed, uint64_t add)
     lp->seed = seed;
     lp->walk_offset_add = add;
   }
-}
-
-// ------------------------------------------------------------------ inside classification (FP64)
-
-template <int DIM, int GEOM>
-__device__ bool inside_point(G<DevGeometry<double>>& g, const double* x) {
-#pragma unroll
-  for (int i = 0; i < DIM; ++i)
-    if (!isfinite(x[i])) return false;
-  if (GEOM == GK_BALL) {
-    double r2 = 0;
-    for (int i = 0; i < DIM; ++i) r2 += (x[i] - g.center[i]) * (x[i] - g.center[i]);
-    return r2 < g.radius * g.radius;
-  } else if (GEOM == GK_BOX) {
-    for (int i = 0; i < DIM; ++i)
-      if (!(x[i] > g.lo[i] && x[i] < g.hi[i])) return false;
-    return true;
-  } else if (GEOM == GK_SDF) {
-    int act;
-    return sdf_value<double, DIM>(g, x, &act) < 0.0;
-  } else if (GEOM == GK_POLYGON) {
-    // even-odd crossing count of a horizontal ray
-    bool in = false;
-    for (int j = 0; j < g.n_prims; ++j) {
-      const WOS_GLOBAL double* s = gptr(g.prims) + (size_t)j * kPrimStride2;
-      const double ay = s[1], by = s[3];
-      if ((ay > x[1]) != (by > x[1])) {
-        const double xi = s[0] + (x[1] - ay) * (s[2] - s[0]) / (by - ay);
-        if (x[0] < xi) in = !in;
-      }
-    }
-    return in;
-  } else {
-    // generalized winding number: sum of signed solid angles / 4 pi
-    // (Van Oosterom and Strackee: tan(Omega/2) = det[a b c] / (|a||b||c| + (a.b)|c| + (a.c)|b| + (b.c)|a|))
-    double w = 0;
-    for (int j = 0; j < g.n_prims; ++j) {
-      const WOS_GLOBAL double* t = gptr(g.prims) + (size_t)j * kPrimStride3;
-      double a[3], b[3], c[3];
-      for (int i = 0; i < 3; ++i) {
-        a[i] = t[i] - x[i];
-        b[i] = t[3 + i] - x[i];
-        c[i] = t[6 + i] - x[i];
-      }
-      const double la = sqrt(a[0] * a[0] + a[1] * a[1] + a[2] * a[2]);
-      const double lb = sqrt(b[0] * b[0] + b[1] * b[1] + b[2] * b[2]);
-      const double lc = sqrt(c[0] * c[0] + c[1] * c[1] + c[2] * c[2]);
-      const double det = a[0] * (b[1] * c[2] - b[2] * c[1]) - a[1] * (b[0] * c[2] - b[2] * c[0]) +
-                         a[2] * (b[0] * c[1] - b[1] * c[0]);
-      const double ab = a[0] * b[0] + a[1] * b[1] + a[2] * b[2];
-      const double ac = a[0] * c[0] + a[1] * c[1] + a[2] * c[2];
-      const double bc = b[0] * c[0] + b[1] * c[1] + b[2] * c[2];
-      w += 2.0 * atan2(det, la * lb * lc + ab * lc + ac * lb + bc * la);
-    }
-    return fabs(w) > 2.0 * M_PI;
-  }
-}
-
-template <int DIM, int GEOM>
-__global__ void classify_kernel(const DevProblem<double>* P, const double* pts, int64_t n, int8_t* inside,
-                                uint64_t* counters) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  bool bad = false;
-  if (i < n) {
-    const bool in = inside_point<DIM, GEOM>(gptr(P)->geom, pts + i * DIM);
-    inside[i] = in ? 1 : 0;
-    bad = !in;
-  }
-  if (counters) {
-    const uint64_t m = __ballot(bad);
-    if (__lane_id() == 0 && m) atomicAdd((unsigned long long*)&counters[0], (unsigned long long)__popcll(m));
-  }
-}
-
-// ------------------------------------------------------------------ sigma' sampling (FP64)
-// out per block: [min sigma', max sigma', min alpha, min sigma, #non-finite, #samples]
-
-template <int DIM, int GEOM>
-__global__ void sigma_sample_kernel(const DevProblem<double>* P, double lo0, double lo1, double lo2, double h0,
-                                    double h1, double h2, int grid, double* out) {
-  const double lo[3] = {lo0, lo1, lo2}, h[3] = {h0, h1, h2};
-  double mn = __builtin_huge_val(), mx = -__builtin_huge_val(), amin = __builtin_huge_val(),
-         smin = __builtin_huge_val(), bad = 0, cnt = 0;
-  const int64_t total = DIM == 2 ? (int64_t)grid * grid : (int64_t)grid * grid * grid;
-  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < total; k += (int64_t)gridDim.x * blockDim.x) {
-    int64_t r = k;
-    double x[DIM];
-    for (int i = 0; i < DIM; ++i) {
-      x[i] = lo[i] + h[i] * ((double)(r % grid) + 0.5);
-      r /= grid;
-    }
-    G<DevProblem<double>>& PR = *gptr(P);
-    if (!inside_point<DIM, GEOM>(PR.geom, x)) continue;
-    const PointCoef<double> c = point_coef<double, DIM, false>(PR, x);
-    const double sig = field_eval<double, DIM, false>(PR.sigma, x).v;
-    cnt += 1;
-    if (!isfinite(c.sigma_prime) || !isfinite(c.alpha)) {
-      bad += 1;
-      continue;
-    }
-    mn = fmin(mn, c.sigma_prime);
-    mx = fmax(mx, c.sigma_prime);
-    amin = fmin(amin, c.alpha);
-    smin = fmin(smin, sig);
-  }
-  __shared__ double red[6][256];
-  const int t = threadIdx.x;
-  red[0][t] = mn; red[1][t] = mx; red[2][t] = amin; red[3][t] = smin; red[4][t] = bad; red[5][t] = cnt;
-  __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if (t < s) {
-      red[0][t] = fmin(red[0][t], red[0][t + s]);
-      red[1][t] = fmax(red[1][t], red[1][t + s]);
-      red[2][t] = fmin(red[2][t], red[2][t + s]);
-      red[3][t] = fmin(red[3][t], red[3][t + s]);
-      red[4][t] += red[4][t + s];
-      red[5][t] += red[5][t + s];
-    }
-    __syncthreads();
-  }
-  if (t == 0)
-    for (int k = 0; k < 6; ++k) out[blockIdx.x * 6 + k] = red[k][0];
 }
 
 // ------------------------------------------------------------------ diagnostics
@@ -445,63 +323,6 @@ hipError_t launch_clear(uint64_t* p, uint64_t n, uint32_t* counters, hipStream_t
 hipError_t launch_set_params(LaunchParams* lp, uint64_t seed, uint64_t walk_offset_add, hipStream_t st) {
   hipLaunchKernelGGL(set_params_kernel, dim3(1), dim3(64), 0, st, lp, seed, walk_offset_add);
   return hipGetLastError();
-}
-
-template <int DIM, int GEOM>
-static hipError_t classify_t(const void* P, const double* pts, int64_t n, int8_t* inside, uint64_t* counters,
-                             hipStream_t st) {
-  hipLaunchKernelGGL((classify_kernel<DIM, GEOM>), dim3(blocks_for(n, 256)), dim3(256), 0, st,
-                     (const DevProblem<double>*)P, pts, n, inside, counters);
-  return hipGetLastError();
-}
-
-hipError_t launch_classify(int dim, int geom, const void* P64, const double* pts, int64_t n, int8_t* inside,
-                           uint64_t* counters, hipStream_t st) {
-  if (n == 0) return hipSuccess;
-  if (dim == 2) {
-    switch (geom) {
-      case GK_BALL: return classify_t<2, GK_BALL>(P64, pts, n, inside, counters, st);
-      case GK_BOX: return classify_t<2, GK_BOX>(P64, pts, n, inside, counters, st);
-      case GK_POLYGON: return classify_t<2, GK_POLYGON>(P64, pts, n, inside, counters, st);
-      case GK_SDF: return classify_t<2, GK_SDF>(P64, pts, n, inside, counters, st);
-      default: return hipErrorInvalidValue;
-    }
-  }
-  switch (geom) {
-    case GK_BALL: return classify_t<3, GK_BALL>(P64, pts, n, inside, counters, st);
-    case GK_BOX: return classify_t<3, GK_BOX>(P64, pts, n, inside, counters, st);
-    case GK_TRIMESH: return classify_t<3, GK_TRIMESH>(P64, pts, n, inside, counters, st);
-    case GK_SDF: return classify_t<3, GK_SDF>(P64, pts, n, inside, counters, st);
-    default: return hipErrorInvalidValue;
-  }
-}
-
-template <int DIM, int GEOM>
-static hipError_t sigma_t(const void* P, const double* lo, const double* h, int grid, int nblocks, double* out,
-                          hipStream_t st) {
-  hipLaunchKernelGGL((sigma_sample_kernel<DIM, GEOM>), dim3(nblocks), dim3(256), 0, st, (const DevProblem<double>*)P,
-                     lo[0], lo[1], lo[2], h[0], h[1], h[2], grid, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_sigma_sample(int dim, int geom, const void* P64, const double* lo, const double* h, int grid,
-                               int nblocks, double* out, hipStream_t st) {
-  if (dim == 2) {
-    switch (geom) {
-      case GK_BALL: return sigma_t<2, GK_BALL>(P64, lo, h, grid, nblocks, out, st);
-      case GK_BOX: return sigma_t<2, GK_BOX>(P64, lo, h, grid, nblocks, out, st);
-      case GK_POLYGON: return sigma_t<2, GK_POLYGON>(P64, lo, h, grid, nblocks, out, st);
-      case GK_SDF: return sigma_t<2, GK_SDF>(P64, lo, h, grid, nblocks, out, st);
-      default: return hipErrorInvalidValue;
-    }
-  }
-  switch (geom) {
-    case GK_BALL: return sigma_t<3, GK_BALL>(P64, lo, h, grid, nblocks, out, st);
-    case GK_BOX: return sigma_t<3, GK_BOX>(P64, lo, h, grid, nblocks, out, st);
-    case GK_TRIMESH: return sigma_t<3, GK_TRIMESH>(P64, lo, h, grid, nblocks, out, st);
-    case GK_SDF: return sigma_t<3, GK_SDF>(P64, lo, h, grid, nblocks, out, st);
-    default: return hipErrorInvalidValue;
-  }
 }
 
 hipError_t launch_gamma0(int fp64, int dim, const void* P, const double* pts, int64_t n, const int8_t* inside,

@@ -1,4 +1,5 @@
-// Host-side launchers of the kernels in wos_kernels.hip (internal interface).
+// Host-side launchers of the kernels in wos_kernels.hip, wos_grid.hip and wos_walker_*.hip
+// (internal interface).
 #pragma once
 #include <hip/hip_runtime_api.h>
 
@@ -61,8 +62,25 @@ hipError_t launch_finalize_components(const double* sum, const double* sum_sq, c
 hipError_t launch_set_params(LaunchParams* lp, uint64_t seed, uint64_t walk_offset_add, hipStream_t st);
 hipError_t launch_classify(int dim, int geom, const void* P64, const double* pts, int64_t n, int8_t* inside,
                            uint64_t* counters, hipStream_t st);
+// Samples sigma' over the interior ones of cell centres first .. first + n - 1 of a grid
+// (`inside`: n bytes of scratch).
 hipError_t launch_sigma_sample(int dim, int geom, const void* P64, const double* lo, const double* h, int grid,
-                               int nblocks, double* out, hipStream_t st);
+                               int64_t first, int64_t n, int nblocks, int8_t* inside, double* out, hipStream_t st);
+// Candidate grid of a polygon or mesh (P64: the problem on the device with its BVH): squared
+// centre distances, nearest primitives and list starts of the cells, and the total of the list lengths (depth:
+// of the BVH; sums: scan_sum_words(cells) words of scratch) ...
+size_t scan_sum_words(int64_t cells);
+hipError_t launch_grid_count(int dim, int depth, const void* P64, const GridShape& s, const GridRule& rule, double* best,
+                             int32_t* near, uint32_t* count, uint32_t* sums, uint32_t* start, uint32_t* total,
+                             hipStream_t st);
+// ... the lists and records ...
+hipError_t launch_grid_fill(int dim, int depth, const void* P64, const GridShape& s, const GridRule& rule,
+                            const double* best, const int32_t* near, const uint32_t* start, const GridOut& out,
+                            hipStream_t st);
+// ... and the class of every cell of a closed boundary (reach: centre distance up to which a
+// primitive may touch the cell; label, roots: one word per cell of scratch).
+hipError_t launch_cell_classes(int dim, const void* P64, const GridShape& s, double reach, const double* best,
+                               uint32_t* label, uint32_t* roots, uint32_t* n_roots, uint8_t* cls, hipStream_t st);
 hipError_t launch_gamma0(int fp64, int dim, const void* P, const double* pts, int64_t n, const int8_t* inside,
                          void* out, hipStream_t st);
 hipError_t launch_coefficients(int fp64, int dim, const void* P, const double* pts, int64_t n, double* out,

@@ -41,6 +41,37 @@ constexpr int kMeshCellList = 6;
 constexpr int kPolygonCellMax = 32;
 constexpr int kPolygonDeepList = 16;
 
+constexpr int kCellMixed = 2;
+constexpr uint32_t kNoLabel = 0xFFFFFFFFu;
+
+// Cells of a candidate grid: cell (i, j, k) at (k ny + j) nx + i covers the cube of side h
+// from lo + (i, j, k) h (nz = 1 in 2D).
+struct GridShape {
+  int32_t nx = 0, ny = 0, nz = 1;
+  double lo[3] = {0, 0, 0};
+  double h = 0;
+#if defined(__HIPCC__)
+  __host__ __device__
+#endif
+  int64_t cells() const { return (int64_t)nx * ny * nz; }
+};
+
+// How long a cell's list may be: candidates lie within d(centre) + 2 halfdiag + margin; a
+// polygon list over max_list keeps deep_list, a mesh list max_list, and a mesh cell whose
+// centre lies `deep` or more from the surface one.
+struct GridRule {
+  double halfdiag, margin, deep;
+  int32_t max_list, deep_list;
+};
+
+// Arrays of a grid in both precisions (segs: polygons only).
+struct GridOut {
+  void *cells32, *cells64;
+  int32_t* prim;
+  float *segs32, *dc32;
+  double *segs64, *dc64;
+};
+
 // One cell of the polygon candidate grid: `count` candidates at cell_prim / cell_segs /
 // cell_dc [start, start + count), the first kCellInline also held here as start point,
 // edge vector and reciprocal squared length (x0, y0, ex, ey), 1/|e|^2, so that their
@@ -113,6 +144,8 @@ struct DevGeometry {
   const int32_t* cell_prim;
   const T* cell_segs;
   const T* cell_dc;
+  const uint8_t* cell_class;   // per cell: 0 outside, 1 inside, kCellMixed on the boundary; null:
+                               // the mesh is not closed
 };
 
 // Dense trigonometric table of the 2D Fourier fields (alpha, psi and sigma: slots 0, 1,
