@@ -282,6 +282,22 @@ GridShape triangle_grid_shape(const std::vector<double>& tris, int64_t n, int64_
   return g;
 }
 
+GridShape box_grid_shape(const double* lo, const double* hi, int dim, int cells_per_axis) {
+  GridShape g;
+  double ext = 0;
+  for (int k = 0; k < dim; ++k) ext = std::max(ext, hi[k] - lo[k]);
+  g.h = ext / cells_per_axis;
+  int32_t nn[3] = {1, 1, 1};
+  for (int k = 0; k < dim; ++k) {
+    g.lo[k] = lo[k];
+    nn[k] = std::max(1, (int32_t)std::ceil((hi[k] - lo[k]) / g.h));
+  }
+  g.nx = nn[0];
+  g.ny = nn[1];
+  g.nz = nn[2];
+  return g;
+}
+
 double cell_halfdiag(const GridShape& s, int dim) { return 0.5 * s.h * std::sqrt((double)dim); }
 
 double deep_distance(const GridShape& s) { return 8 * s.h; }

@@ -48,6 +48,9 @@ struct SegmentGrid : GridShape {
 GridShape segment_grid_shape(const std::vector<double>& segs, int64_t n, int64_t target_cells);
 GridShape triangle_grid_shape(const std::vector<double>& tris, int64_t n, int64_t target_cells);
 
+// The same over a box, with so many cells along its longest side.
+GridShape box_grid_shape(const double* lo, const double* hi, int dim, int cells_per_axis);
+
 // Half diagonal of a cell, and the centre distance from which a mesh cell keeps one triangle.
 double cell_halfdiag(const GridShape& s, int dim);
 double deep_distance(const GridShape& s);

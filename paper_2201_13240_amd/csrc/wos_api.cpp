@@ -13,6 +13,7 @@
 #include <mutex>
 #include <string>
 #include <tuple>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/wos.h"
@@ -612,6 +613,30 @@ struct DeviceScratch {
   }
 };
 
+// Row lists of the cells of an SDF domain: 128 cells along the longest side of its box (32 in
+// 3D; 128 KB and 256 KB in all). The headers read at most one list per query.
+hipError_t build_sdf_cells(wos_problem* p, const wos_geometry_desc& d, DevProblem<float>& h32, DevProblem<double>& h64) {
+  const GridShape s = box_grid_shape(d.lo, d.hi, p->dim, p->dim == 2 ? 128 : 32);
+  double scale = 1.0;
+  for (int i = 0; i < p->dim; ++i) scale += std::max(std::fabs(d.lo[i]), std::fabs(d.hi[i]));
+  hipError_t e = hipMalloc(&p->grid_mem, (size_t)s.cells() * sizeof(uint64_t));
+  if (e == hipSuccess) e = launch_sdf_cells(p->dim, p->d64(), s, scale, (uint64_t*)p->grid_mem, 0);
+  if (e != hipSuccess) return e;
+  auto point = [&](auto& h) {
+    using T = typename std::remove_reference<decltype(h.epsilon)>::type;
+    h.geom.grid_nx = s.nx;
+    h.geom.grid_ny = s.ny;
+    h.geom.grid_nz = s.nz;
+    for (int i = 0; i < 3; ++i) h.geom.grid_lo[i] = (T)s.lo[i];
+    h.geom.grid_inv_h = (T)(1.0 / s.h);
+    h.geom.grid_h = (T)s.h;
+    h.geom.cells = p->grid_mem;
+  };
+  point(h32);
+  point(h64);
+  return hipSuccess;
+}
+
 // Builds the candidate grid of a polygon or mesh on the device (its BVH is there already):
 // list lengths, their prefix sum, one allocation of the exact size, the lists. Sets the
 // grid pointers of both headers on the host.
@@ -749,8 +774,10 @@ static wos_status problem_create_impl(const wos_problem_desc* desc, int device, 
   };
   const double upload_ms = ms_since(t0);
   t0 = clock::now();
-  if (g.grid.nx > 0) {
-    if ((e = build_grid(p, g, h32, h64)) == hipSuccess) e = upload_headers();
+  const bool rows = g.kind == WOS_GEOM_SDF && g.n_prims >= kSdfGridRows;
+  if (g.grid.nx > 0 || rows) {
+    e = rows ? build_sdf_cells(p, d.geometry, h32, h64) : build_grid(p, g, h32, h64);
+    if (e == hipSuccess) e = upload_headers();
     if (e != hipSuccess) {
       cleanup();
       return fail(e == hipErrorOutOfMemory ? WOS_ERR_OUT_OF_MEMORY : WOS_ERR_DEVICE,

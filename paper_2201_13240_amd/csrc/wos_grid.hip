@@ -649,6 +649,62 @@ __global__ void __launch_bounds__(64) grid_fill_kernel(const DevProblem<double>*
   }
 }
 
+// ------------------------------------------------------------------ SDF cells
+//
+// Rows that can decide the combined field somewhere in a cell. Every primitive field, and
+// with it every minimum and maximum of them, changes by at most the half diagonal hd between
+// the cell's centre and any of its points. A run of unions (or of intersections and
+// subtractions) leaves the minimum (maximum) of its rows and of the field before it, so a
+// row, or everything before the run, that stays 2 hd and a rounding margin away from that
+// value at the centre never is the value itself. The row that is read first sets the field.
+template <int DIM>
+__global__ void __launch_bounds__(64) sdf_cells_kernel(const DevProblem<double>* P, GridShape s, double scale,
+                                                       uint64_t* cells) {
+  double p[3];
+  const int64_t c = block_cell<DIM>(s, p);
+  if (c < 0) return;
+  G<DevGeometry<double>>& g = gptr(P)->geom;
+  const WOS_GLOBAL double* rows = gptr(g.prims);
+  const double hd = 0.5 * s.h * sqrt((double)DIM);
+  auto field = [&](int k) {
+    const WOS_GLOBAL double* r = rows + (size_t)k * kSdfStride;
+    const double f = sdf_shape<double, DIM, false>(r, p, nullptr);
+    return (int)r[0] == 2 ? -f : f;
+  };
+  // FP32 rounding of the point, the cell index and the two fields that are compared
+  auto margin = [&](int k) {
+    const WOS_GLOBAL double* r = rows + (size_t)k * kSdfStride;
+    double m = scale;
+    for (int e = 2; e < kSdfStride; ++e) m += fabs(r[e]);
+    return 1e-5 * m;
+  };
+  double f = __builtin_huge_val(), reach = 0;   // reach: largest margin of the rows behind f
+  uint64_t list = 0;
+  int n = 0;
+  for (int i0 = 0; i0 < g.n_prims;) {
+    const bool uni = (int)rows[(size_t)i0 * kSdfStride] == 0;
+    const double sg = uni ? 1.0 : -1.0;   // sg * value is minimised over the run
+    int i1 = i0;
+    double best = sg * f;
+    for (; i1 < g.n_prims && ((int)rows[(size_t)i1 * kSdfStride] == 0) == uni; ++i1) {
+      best = fmin(best, sg * field(i1));
+      reach = fmax(reach, margin(i1));
+    }
+    if (sg * f > best + 2 * hd + 2 * reach) {
+      list = 0;
+      n = 0;
+    }
+    for (int i = i0; i < i1; ++i)
+      if (sg * field(i) <= best + 2 * hd + 2 * reach) {
+        if (n < kSdfCellRows) list |= (uint64_t)i << (8 * n + 8);
+        ++n;
+      }
+    f = sg * best;
+    i0 = i1;
+  }
+  cells[c] = n <= kSdfCellRows ? list | (uint64_t)n : 0xFFull;
+}
+
 // ------------------------------------------------------------------ prefix sum
 // start[c] = count[0] + ... + count[c - 1] over n cells, and the total: sums of 4096 counts,
 // their running sums, then the counts of each block again.
@@ -812,6 +868,15 @@ hipError_t launch_cell_classes(int dim, const void* P64, const GridShape& s, dou
   else
     hipLaunchKernelGGL((root_class_kernel<GK_TRIMESH>), dim3(512), b, 0, st, P, s, roots, n_roots, cls);
   hipLaunchKernelGGL(cell_class_kernel, g, b, 0, st, label, n, cls);
+  return hipGetLastError();
+}
+
+hipError_t launch_sdf_cells(int dim, const void* P64, const GridShape& s, double scale, uint64_t* cells, hipStream_t st) {
+  const DevProblem<double>* P = (const DevProblem<double>*)P64;
+  if (dim == 2)
+    hipLaunchKernelGGL((sdf_cells_kernel<2>), dim3((unsigned)CellBlocks<2>::blocks(s)), dim3(64), 0, st, P, s, scale, cells);
+  else
+    hipLaunchKernelGGL((sdf_cells_kernel<3>), dim3((unsigned)CellBlocks<3>::blocks(s)), dim3(64), 0, st, P, s, scale, cells);
   return hipGetLastError();
 }
 

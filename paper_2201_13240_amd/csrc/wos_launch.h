@@ -81,6 +81,8 @@ hipError_t launch_grid_fill(int dim, int depth, const void* P64, const GridShape
 // primitive may touch the cell; label, roots: one word per cell of scratch).
 hipError_t launch_cell_classes(int dim, const void* P64, const GridShape& s, double reach, const double* best,
                                uint32_t* label, uint32_t* roots, uint32_t* n_roots, uint8_t* cls, hipStream_t st);
+// Row lists of the cells of an SDF domain (scale: largest coordinate of its box).
+hipError_t launch_sdf_cells(int dim, const void* P64, const GridShape& s, double scale, uint64_t* cells, hipStream_t st);
 hipError_t launch_gamma0(int fp64, int dim, const void* P, const double* pts, int64_t n, const int8_t* inside,
                          void* out, hipStream_t st);
 hipError_t launch_coefficients(int fp64, int dim, const void* P, const double* pts, int64_t n, double* out,

@@ -100,6 +100,12 @@ struct __attribute__((aligned(16))) MeshCell {
   T tail;
 };
 
+// SDF grid cell: the number of rows that can decide the field in the cell (low byte; more
+// than kSdfCellRows: take every row) and their indices, in order, a byte each. Lists of
+// kSdfGridRows rows or more get a grid.
+constexpr int kSdfCellRows = 7;
+constexpr int kSdfGridRows = 6;
+
 // Binary BVH node that stores the bounds of both children, so a visit tests both
 // boxes with one load. A child reference c >= 0 is an inner node index; c < 0 encodes
 // a leaf: -1 - c = (first primitive << 3) | count, count in 1..7.
@@ -140,7 +146,8 @@ struct DevGeometry {
   T grid_inv_h;
   T grid_h;
   T grid_lb_min;         // smallest lower bound a walk step may take (> 2 epsilon)
-  const void* cells;     // CellRec<T>[nx * ny] or MeshCell<T>[nx * ny * nz]
+  const void* cells;     // CellRec<T>[nx * ny], MeshCell<T>[nx * ny * nz] or, for SDF rows,
+                         // uint64_t[nx * ny (* nz)] (kSdfCellRows)
   const int32_t* cell_prim;
   const T* cell_segs;
   const T* cell_dc;

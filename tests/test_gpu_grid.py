@@ -120,3 +120,62 @@ def test_polygon_inside(W, n):
     want = WL.inside_mask(g, p)
     got = W.classify(W.Problem(_problem(2, g)), dev(p)).cpu().numpy().astype(bool)
     assert np.array_equal(got, want)
+
+
+def _sdf_rows(rng, dim, n):
+    """A first shape over most of the box, then rows of every kind: runs of unions,
+    intersections and subtractions, some of them repeated."""
+    rows = [WL.sdf_row(WL.SDF_UNION, "box", [0.0] * dim, [0.9] * dim)]
+    op = WL.SDF_SUBTRACT
+    while len(rows) < n:
+        if rng.uniform() < 0.3:
+            op = int(rng.integers(0, 3))
+        c = rng.uniform(-1.0, 1.0, dim)
+        kind = rng.integers(0, 3)
+        if op == WL.SDF_INTERSECT:   # keeps most of the domain
+            r = WL.sdf_row(op, "ball", 0.2 * c, [rng.uniform(0.9, 1.3)])
+        elif kind == 0:
+            r = WL.sdf_row(op, "ball", c, [rng.uniform(0.03, 0.2)])
+        elif kind == 1:
+            r = WL.sdf_row(op, "box", c, rng.uniform(0.03, 0.2, dim))
+        else:
+            r = WL.sdf_row(op, "halfspace", c, [-rng.uniform(0.9, 1.2) * np.linalg.norm(c)])
+        rows.append(rows[-1] if rng.uniform() < 0.1 and len(rows) > 1 else r)
+    return np.array(rows)
+
+
+def _sdf_field(rows, p):
+    dim = p.shape[1]
+    f = np.full(len(p), np.inf)
+    for r in rows:
+        c = r[2:2 + dim]
+        if r[1] == 0:
+            d = np.linalg.norm(p - c, axis=1) - r[5]
+        elif r[1] == 1:
+            q = np.abs(p - c) - r[5:5 + dim]
+            d = np.where((q > 0).any(1), np.linalg.norm(np.maximum(q, 0), axis=1), q.max(1))
+        else:
+            d = (p @ c - r[5]) / np.linalg.norm(c)
+        f = np.minimum(f, d) if r[0] == 0 else np.maximum(f, d if r[0] == 1 else -d)
+    return f
+
+
+@pytest.mark.parametrize("dim", [2, 3])
+@pytest.mark.parametrize("n", [5, 6, 7, 33, 256])
+def test_sdf_cell_rows_decide_as_all_rows(W, dim, n):
+    """The field from the rows a cell lists against all rows in numpy, inside, outside and
+    beyond the box, for short lists (no cells), lists at the limit and long ones. FP64 to
+    1e-12; FP32 to 16 units in the last place of the coordinates (about ten roundings)."""
+    for seed in range(4):
+        rng = np.random.default_rng([n, dim, seed])
+        rows = _sdf_rows(rng, dim, n)
+        p = np.concatenate([rng.uniform(-1.0, 1.0, (4000, dim)), rng.uniform(-1.5, 1.5, (500, dim))])
+        h = W.Problem(_problem(dim, WL.geom_sdf(rows, [-1.0] * dim, [1.0] * dim)))
+        want = -_sdf_field(rows, p)
+        for precision, tol in (("fp64", 1e-12), ("fp32", 16 * 2.0 ** -24 * 2)):
+            x = p if precision == "fp64" else p.astype(np.float32).astype(np.float64)
+            ref = want if precision == "fp64" else -_sdf_field(rows, x)
+            d, _ = W.eval_distance(h, dev(x), precision)
+            np.testing.assert_allclose(d.cpu().numpy(), ref, rtol=0, atol=tol)
+        got = W.classify(h, dev(p)).cpu().numpy().astype(bool)
+        assert np.array_equal(got, want > 0)
