@@ -1010,10 +1010,14 @@ wos_status check_items(const wos_batch_item* items, int n_items, const wos_optio
   return WOS_OK;
 }
 
-// Bytes of one lane's gradient record, and the lanes of any persistent grid on the device
-// (resident threads per CU at most 2048).
-size_t grad_record_bytes(const Schedule& s) {
-  return (size_t)(1 + 3 * s.dim) * (s.fp64 ? sizeof(double) : sizeof(float));
+// Bytes of a launch's gradient records (1 + 3 dim numbers for each of the 2048 threads a CU may
+// hold), and of the records of one wave: five waves per SIMD take 94-98% of them.
+size_t grad_bytes(const Schedule& s, int cus) {
+  return (size_t)cus * 2048u * (size_t)(1 + 3 * s.dim) * (s.fp64 ? sizeof(double) : sizeof(float));
+}
+size_t grad_wave_bytes(const Schedule& s) {
+  const int stride = s.dim == 2 ? GradRecord<2>::kStride : GradRecord<3>::kStride;
+  return (size_t)kGradRecords * stride * (s.fp64 ? sizeof(double) : sizeof(float));
 }
 
 std::mutex g_occ_mutex;
@@ -1039,8 +1043,6 @@ wos_status device_cus(int device, int* cus) {
   return WOS_OK;
 }
 
-uint64_t max_grid_lanes(int cus) { return (uint64_t)cus * 2048u; }
-
 // Persistent grid for a block size: resident blocks per CU times CUs.
 wos_status grid_for_block(Schedule& s, unsigned block) {
   int cus = 0;
@@ -1053,6 +1055,9 @@ wos_status grid_for_block(Schedule& s, unsigned block) {
     int per_cu = 0;
     WOS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, walker_symbol(s.fp64, s.dim, s.geom, s.mode), (int)block, 0));
     unsigned grid = (unsigned)std::max(1, per_cu) * (unsigned)cus;
+    // mode 1 may hold gradient records: no more waves than they are allotted for
+    if (s.mode == 1)
+      grid = (unsigned)std::min<size_t>(grid, std::max<size_t>(1, grad_bytes(s, cus) / grad_wave_bytes(s) / (block / 64)));
     it = g_occ.emplace(key, grid).first;
   }
   s.block = block;
@@ -1180,7 +1185,7 @@ struct Workspace {
   uint32_t* counter = nullptr;
   LaunchParams* lp = nullptr;
   uint64_t* slots = nullptr;      // [slots of the largest launch][slot_words]
-  void* grad = nullptr;           // per-lane gradient records, when any item asks for gradients
+  void* grad = nullptr;           // gradient records, when any item asks for gradients
 };
 
 }  // namespace
@@ -1223,7 +1228,7 @@ WsLayout ws_layout(const Schedule& s, int n_items, uint64_t max_slots, int cus) 
   L.counter = take(sizeof(uint32_t) * kTileQueues * kTileQueueStride);
   L.lp = take(sizeof(LaunchParams));
   L.slots = take((size_t)std::max<uint64_t>(max_slots, 1) * s.slot_words * sizeof(uint64_t));
-  L.grad = take(s.grad ? grad_record_bytes(s) * max_grid_lanes(cus) : 0);
+  L.grad = take(s.grad ? grad_bytes(s, cus) : 0);
   L.total = off;
   return L;
 }

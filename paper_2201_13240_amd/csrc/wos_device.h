@@ -1437,10 +1437,11 @@ constexpr int kPrimStride2 = 4;    // segment: x0 y0 x1 y1
 constexpr int kPrimStride3 = 12;   // triangle: a, b, c, (pad)
 constexpr int kStackDepth = 48;     // private (scratch) stack: any tree the host accepts
 // LDS stack depths of the walker. The walker's LDS must leave room for five 256-thread
-// blocks per CU: the mesh walker takes trees of depth <= 15 (30 KB in FP32), the polygon
-// walker, whose candidate grid answers most queries, trees of depth <= 11 (22 KB; up to
-// 8192 edges). Deeper trees use the private stack.
-constexpr int kLdsStackDepth = 15;
+// blocks per CU beside the queue of finished walks: the mesh walker takes trees of depth
+// <= 13 (26 KB in FP32; up to 32,768 triangles), the polygon walker, whose candidate grid
+// answers most queries, trees of depth <= 11 (22 KB; up to 8192 edges). Deeper trees use the
+// private stack.
+constexpr int kLdsStackDepth = 13;
 constexpr int kLdsStackDepthPolygon = 11;
 
 // Traversal stack of far children with their box distances, either in LDS (one column

@@ -31,7 +31,7 @@ struct WalkerLaunch {
   int rr;
   double ww_lo;
   double ww_hi;       // 0: no splitting
-  void* grad;         // gradient records (T[grid lane][1 + 3 dim]) or null
+  void* grad;         // gradient records (T[grid wave][kGradRecords][2 + 3 dim]) or null
   uint64_t* events;   // non-null selects the event-counting build of the walker
 };
 

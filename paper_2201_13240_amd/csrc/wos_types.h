@@ -241,12 +241,17 @@ constexpr uint32_t kMaxTileLen = 65536;   // keeps a slot's limbs below 2^49 bef
 inline constexpr int slot_words(int grad_dim) { return grad_dim ? (kSlotGrad + 2 * kFxLimbs * grad_dim + 15) / 16 * 16 : 16; }
 
 // Per-walk record of the gradient estimate (supplemental Sec. 2), in the walker's
-// precision: [A0, a (dim), b (dim), grad gamma(x0) (dim)]. One record per lane of the
-// persistent grid (a lane runs one walk at a time); it is read back when the walk ends.
+// precision: [A0, y - x0 (dim), direction of the exit point (dim), grad gamma(x0) (dim), R],
+// of the first ball; R is negative after a volume event and 0 for a walk that had no ball.
+// A wave of the persistent grid holds kGradRecords of them: one per lane, whose walk writes
+// it, and one per entry of its queue of finished walks.
 template <int DIM>
 struct GradRecord {
-  static constexpr int kStride = 1 + 3 * DIM;
+  static constexpr int kRadius = 1 + 3 * DIM;
+  static constexpr int kStride = 2 + 3 * DIM;
 };
+constexpr int kGradQueue = 24;
+constexpr int kGradRecords = 64 + kGradQueue;
 
 // Tile queues of a launch of several items (one per XCD), and the distance of their
 // counters in 32-bit words (a cache line each).

@@ -86,7 +86,7 @@ struct WalkerArgs {
   int32_t rr;
   T ww_lo;
   T ww_hi;               // > 0: expected-value splitting above this weight (delta tracking)
-  T* grad;               // [grid lane][GradRecord<DIM>::kStride] or null: gradient records
+  T* grad;               // [grid wave][kGradRecords][GradRecord<DIM>::kStride] or null
   uint64_t* events;      // event-counting build only: [kEvents]
 };
 
@@ -328,26 +328,34 @@ struct SlotCache {
 // the other 61: with the boundary terms evaluated there, they took 3600 of an iteration's
 // 26,800 cycles on the star polygon. The terms are the same, in the same order, so the
 // estimates are too. Called with every lane active.
+//
+// With gradients (GD = dim) an entry also carries the walk's gradient record: a lane appends
+// the number of its record and takes over the one the entry held before, so records are
+// swapped, never copied. Their kernel ratios, two or three Bessel functions each, are formed
+// here too.
 constexpr int32_t kNoBoundary = -1;   // `prim` of a walk without a boundary term
 
-template <typename T, int DIM, int CAP>
+template <typename T, int DIM, int CAP, int GD>
 struct EmitQueue {
   static constexpr bool kComp = sizeof(T) == 4;   // only the FP32 walk carries a compensation
-  static constexpr int kBytes = CAP * (int)(8 + 4 + sizeof(T) * (DIM + 2 + (kComp ? 1 : 0)));
+  static constexpr int kBytes = CAP * (int)(8 + 4 + (GD ? 4 : 0) + sizeof(T) * (DIM + 2 + (kComp ? 1 : 0)));
   uint2* meta;     // [CAP] (steps | flags, slot reference)
   T* val;          // [DIM + 2 or 3][CAP]: last point, weight, estimate, its compensation
   int32_t* prim;   // [CAP]
+  uint32_t* rec;   // [CAP] gradient records of the entries, spare ones in the free entries
   uint32_t n;      // queued entries; wave-uniform
 
-  __device__ __forceinline__ void init(unsigned char* base) {
+  __device__ __forceinline__ void init(unsigned char* base, uint32_t lane) {
     meta = (uint2*)base;
     val = (T*)(meta + CAP);
     prim = (int32_t*)(val + CAP * (DIM + 2 + (kComp ? 1 : 0)));
+    rec = (uint32_t*)(prim + CAP);
     n = 0;
+    if (GD && lane < (uint32_t)CAP) rec[lane] = 64u + lane;
   }
   // Appends the calling lane's walk if it ended and fits; returns whether it was taken.
   __device__ __forceinline__ bool push(bool ended, bool boundary, const T* x, int p, T w, T A, T Ac,
-                                       uint32_t steps_flags, uint32_t ref) {
+                                       uint32_t steps_flags, uint32_t ref, uint32_t& record) {
     const uint64_t fin = __ballot(ended);
     const uint32_t r = n + lanes_below(fin);
     const bool taken = ended && r < (uint32_t)CAP;
@@ -359,6 +367,11 @@ struct EmitQueue {
       val[DIM * CAP + r] = w;
       val[(DIM + 1) * CAP + r] = A;
       if constexpr (kComp) val[(DIM + 2) * CAP + r] = Ac;
+      if constexpr (GD > 0) {
+        const uint32_t spare = rec[r];
+        rec[r] = record;
+        record = spare;
+      }
     }
     n = (uint32_t)uniform_int((int)min(n + (uint32_t)__popcll(fin), (uint32_t)CAP));
     return taken;
@@ -371,9 +384,10 @@ struct EmitQueue {
     if (lane < n && meta[lane].y == from) meta[lane].y = to;
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   }
+  // grad: the wave's gradient records, or null
   template <int GEOM, int WORDS, int ENTRIES>
-  __device__ __forceinline__ void drain(G<DevProblem<T>>& P, int compensated, SlotCache<WORDS, ENTRIES>& cache,
-                                        uint64_t* slots, int slot_words) {
+  __device__ __forceinline__ void drain(G<DevProblem<T>>& P, int compensated, const T* grad,
+                                        SlotCache<WORDS, ENTRIES>& cache, uint64_t* slots, int slot_words) {
     const uint32_t lane = lane_here();
     // entries were written by other lanes of this wave: keep the compiler from moving
     // the reads above those LDS stores (the wave's LDS operations run in order)
@@ -390,8 +404,40 @@ struct EmitQueue {
         closest_point<T, DIM, GEOM>(P.geom, x, p, xb);
         add_estimate(A, Ac, val[DIM * CAP + lane] * boundary_value<T, DIM>(P, xb), compensated);
       }
-      cache.template emit<0>(m.y, slots, slot_words, (double)A + (double)Ac, m.x, kStepMask, kFlagCapped, kFlagRR,
-                             nullptr);
+      const double v = (double)A + (double)Ac;
+      if (GD > 0 && grad) {
+        // per-walk gradient estimate (supplemental Sec. 2): A0 a + (A - A0) b - A grad
+        // gamma(x0), a = grad G/G at the first ball's y, b = a after a volume event or grad
+        // P/P at its exit point z
+        const T* gr = grad + (size_t)rec[lane] * GradRecord<DIM>::kStride;
+        const T Rs = gr[GradRecord<DIM>::kRadius], R = m_fabs(Rs);
+        T a[DIM], b[DIM];
+#pragma unroll
+        for (int i = 0; i < DIM; ++i) a[i] = b[i] = 0;
+        if (R > (T)0) {
+          T w[DIM], r2 = 0;
+#pragma unroll
+          for (int i = 0; i < DIM; ++i) {
+            w[i] = gr[1 + i];
+            r2 = m_fma(w[i], w[i], r2);
+          }
+          const T fg = grad_ratio_green<T, DIM>(m_sqrt(r2), R, P.sqrt_sigma_bar);
+          const T fp = grad_ratio_poisson<T, DIM>(R, P.sqrt_sigma_bar);
+#pragma unroll
+          for (int i = 0; i < DIM; ++i) {
+            a[i] = fg * w[i];
+            b[i] = Rs < (T)0 ? fg * w[i] : fp * R * gr[1 + DIM + i];
+          }
+        }
+        double g[DIM];
+        const double a0 = (double)gr[0];
+#pragma unroll
+        for (int c = 0; c < DIM; ++c)
+          g[c] = a0 * (double)a[c] + (v - a0) * (double)b[c] - v * (double)gr[1 + 2 * DIM + c];
+        cache.template emit<GD>(m.y, slots, slot_words, v, m.x, kStepMask, kFlagCapped, kFlagRR, g);
+      } else {
+        cache.template emit<0>(m.y, slots, slot_words, v, m.x, kStepMask, kFlagCapped, kFlagRR, nullptr);
+      }
     }
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     n = 0;
@@ -437,15 +483,16 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
   __shared__ uint64_t s_slot_cache[4 * kCacheEntries * kCacheWords];
   SlotCache<kCacheWords, kCacheEntries> cache;
   cache.init(s_slot_cache + wave * (kCacheEntries * kCacheWords), lane);
-  // queue of finished walks (not with gradient records, whose results come from a
-  // per-lane record; not for meshes, whose LDS stacks leave no room at five blocks per CU;
-  // 56 entries are what five blocks of the FP32 polygon walker leave room for)
-  constexpr bool kQueue = MODE != 1 && GEOM != GK_TRIMESH;
-  constexpr int kQueueCap = (sizeof(T) == 4 && GEOM == GK_POLYGON) ? 56 : 64;
-  using Queue = EmitQueue<T, DIM, kQueueCap>;
-  __shared__ __align__(16) unsigned char s_queue[kQueue ? 4 * Queue::kBytes : 16];
+  // queue of finished walks: 64 entries, one per lane, or what five FP32 blocks (32,000 bytes
+  // each) leave room for; with gradient records as many as there are spare records
+  constexpr int kQueueCap = EXTRA                                        ? kGradQueue
+                            : sizeof(T) == 4 && GEOM == GK_POLYGON       ? 56
+                            : sizeof(T) == 4 && GEOM == GK_TRIMESH       ? 22
+                                                                         : 64;
+  using Queue = EmitQueue<T, DIM, kQueueCap, EXTRA ? DIM : 0>;
+  __shared__ __align__(16) unsigned char s_queue[4 * Queue::kBytes];
   Queue queue;
-  if constexpr (kQueue) queue.init(s_queue + wave * Queue::kBytes);
+  queue.init(s_queue + wave * Queue::kBytes, lane);
   Tally tally = {0, 0, 0, 0};
   uint32_t ev[kEvents];
   if constexpr (COUNT) {
@@ -474,8 +521,11 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
   // to last_prim, of weight Pi; slot: accumulation slot of the walk
   int phase = 0;
   uint32_t slot = 0;
-  T* const grad_rec = EXTRA && a.grad ? a.grad + ((size_t)blockIdx.x * blockDim.x + threadIdx.x) * GradRecord<DIM>::kStride
-                                     : nullptr;
+  // gradient records of the wave, and the number of the lane's own
+  T* const grad_recs = EXTRA && a.grad ? a.grad + (size_t)(blockIdx.x * (blockDim.x >> 6) + (uint32_t)wave) *
+                                                      (kGradRecords * GradRecord<DIM>::kStride)
+                                       : nullptr;
+  uint32_t record = lane;
   T x[DIM];
   T gamma0 = 0, gx = 0;
   bool gx_known = false;
@@ -511,29 +561,11 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
     // ---------------------------------------------------------------- finished walks
     // A walk that ended in the last iteration adds its estimate A + Ac, its square, its
     // distance queries and flags (in nsteps) to its slot here, where little else is live.
-    if constexpr (kQueue) {
-      for (;;) {
-        if (queue.push(phase >= 4, phase == 5, x, last_prim, Pi, A, Ac, nsteps, slot)) phase = 0;
-        if (queue.n == 0u || (queue.n < (uint32_t)kQueueCap && __ballot(phase != 0) != 0)) break;
-        queue.template drain<GEOM>(*Pp, a.compensated, cache, slots, a.slot_words);
-        if (__ballot(phase >= 4) == 0) break;
-      }
-    } else if (phase == 4) {
-      const double v = (double)A + (double)Ac;
-      if (EXTRA && a.grad) {
-        // per-walk gradient estimate (supplemental Sec. 2):
-        // A0 a + (A - A0) b - A grad gamma(x0), from the lane's record
-        double g[DIM];
-        const T* gr = grad_rec;
-        const double a0 = (double)gr[0];
-#pragma unroll
-        for (int c = 0; c < DIM; ++c)
-          g[c] = a0 * (double)gr[1 + c] + (v - a0) * (double)gr[1 + DIM + c] - v * (double)gr[1 + 2 * DIM + c];
-        cache.template emit<DIM>(slot, slots, a.slot_words, v, nsteps, kStepMask, kFlagCapped, kFlagRR, g);
-      } else {
-        cache.template emit<0>(slot, slots, a.slot_words, v, nsteps, kStepMask, kFlagCapped, kFlagRR, nullptr);
-      }
-      phase = 0;
+    for (;;) {
+      if (queue.push(phase >= 4, phase == 5, x, last_prim, Pi, A, Ac, nsteps, slot, record)) phase = 0;
+      if (queue.n == 0u || (queue.n < (uint32_t)kQueueCap && __ballot(phase != 0) != 0)) break;
+      queue.template drain<GEOM>(*Pp, a.compensated, grad_recs, cache, slots, a.slot_words);
+      if (__ballot(phase >= 4) == 0) break;
     }
     // ---------------------------------------------------------------- refill idle lanes
     uint64_t idle = __ballot(phase == 0);
@@ -589,7 +621,7 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
           } else {
             uint32_t held;
             const uint32_t ref = cache.take(tl_slot0, slots, a.slot_words, slot, &held);
-            if constexpr (kQueue) queue.retarget(ref, held);
+            queue.retarget(ref, held);
             tl_slot0 = uniform_int((int)ref);
 #pragma unroll
             for (int i = 0; i < DIM; ++i) tl_x[i] = uniform_val((T)gptr(it.points)[(size_t)tl_p0 * DIM + i]);
@@ -680,7 +712,6 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
         // sigma' = sigma_bar needs no division. U(x_k) ~ T U(z) + S; Pi = prod T.
         bool done = false, terminal = false, sample = false;
         uint32_t flag = 0;
-        T gb = 0;
         T q[DIM], xn[DIM];
 #pragma unroll
         for (int i = 0; i < DIM; ++i) {
@@ -717,11 +748,6 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
               done = true;
               flag = kFlagCapped;
             } else if (d < P.epsilon) {
-              if constexpr (!kQueue) {
-                T xb[DIM];
-                closest_point<T, DIM, GEOM>(P.geom, x, prim, xb);
-                gb = boundary_value<T, DIM>(P, xb);
-              }
               terminal = true;
               if constexpr (COUNT) {
                 ++ev[EV_TERMINAL];
@@ -765,7 +791,6 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
           phase = 2;
         } else if (terminal) {
           Pi *= m_exp(cq.gamma - gamma0);
-          if constexpr (!kQueue) add_estimate(A, Ac, Pi * gb, a.compensated);
           done = true;
         } else if (sample) {
           const NfBall<T, DIM> nb = nf_ball<T, DIM>(nf_R, P.sqrt_sigma_bar, nf_c);
@@ -779,7 +804,7 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
         }
         if (done) {
           nsteps = (nsteps & kStepMask) | flag;
-          phase = kQueue && terminal ? 5 : 4;   // added to its slot at the top of the next iteration
+          phase = terminal ? 5 : 4;   // added to its slot at the top of the next iteration
         }
       } else {
         bool done = false, terminal = false, sampled = false;
@@ -816,7 +841,8 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
             } else if (d < P.epsilon) {
               // epsilon shell: the walk returns g(xbar) (Alg. 1) times its weight, which
               // needs gamma at the current point (g(xbar) itself is taken from the queue)
-              if constexpr (!kQueue) {
+              if (EXTRA && (split_state & 0xFFu)) {
+                // sibling branches add to the estimate after this one: its term goes first
                 T xb[DIM];
                 closest_point<T, DIM, GEOM>(P.geom, x, prim, xb);
                 gb = boundary_value<T, DIM>(P, xb);
@@ -881,18 +907,15 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
           if (EXTRA && a.grad) {
             // gradient record of the walk: grad gamma(x0) now, the first ball's terms
             // when it is sampled (they stay zero for a walk that starts in the shell)
-            T* gr = grad_rec;
+            T* gr = grad_recs + (size_t)record * GradRecord<DIM>::kStride;
             gr[0] = 0;
 #pragma unroll
-            for (int i = 0; i < DIM; ++i) {
-              gr[1 + i] = 0;
-              gr[1 + DIM + i] = 0;
-              gr[1 + 2 * DIM + i] = ggx[i];
-            }
+            for (int i = 0; i < DIM; ++i) gr[1 + 2 * DIM + i] = ggx[i];
+            gr[GradRecord<DIM>::kRadius] = 0;
           }
         } else if (terminal) {
-          if constexpr (kQueue) Pi = pe;
-          else add_estimate(A, Ac, pe * gb, a.compensated);
+          Pi = pe;
+          if (EXTRA && (split_state & 0xFFu)) add_estimate(A, Ac, pe * gb, a.compensated);
           done = true;
         } else if (sampled) {
           const T mu = uniform01<T, SL::kMu>(rng);
@@ -907,25 +930,18 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
           add_estimate(A, Ac, term, a.compensated);
           if constexpr (COUNT) ++ev[volume ? EV_VOLUME : EV_EXIT];
           if (EXTRA && a.grad && (nsteps & kStepMask) == 1u && (split_state >> 8) == 0u) {
-            // first ball (supplemental Sec. 2): A0 = its source term, a = grad G/G at y,
-            // b = a after a volume event or grad P/P at the exit point z
-            T* gr = grad_rec;
-            T w[DIM], r2 = 0;
-#pragma unroll
-            for (int i = 0; i < DIM; ++i) {
-              w[i] = q[i] - x[i];
-              r2 = m_fma(w[i], w[i], r2);
-            }
-            const T fg = grad_ratio_green<T, DIM>(m_sqrt(r2), R, P.sqrt_sigma_bar);
-            const T fp = grad_ratio_poisson<T, DIM>(R, P.sqrt_sigma_bar);
+            // first ball (supplemental Sec. 2): its source term, y - x, the direction of its exit
+            // point and its radius, negative after a volume event
+            T* gr = grad_recs + (size_t)record * GradRecord<DIM>::kStride;
             T vz[DIM];
             uniform_direction<T, DIM, SL::kExitDir>(rng, vz);   // the exit direction drawn below
             gr[0] = term;
 #pragma unroll
             for (int i = 0; i < DIM; ++i) {
-              gr[1 + i] = fg * w[i];
-              gr[1 + DIM + i] = volume ? fg * w[i] : fp * R * vz[i];
+              gr[1 + i] = q[i] - x[i];
+              gr[1 + DIM + i] = vz[i];
             }
+            gr[GradRecord<DIM>::kRadius] = volume ? -R : R;
           }
           if (volume) {
             // null event: weight (1 - sigma'(y)/sigma_bar) e^{gamma(y) - gamma(x)}, move to y
@@ -1003,7 +1019,7 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
             rng.init(rng.walk, rng.point, (rng.problem & 0xFFFFu) | ((split_state >> 8) << 16));
             pending = false;
           } else {
-            phase = kQueue && terminal ? 5 : 4;   // added to its slot at the top of the next iteration
+            phase = terminal ? 5 : 4;   // added to its slot at the top of the next iteration
           }
         }
       }
