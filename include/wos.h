@@ -288,7 +288,8 @@ wos_status wos_solve(const wos_batch_item* items, int32_t n_items, const wos_opt
  * any work is queued. Walks per point that do not fit at once run in several launches.
  * Calls on one GPU share its array: two calls that overlap on one GPU (other streams or
  * host threads) race and corrupt each other's results; calls in one stream are safe.
- * Synchronous like wos_solve up to the item-table upload; then asynchronous on stream. */
+ * Asynchronous on stream like wos_solve (a job of several launches waits for the upload of
+ * its item tables). */
 wos_status wos_solve_static(const wos_batch_item* items, int32_t n_items, const wos_options* opt, void* stream);
 
 /* Runs the same walks as wos_solve (same outputs, accumulated the same way) with the

@@ -1152,7 +1152,7 @@ void build_items(const wos_batch_item* items, int n_items, const wos_options* op
                  uint64_t nw, const std::vector<int8_t*>& inside, const std::vector<void*>& gamma0,
                  std::vector<DevItem>& dit, uint64_t* n_tiles, uint64_t* n_slots) {
   dit.resize(n_items);
-  uint64_t pbase = 0;
+  uint64_t rblock = 0;
   for (int k = 0; k < n_items; ++k) {
     const wos_batch_item& it = items[k];
     DevItem& d = dit[k];
@@ -1171,9 +1171,9 @@ void build_items(const wos_batch_item* items, int n_items, const wos_options* op
     d.n_points = it.n_points;
     d.walks = nw;
     d.walk_offset = opt->walk_offset + w0;
-    d.point_base = pbase;
+    d.reduce_block = rblock;
     d.problem_index = it.problem_index;
-    pbase += (uint64_t)it.n_points;
+    rblock += ((uint64_t)it.n_points + kReducePoints - 1) / kReducePoints;
   }
   layout_items(dit, s.tile_walks, n_tiles, n_slots);
 }
@@ -1314,47 +1314,55 @@ WalkerLaunch walker_launch(const wos_options* opt, const Schedule& s, const Work
   return L;
 }
 
-// Classifies every query point (FP64) and evaluates gamma at the interior ones in the
-// walker's precision.
-hipError_t classify_items(const wos_batch_item* items, int n_items, const Schedule& s, const Workspace& w,
-                          hipStream_t st) {
-  uint64_t pb = 0;
-  for (int k = 0; k < n_items; ++k) {
-    const wos_batch_item& it = items[k];
-    hipError_t e = launch_classify(s.dim, s.geom, it.problem->d64(), it.points, it.n_points, w.inside + pb,
-                                   it.counters, st);
-    if (e == hipSuccess)
-      e = launch_gamma0(s.fp64, s.dim, s.fp64 ? it.problem->d64() : it.problem->d32(), it.points, it.n_points,
-                        w.inside + pb, w.gamma0 + pb * (s.fp64 ? 8 : 4), st);
-    if (e != hipSuccess) return e;
-    pb += (uint64_t)it.n_points;
+// Prepares the first launch of a schedule on the device (launch_prep, kPrepItems items at a
+// time). The item table travels with the launches where the schedule has one launch; that of
+// several launches is copied (upload_items).
+wos_status prep_job(const wos_batch_item* items, int n_items, const Schedule& s, const Workspace& w,
+                    const std::vector<DevItem>& dit, uint64_t n_slots, uint64_t seed, hipStream_t st) {
+  PrepArgs a;
+  for (int first = 0; first < n_items; first += kPrepItems) {
+    a.n = std::min(kPrepItems, n_items - first);
+    for (int k = 0; k < a.n; ++k) {
+      a.item[k] = dit[first + k];
+      a.problem64[k] = items[first + k].problem->d64();
+    }
+    a.table = s.n_launches == 1 ? w.items + first : nullptr;
+    a.lp = first ? nullptr : w.lp;
+    a.seed = seed;
+    a.counters = first ? nullptr : w.counter;
+    a.slots = w.slots;
+    a.slot_words = first ? 0 : n_slots * (uint64_t)s.slot_words;
+    WOS_HIP(launch_prep(s.fp64, s.dim, s.geom, a, st));
   }
-  return hipSuccess;
+  return WOS_OK;
 }
 
-// Enqueues [clear, walker, reduce per item] for every launch of the schedule. With
-// `marks`, an event pair is recorded around each walker launch (eager timing only: a
-// captured job takes none).
-wos_status enqueue_job(const wos_batch_item* items, int n_items, const wos_options* opt, const Schedule& s,
-                       const Workspace& w, const std::vector<std::vector<DevItem>>& dit,
-                       const std::vector<uint64_t>& n_tiles, const std::vector<uint64_t>& n_slots, bool classify,
-                       uint64_t* events, hipStream_t st, const std::vector<hipEvent_t>* marks = nullptr) {
-  if (classify) WOS_HIP(classify_items(items, n_items, s, w, st));
+// Enqueues [clear, walker, reduce] for every launch of the schedule (`cleared`: the first one
+// finds its slots and counters cleared). With `marks`, an event pair is recorded around each
+// walker launch (eager timing only: a captured job takes none).
+wos_status enqueue_job(int n_items, const wos_options* opt, const Schedule& s, const Workspace& w,
+                       const std::vector<std::vector<DevItem>>& dit, const std::vector<uint64_t>& n_tiles,
+                       const std::vector<uint64_t>& n_slots, bool cleared, uint64_t* events, hipStream_t st,
+                       const std::vector<hipEvent_t>* marks = nullptr) {
   for (int c = 0; c < s.n_launches; ++c) {
     if (n_tiles[c] == 0) continue;
-    WOS_HIP(launch_clear(w.slots, n_slots[c] * (uint64_t)s.slot_words, w.counter, st));
-    WalkerLaunch L = walker_launch(opt, s, w, w.items + (size_t)c * n_items, n_items, n_tiles[c]);
+    if (!(cleared && c == 0)) WOS_HIP(launch_clear(w.slots, n_slots[c] * (uint64_t)s.slot_words, w.counter, st));
+    const DevItem* table = w.items + (size_t)c * n_items;
+    WalkerLaunch L = walker_launch(opt, s, w, table, n_items, n_tiles[c]);
     L.events = events;
     if (marks) WOS_HIP(hipEventRecord((*marks)[2 * c], st));
     WOS_HIP(launch_walker(L, st));
     if (marks) WOS_HIP(hipEventRecord((*marks)[2 * c + 1], st));
-    for (int k = 0; k < n_items; ++k) WOS_HIP(launch_reduce(s.grad_dim, dit[c][k], w.slots, s.slot_words, st));
+    const DevItem& last = dit[c].back();
+    const uint64_t blocks = last.reduce_block + ((uint64_t)last.n_points + kReducePoints - 1) / kReducePoints;
+    WOS_HIP(launch_reduce(s.grad_dim, table, n_items, blocks, w.slots, s.slot_words, st));
   }
   return WOS_OK;
 }
 
 wos_status upload_items(const Schedule& s, int n_items, const Workspace& w, const std::vector<std::vector<DevItem>>& dit,
                         hipStream_t st) {
+  if (s.n_launches == 1) return WOS_OK;   // written by prep_job
   // Pageable host source: the runtime stages the copy before returning.
   std::vector<DevItem> all_items((size_t)n_items * s.n_launches);
   for (int c = 0; c < s.n_launches; ++c) std::copy(dit[c].begin(), dit[c].end(), all_items.begin() + (size_t)c * n_items);
@@ -1388,11 +1396,8 @@ static wos_status solve_impl(const wos_batch_item* items, int32_t n_items, const
   ws_bind(w, base, L);
   r = prepare(items, n_items, opt, s, w, dit, n_tiles, n_slots);
   if (r == WOS_OK) r = upload_items(s, n_items, w, dit, st);
-  if (r == WOS_OK) {
-    const hipError_t e = launch_set_params(w.lp, opt->seed, 0, st);
-    r = e != hipSuccess ? fail(WOS_ERR_DEVICE, "launch failed")
-                        : enqueue_job(items, n_items, opt, s, w, dit, n_tiles, n_slots, true, events, st);
-  }
+  if (r == WOS_OK) r = prep_job(items, n_items, s, w, dit[0], n_slots[0], opt->seed, st);
+  if (r == WOS_OK) r = enqueue_job(n_items, opt, s, w, dit, n_tiles, n_slots, true, events, st);
   (void)hipFreeAsync(base, st);
   return r;
 }
@@ -1440,8 +1445,8 @@ static wos_status solve_static_impl(const wos_batch_item* items, int32_t n_items
   std::vector<uint64_t> n_tiles, n_slots;
   if ((r = prepare(items, n_items, &o, s, w, dit, n_tiles, n_slots)) != WOS_OK) return r;
   if ((r = upload_items(s, n_items, w, dit, st)) != WOS_OK) return r;
-  WOS_HIP(launch_set_params(w.lp, o.seed, 0, st));
-  return enqueue_job(items, n_items, &o, s, w, dit, n_tiles, n_slots, true, nullptr, st);
+  if ((r = prep_job(items, n_items, s, w, dit[0], n_slots[0], o.seed, st)) != WOS_OK) return r;
+  return enqueue_job(n_items, &o, s, w, dit, n_tiles, n_slots, true, nullptr, st);
 }
 
 wos_status wos_solve_static(const wos_batch_item* items, int32_t n_items, const wos_options* opt, void* stream) {
@@ -1506,9 +1511,8 @@ wos_status plan_build(const wos_batch_item* items, int32_t n_items, const wos_op
   };
   if ((r = prepare(items, n_items, opt, s, P->ws, P->dit, P->n_tiles, P->n_slots)) != WOS_OK) return bail(r, g_error);
   if ((r = upload_items(s, n_items, P->ws, P->dit, st)) != WOS_OK) return bail(r, g_error);
-  // classification and gamma(x0) once, outside the graph
-  if ((e = classify_items(items, n_items, s, P->ws, st)) != hipSuccess)
-    return bail(WOS_ERR_DEVICE, "classification launch failed");
+  // classification, gamma(x0) and the item table once, outside the graph
+  if ((r = prep_job(items, n_items, s, P->ws, P->dit[0], 0, 0, st)) != WOS_OK) return bail(r, g_error);
   // capture clear + walker + reduce of every launch on a private stream
   hipStream_t cap;
   if ((e = hipStreamCreateWithFlags(&cap, hipStreamNonBlocking)) != hipSuccess) return bail(WOS_ERR_DEVICE, "stream creation failed");
@@ -1520,7 +1524,7 @@ wos_status plan_build(const wos_batch_item* items, int32_t n_items, const wos_op
     (void)hipStreamDestroy(cap);
     return bail(WOS_ERR_DEVICE, "graph capture failed to start");
   }
-  r = enqueue_job(items, n_items, opt, s, P->ws, P->dit, P->n_tiles, P->n_slots, false, nullptr, cap);
+  r = enqueue_job(n_items, opt, s, P->ws, P->dit, P->n_tiles, P->n_slots, false, nullptr, cap);
   const hipError_t ec = hipStreamEndCapture(cap, &P->graph);
   (void)hipStreamDestroy(cap);
   if (r != WOS_OK || ec != hipSuccess) return bail(WOS_ERR_DEVICE, "graph capture failed");
@@ -1876,8 +1880,8 @@ wos_status wos_plan_time(wos_plan* P, uint64_t seed, uint64_t walk_offset_add, v
     if (e != hipSuccess) r = fail(WOS_ERR_DEVICE, "launch failed");
   }
   if (r == WOS_OK)
-    r = enqueue_job(P->items.data(), (int)P->items.size(), &P->opt, P->s, P->ws, P->dit, P->n_tiles, P->n_slots,
-                    false, nullptr, st, &marks);
+    r = enqueue_job((int)P->items.size(), &P->opt, P->s, P->ws, P->dit, P->n_tiles, P->n_slots, false, nullptr, st,
+                    &marks);
   if (r == WOS_OK) {
     hipError_t e = hipEventRecord(t1, st);
     if (e == hipSuccess) e = hipEventSynchronize(t1);
@@ -2003,7 +2007,7 @@ wos_status wos_eval_offcentred(int32_t which, int32_t dim, int32_t precision, do
 wos_status wos_classify(const wos_problem* p, const double* points, int64_t n, int8_t* inside, void* stream) {
   if (!p || n < 0 || (n > 0 && (!points || !inside))) return fail(WOS_ERR_INVALID_ARG, "bad arguments");
   WOS_HIP(hipSetDevice(p->device));
-  WOS_HIP(launch_classify(p->dim, p->geom, p->d64(), points, n, inside, nullptr, (hipStream_t)stream));
+  WOS_HIP(launch_classify(p->dim, p->geom, p->d64(), points, n, inside, (hipStream_t)stream));
   return WOS_OK;
 }
 

@@ -130,45 +130,35 @@ struct SamplePoints {
 
 // Analytic and SDF domains: one point per thread.
 template <int DIM, int GEOM, typename SRC>
-__global__ void classify_analytic_kernel(const DevProblem<double>* P, SRC src, int64_t n, int8_t* inside,
-                                         uint64_t* counters) {
+__global__ void classify_analytic_kernel(const DevProblem<double>* P, SRC src, int64_t n, int8_t* inside) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  bool bad = false;
-  if (i < n) {
-    double x[DIM];
-    src.get(i, x);
-    const bool in = inside_analytic<DIM, GEOM>(gptr(P)->geom, x);
-    inside[i] = in ? 1 : 0;
-    bad = !in;
-  }
-  if (counters) {
-    const uint64_t m = __ballot(bad);
-    if (__lane_id() == 0 && m) atomicAdd((unsigned long long*)&counters[0], (unsigned long long)__popcll(m));
-  }
+  if (i >= n) return;
+  double x[DIM];
+  src.get(i, x);
+  inside[i] = inside_analytic<DIM, GEOM>(gptr(P)->geom, x) ? 1 : 0;
 }
 
-// Polygons and meshes: 64 points per block. The first wave looks up their cells; the points
-// that lie in a cell of the boundary (2-10% of a slice) go through every primitive, a wave
-// each. One point per thread over every primitive, as before, is a serial chain of n_prims
-// terms: 15.7 ms for 131,000 points of a 20,480-triangle mesh, 156 us on average for the
-// polygons of a batch.
+// Polygons and meshes: 64 points per block of 256 threads. The first wave looks up their cells;
+// the points that lie in a cell of the boundary (2-10% of a slice) go through every
+// primitive, a wave each. One point per thread over every primitive, as before, is a serial
+// chain of n_prims terms: 15.7 ms for 131,000 points of a 20,480-triangle mesh, 156 us on
+// average for the polygons of a batch.
 constexpr int kClassifyPoints = 64;
 
+// Classifies the block's points first .. first + 63 (those below n); returns for threads
+// below 64 whether theirs is inside. Called by the whole block.
 template <int DIM, int GEOM, typename SRC>
-__global__ void __launch_bounds__(256) classify_cells_kernel(const DevProblem<double>* P, SRC src, int64_t n,
-                                                             int8_t* inside, uint64_t* counters) {
+__device__ __forceinline__ bool classify_block(G<DevGeometry<double>>& g, const SRC& src, int64_t first, int64_t n) {
   __shared__ double s_x[kClassifyPoints][DIM];
   __shared__ int s_todo[kClassifyPoints];
   __shared__ int s_n;
   __shared__ int s_in[kClassifyPoints];
-  G<DevGeometry<double>>& g = gptr(P)->geom;
   const int t = (int)threadIdx.x, wave = t >> 6;
-  const int64_t i = (int64_t)blockIdx.x * kClassifyPoints + t;
   if (wave == 0) {
     int c = 0;
-    if (i < n) {
+    if (first + t < n) {
       double x[DIM];
-      src.get(i, x);
+      src.get(first + t, x);
       c = cell_class_of<DIM>(g, x);
 #pragma unroll
       for (int k = 0; k < DIM; ++k) s_x[t][k] = x[k];
@@ -188,13 +178,68 @@ __global__ void __launch_bounds__(256) classify_cells_kernel(const DevProblem<do
     if (__lane_id() == 0) s_in[p] = in;
   }
   __syncthreads();
-  if (wave == 0) {
-    const bool in = s_in[t] != 0;
-    if (i < n) inside[i] = in ? 1 : 0;
-    if (counters) {
-      const uint64_t m = __ballot(i < n && !in);
-      if (t == 0 && m) atomicAdd((unsigned long long*)&counters[0], (unsigned long long)__popcll(m));
+  return wave == 0 && s_in[t] != 0;
+}
+
+template <int DIM, int GEOM, typename SRC>
+__global__ void __launch_bounds__(256) classify_cells_kernel(const DevProblem<double>* P, SRC src, int64_t n,
+                                                             int8_t* inside) {
+  const int64_t first = (int64_t)blockIdx.x * kClassifyPoints;
+  const bool in = classify_block<DIM, GEOM>(gptr(P)->geom, src, first, n);
+  if (threadIdx.x < kClassifyPoints && first + threadIdx.x < n) inside[first + threadIdx.x] = in ? 1 : 0;
+}
+
+// ------------------------------------------------------------------ preparing a job
+//
+// One launch per kPrepItems items classifies their points, evaluates gamma(x0) (the same for
+// all walks of a point, so each walk starts from it), and leaves everything else the walker
+// finds in memory: the item table, which comes with the launch's arguments and needs no copy
+// or wait, the launch parameters, cleared slots and tile counters. As five launches, a copy
+// and a wait for it, this was 60 of the 350 us of a solve of 16 points x 128 walks.
+template <typename T, int DIM, int GEOM>
+__global__ void __launch_bounds__(256) prep_kernel(PrepArgs a) {
+  constexpr bool kCells = GEOM == GK_POLYGON || GEOM == GK_TRIMESH;
+  constexpr int kPoints = kCells ? kClassifyPoints : 256;
+  const int t = (int)threadIdx.x;
+  if (blockIdx.x == 0) {
+    constexpr int kWords = (int)(sizeof(DevItem) / sizeof(uint32_t));
+    if (a.table)
+      for (int w = t; w < a.n * kWords; w += 256) ((uint32_t*)a.table)[w] = ((const uint32_t*)a.item)[w];
+    if (a.counters && t < (int)(kTileQueues * kTileQueueStride)) a.counters[t] = 0;
+    if (a.lp && t == 0) {
+      a.lp->seed = a.seed;
+      a.lp->walk_offset_add = 0;
     }
+  }
+  for (uint64_t i = (uint64_t)blockIdx.x * 256 + t; i < a.slot_words; i += (uint64_t)gridDim.x * 256) a.slots[i] = 0;
+  int k = 0;
+  while (k + 1 < a.n && blockIdx.x >= a.block0[k + 1]) ++k;
+  const DevItem& it = a.item[k];
+  const int64_t first = (int64_t)(blockIdx.x - a.block0[k]) * kPoints, i = first + t;
+  const DevProblem<double>* P64 = (const DevProblem<double>*)a.problem64[k];
+  bool in = false;
+  if constexpr (kCells) {
+    in = classify_block<DIM, GEOM>(gptr(P64)->geom, ArrayPoints<DIM>{it.points}, first, it.n_points);
+  } else if (i < it.n_points) {
+    double x[DIM];
+    ArrayPoints<DIM>{it.points}.get(i, x);
+    in = inside_analytic<DIM, GEOM>(gptr(P64)->geom, x);
+  }
+  const bool mine = t < kPoints && i < it.n_points;
+  if (mine) {
+    ((int8_t*)it.inside)[i] = in ? 1 : 0;
+    T g = 0;
+    if (in) {
+      T x[DIM];
+#pragma unroll
+      for (int c = 0; c < DIM; ++c) x[c] = (T)it.points[i * DIM + c];
+      g = point_gamma<T, DIM>(*gptr((const DevProblem<T>*)it.problem), x);
+    }
+    ((T*)it.gamma0)[i] = g;
+  }
+  if (it.counters) {
+    const uint64_t m = __ballot(mine && !in);
+    if (__lane_id() == 0 && m) atomicAdd((unsigned long long*)&it.counters[0], (unsigned long long)__popcll(m));
   }
 }
 
@@ -770,29 +815,51 @@ __global__ void __launch_bounds__(256) scan_write_kernel(const uint32_t* count, 
 static inline unsigned blocks_for(int64_t n, int bs) { return (unsigned)((n + bs - 1) / bs); }
 
 template <int DIM, typename SRC>
-static hipError_t classify_t(int geom, const void* P64, const SRC& src, int64_t n, int8_t* inside, uint64_t* counters,
-                             hipStream_t st) {
+static hipError_t classify_t(int geom, const void* P64, const SRC& src, int64_t n, int8_t* inside, hipStream_t st) {
   const DevProblem<double>* P = (const DevProblem<double>*)P64;
   const dim3 b(256), ga(blocks_for(n, 256)), gc(blocks_for(n, kClassifyPoints));
   if (geom == GK_BALL)
-    hipLaunchKernelGGL((classify_analytic_kernel<DIM, GK_BALL, SRC>), ga, b, 0, st, P, src, n, inside, counters);
+    hipLaunchKernelGGL((classify_analytic_kernel<DIM, GK_BALL, SRC>), ga, b, 0, st, P, src, n, inside);
   else if (geom == GK_BOX)
-    hipLaunchKernelGGL((classify_analytic_kernel<DIM, GK_BOX, SRC>), ga, b, 0, st, P, src, n, inside, counters);
+    hipLaunchKernelGGL((classify_analytic_kernel<DIM, GK_BOX, SRC>), ga, b, 0, st, P, src, n, inside);
   else if (geom == GK_SDF)
-    hipLaunchKernelGGL((classify_analytic_kernel<DIM, GK_SDF, SRC>), ga, b, 0, st, P, src, n, inside, counters);
+    hipLaunchKernelGGL((classify_analytic_kernel<DIM, GK_SDF, SRC>), ga, b, 0, st, P, src, n, inside);
   else if (geom == (DIM == 2 ? GK_POLYGON : GK_TRIMESH))
     hipLaunchKernelGGL((classify_cells_kernel<DIM, DIM == 2 ? GK_POLYGON : GK_TRIMESH, SRC>), gc, b, 0, st, P, src, n,
-                       inside, counters);
+                       inside);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
 hipError_t launch_classify(int dim, int geom, const void* P64, const double* pts, int64_t n, int8_t* inside,
-                           uint64_t* counters, hipStream_t st) {
+                           hipStream_t st) {
   if (n == 0) return hipSuccess;
-  return dim == 2 ? classify_t<2>(geom, P64, ArrayPoints<2>{pts}, n, inside, counters, st)
-                  : classify_t<3>(geom, P64, ArrayPoints<3>{pts}, n, inside, counters, st);
+  return dim == 2 ? classify_t<2>(geom, P64, ArrayPoints<2>{pts}, n, inside, st)
+                  : classify_t<3>(geom, P64, ArrayPoints<3>{pts}, n, inside, st);
+}
+
+template <typename T, int DIM>
+static hipError_t prep_t(int geom, const dim3& g, const PrepArgs& a, hipStream_t st) {
+  const dim3 b(256);
+  if (geom == GK_BALL) hipLaunchKernelGGL((prep_kernel<T, DIM, GK_BALL>), g, b, 0, st, a);
+  else if (geom == GK_BOX) hipLaunchKernelGGL((prep_kernel<T, DIM, GK_BOX>), g, b, 0, st, a);
+  else if (geom == GK_SDF) hipLaunchKernelGGL((prep_kernel<T, DIM, GK_SDF>), g, b, 0, st, a);
+  else if (geom == (DIM == 2 ? GK_POLYGON : GK_TRIMESH))
+    hipLaunchKernelGGL((prep_kernel<T, DIM, DIM == 2 ? GK_POLYGON : GK_TRIMESH>), g, b, 0, st, a);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
+hipError_t launch_prep(int fp64, int dim, int geom, PrepArgs& a, hipStream_t st) {
+  const int points = geom == GK_POLYGON || geom == GK_TRIMESH ? kClassifyPoints : 256;
+  a.block0[0] = 0;
+  for (int k = 0; k < a.n; ++k) a.block0[k + 1] = a.block0[k] + blocks_for(a.item[k].n_points, points);
+  // at least one block writes the tables; slots beyond the points' share get blocks of their own
+  const uint64_t clear = std::min<uint64_t>((a.slot_words + 2047) / 2048, 4096);
+  const dim3 g((unsigned)std::max<uint64_t>(std::max<uint64_t>(a.block0[a.n], clear), 1));
+  if (fp64) return dim == 2 ? prep_t<double, 2>(geom, g, a, st) : prep_t<double, 3>(geom, g, a, st);
+  return dim == 2 ? prep_t<float, 2>(geom, g, a, st) : prep_t<float, 3>(geom, g, a, st);
 }
 
 template <int DIM>
@@ -805,7 +872,7 @@ static hipError_t sigma_t(int geom, const void* P64, const double* lo, const dou
   }
   src.grid = grid;
   src.first = first;
-  const hipError_t e = classify_t<DIM>(geom, P64, src, n, inside, nullptr, st);
+  const hipError_t e = classify_t<DIM>(geom, P64, src, n, inside, st);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((sigma_sample_kernel<DIM>), dim3(nblocks), dim3(256), 0, st, (const DevProblem<double>*)P64, src,
                      n, inside, out);

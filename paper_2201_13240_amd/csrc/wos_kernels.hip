@@ -50,8 +50,17 @@ __device__ __forceinline__ void fx_accumulate(int64_t* L, const uint64_t* words)
 // double once and added into the caller's accumulators. With grad_dim > 0 also the sums
 // of the gradient components (supplemental Sec. 2).
 template <int GD>
-__global__ void reduce_kernel(DevItem it, const uint64_t* __restrict__ slots, int slot_words) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+__global__ void __launch_bounds__(kReducePoints) reduce_kernel(const DevItem* __restrict__ items, int n_items,
+                                                               const uint64_t* __restrict__ slots, int slot_words) {
+  // the block's item: the last one that starts at or before it
+  int lo = 0;
+  for (int hi = n_items; hi - lo > 1;) {
+    const int mid = (lo + hi) / 2;
+    if (gptr(items)[mid].reduce_block <= blockIdx.x) lo = mid;
+    else hi = mid;
+  }
+  G<DevItem>& it = gptr(items)[lo];
+  const int64_t p = (int64_t)(blockIdx.x - it.reduce_block) * blockDim.x + threadIdx.x;
   uint64_t capped = 0, killed = 0;
   if (p < it.n_points) {
     const uint32_t spp = it.tiles_per_point > 0u ? it.tiles_per_point : 1u;
@@ -144,21 +153,6 @@ __global__ void coef_kernel(const DevProblem<T>* P, const double* pts, int64_t n
   o[3] = (double)c.f_over_alpha * (double)c.alpha;
   o[4] = (double)m_exp(c.gamma) * (double)c.f_over_alpha;
   o[5] = boundary_value<T, DIM>(PR, x);
-}
-
-// gamma(x0) of every interior query point: the same for all walks of a point, so each
-// walk starts from it instead of spending an iteration of the walker on it.
-template <typename T, int DIM>
-__global__ void gamma0_kernel(const DevProblem<T>* P, const double* pts, int64_t n, const int8_t* inside, T* out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  T g = 0;
-  if (inside[i]) {
-    T x[DIM];
-    for (int k = 0; k < DIM; ++k) x[k] = (T)pts[i * DIM + k];
-    g = point_gamma<T, DIM>(*gptr(P), x);
-  }
-  out[i] = g;
 }
 
 template <typename T, int DIM, int GEOM>
@@ -305,12 +299,13 @@ const void* walker_symbol(int fp64, int dim, int geom, int mode) {
   return dim == 2 ? walker_symbol_f32_2d(geom, mode) : walker_symbol_f32_3d(geom, mode);
 }
 
-hipError_t launch_reduce(int grad_dim, const DevItem& it, const uint64_t* slots, int slot_words, hipStream_t st) {
-  if (it.n_points == 0) return hipSuccess;
-  const dim3 g(blocks_for(it.n_points, 256)), b(256);
-  if (grad_dim == 2) hipLaunchKernelGGL(reduce_kernel<2>, g, b, 0, st, it, slots, slot_words);
-  else if (grad_dim == 3) hipLaunchKernelGGL(reduce_kernel<3>, g, b, 0, st, it, slots, slot_words);
-  else hipLaunchKernelGGL(reduce_kernel<0>, g, b, 0, st, it, slots, slot_words);
+hipError_t launch_reduce(int grad_dim, const DevItem* items, int n_items, uint64_t n_blocks, const uint64_t* slots,
+                         int slot_words, hipStream_t st) {
+  if (n_blocks == 0) return hipSuccess;
+  const dim3 g((unsigned)n_blocks), b(kReducePoints);
+  if (grad_dim == 2) hipLaunchKernelGGL(reduce_kernel<2>, g, b, 0, st, items, n_items, slots, slot_words);
+  else if (grad_dim == 3) hipLaunchKernelGGL(reduce_kernel<3>, g, b, 0, st, items, n_items, slots, slot_words);
+  else hipLaunchKernelGGL(reduce_kernel<0>, g, b, 0, st, items, n_items, slots, slot_words);
   return hipGetLastError();
 }
 
@@ -322,24 +317,6 @@ hipError_t launch_clear(uint64_t* p, uint64_t n, uint32_t* counters, hipStream_t
 
 hipError_t launch_set_params(LaunchParams* lp, uint64_t seed, uint64_t walk_offset_add, hipStream_t st) {
   hipLaunchKernelGGL(set_params_kernel, dim3(1), dim3(64), 0, st, lp, seed, walk_offset_add);
-  return hipGetLastError();
-}
-
-hipError_t launch_gamma0(int fp64, int dim, const void* P, const double* pts, int64_t n, const int8_t* inside,
-                         void* out, hipStream_t st) {
-  if (n == 0) return hipSuccess;
-  const dim3 g(blocks_for(n, 256)), b(256);
-  if (fp64) {
-    if (dim == 2)
-      hipLaunchKernelGGL((gamma0_kernel<double, 2>), g, b, 0, st, (const DevProblem<double>*)P, pts, n, inside, (double*)out);
-    else
-      hipLaunchKernelGGL((gamma0_kernel<double, 3>), g, b, 0, st, (const DevProblem<double>*)P, pts, n, inside, (double*)out);
-  } else {
-    if (dim == 2)
-      hipLaunchKernelGGL((gamma0_kernel<float, 2>), g, b, 0, st, (const DevProblem<float>*)P, pts, n, inside, (float*)out);
-    else
-      hipLaunchKernelGGL((gamma0_kernel<float, 3>), g, b, 0, st, (const DevProblem<float>*)P, pts, n, inside, (float*)out);
-  }
   return hipGetLastError();
 }
 

@@ -35,6 +35,22 @@ struct WalkerLaunch {
   uint64_t* events;   // non-null selects the event-counting build of the walker
 };
 
+// Items of a job handed to the device with the launch that prepares it: their table entries,
+// the problems in FP64, and the first block that each takes of the launch.
+constexpr int kPrepItems = 16;
+struct PrepArgs {
+  DevItem item[kPrepItems];
+  const void* problem64[kPrepItems];
+  uint32_t block0[kPrepItems + 1];
+  int32_t n;
+  DevItem* table;          // entry of the first item, or null: the table is there already
+  LaunchParams* lp;
+  uint64_t seed;
+  uint32_t* counters;
+  uint64_t* slots;
+  uint64_t slot_words;     // words to clear
+};
+
 hipError_t launch_walker(const WalkerLaunch& L, hipStream_t st);
 // The walkers of one precision and dimension (wos_walker_{f32,f64}_{2d,3d}.hip).
 hipError_t launch_walker_f32_2d(const WalkerLaunch& L, hipStream_t st);
@@ -53,15 +69,18 @@ hipError_t static_scratch(int device, void** ptr);
 // 0 delta tracking, 1 delta tracking with splitting or gradient records, 2 next flight
 int walker_mode(int variant, bool grad, bool split);
 const void* walker_symbol(int fp64, int dim, int geom, int mode);
-// Per-point sums of one item from its slots, added into the item's outputs.
-hipError_t launch_reduce(int grad_dim, const DevItem& it, const uint64_t* slots, int slot_words, hipStream_t st);
+// Per-point sums of every item from its slots, added into the item's outputs (n_blocks: blocks
+// of kReducePoints points, each item its own).
+constexpr int kReducePoints = 256;
+hipError_t launch_reduce(int grad_dim, const DevItem* items, int n_items, uint64_t n_blocks, const uint64_t* slots,
+                         int slot_words, hipStream_t st);
 // Zeroes n words at p and the tile counters (a kernel, so that it can sit in a captured graph).
 hipError_t launch_clear(uint64_t* p, uint64_t n, uint32_t* counters, hipStream_t st);
 hipError_t launch_finalize_components(const double* sum, const double* sum_sq, const uint64_t* nw, int64_t n, int dim,
                                       double* mean, double* se, hipStream_t st);
 hipError_t launch_set_params(LaunchParams* lp, uint64_t seed, uint64_t walk_offset_add, hipStream_t st);
 hipError_t launch_classify(int dim, int geom, const void* P64, const double* pts, int64_t n, int8_t* inside,
-                           uint64_t* counters, hipStream_t st);
+                           hipStream_t st);
 // Samples sigma' over the interior ones of cell centres first .. first + n - 1 of a grid
 // (`inside`: n bytes of scratch).
 hipError_t launch_sigma_sample(int dim, int geom, const void* P64, const double* lo, const double* h, int grid,
@@ -83,8 +102,10 @@ hipError_t launch_cell_classes(int dim, const void* P64, const GridShape& s, dou
                                uint32_t* label, uint32_t* roots, uint32_t* n_roots, uint8_t* cls, hipStream_t st);
 // Row lists of the cells of an SDF domain (scale: largest coordinate of its box).
 hipError_t launch_sdf_cells(int dim, const void* P64, const GridShape& s, double scale, uint64_t* cells, hipStream_t st);
-hipError_t launch_gamma0(int fp64, int dim, const void* P, const double* pts, int64_t n, const int8_t* inside,
-                         void* out, hipStream_t st);
+// Prepares a job: classifies the query points (counters[0] of their item counts those outside),
+// evaluates gamma at the interior ones in the walker's precision, writes the item table and the
+// launch parameters, and clears the accumulation slots and tile counters. Sets block0.
+hipError_t launch_prep(int fp64, int dim, int geom, PrepArgs& a, hipStream_t st);
 hipError_t launch_coefficients(int fp64, int dim, const void* P, const double* pts, int64_t n, double* out,
                                hipStream_t st);
 hipError_t launch_distance(int fp64, int dim, int geom, const void* P, const double* pts, int64_t n, double* d,

@@ -204,7 +204,7 @@ struct DevItem {
   int64_t n_points;
   uint64_t walks;            // walks per point in this launch
   uint64_t walk_offset;      // first global walk index of this launch
-  uint64_t point_base;       // offset of this item in the launch's point space
+  uint64_t reduce_block;     // first block of this item in the reduction
   uint32_t problem_index;
   uint32_t tile_len;         // walks per tile when tiles_per_point > 0
   double* grad_sum;          // [n_points][dim] or null
