@@ -637,44 +637,49 @@ hipError_t build_sdf_cells(wos_problem* p, const wos_geometry_desc& d, DevProble
   return hipSuccess;
 }
 
-// Builds the candidate grid of a polygon or mesh on the device (its BVH is there already):
-// list lengths, their prefix sum, one allocation of the exact size, the lists. Sets the
-// grid pointers of both headers on the host.
+// Builds the candidate grid of a polygon or mesh on the device (its BVH is there already). A
+// polygon's list lengths and their prefix sum give the size of its one allocation; a mesh's
+// cells have one size. Sets the grid pointers of both headers on the host.
 hipError_t build_grid(wos_problem* p, const HostGeometry& g, DevProblem<float>& h32, DevProblem<double>& h64) {
   const int64_t nc = g.grid.cells();
+  const bool seg = p->dim == 2;
   size_t off = 0;
   auto take = [&off](size_t bytes) {
     const size_t o = off;
     off = (off + bytes + 255) / 256 * 256;
     return o;
   };
-  const size_t o_best = take(nc * sizeof(double)), o_near = take(nc * 4), o_count = take(nc * 4), o_start = take(nc * 4),
-               o_sums = take(scan_sum_words(nc) * 4), o_total = take(8);
+  const size_t o_best = take(nc * sizeof(double)), o_count = take(nc * 4), o_start = take(nc * 4),
+               o_sums = take(seg ? scan_sum_words(nc) * 4 : 0), o_total = take(8);
   DeviceScratch scratch;
   hipError_t e = hipMalloc(&scratch.p, off);
   if (e != hipSuccess) return e;
   unsigned char* b = (unsigned char*)scratch.p;
   double* best = (double*)(b + o_best);
-  int32_t* near = (int32_t*)(b + o_near);
   uint32_t *count = (uint32_t*)(b + o_count), *start = (uint32_t*)(b + o_start), *total = (uint32_t*)(b + o_total);
-  e = launch_grid_count(p->dim, p->depth, p->d64(), g.grid, g.rule, best, near, count, (uint32_t*)(b + o_sums), start,
-                        total, 0);
   uint32_t n = 0;
-  if (e == hipSuccess) e = hipMemcpy(&n, total, sizeof(n), hipMemcpyDeviceToHost);
-  if (e != hipSuccess) return e;
-  p->grid_candidates = n;
-  const bool seg = p->dim == 2;
-  const size_t r32 = seg ? sizeof(CellRec<float>) : sizeof(MeshCell<float>);
-  const size_t r64 = seg ? sizeof(CellRec<double>) : sizeof(MeshCell<double>);
+  if (seg) {
+    e = launch_segment_count(p->depth, p->d64(), g.grid, g.rule, best, count, (uint32_t*)(b + o_sums), start, total, 0);
+    if (e == hipSuccess) e = hipMemcpy(&n, total, sizeof(n), hipMemcpyDeviceToHost);
+    if (e != hipSuccess) return e;
+  }
   off = 0;
-  const size_t o_c32 = take(nc * r32), o_c64 = take(nc * r64), o_prim = take((size_t)n * 4),
-               o_s32 = take(seg ? (size_t)n * 16 : 0), o_s64 = take(seg ? (size_t)n * 32 : 0), o_d32 = take((size_t)n * 4),
+  const size_t o_c32 = take(nc * (seg ? sizeof(CellRec<float>) : sizeof(MeshCell<float>))),
+               o_c64 = take(nc * (seg ? sizeof(CellRec<double>) : sizeof(MeshCell<double>))), o_prim = take((size_t)n * 4),
+               o_s32 = take((size_t)n * 16), o_s64 = take((size_t)n * 32), o_d32 = take((size_t)n * 4),
                o_d64 = take((size_t)n * 8), o_cls = take(nc);
   if ((e = hipMalloc(&p->grid_mem, off)) != hipSuccess) return e;
   b = (unsigned char*)p->grid_mem;
   const GridOut o{b + o_c32,           b + o_c64,           (int32_t*)(b + o_prim),
                   (float*)(b + o_s32), (float*)(b + o_d32), (double*)(b + o_s64), (double*)(b + o_d64)};
-  if ((e = launch_grid_fill(p->dim, p->depth, p->d64(), g.grid, g.rule, best, near, start, o, 0)) != hipSuccess) return e;
+  if (seg) {
+    e = launch_segment_fill(p->depth, p->d64(), g.grid, g.rule, best, start, o, 0);
+  } else {
+    e = launch_mesh_cells(p->depth, p->d64(), g.grid, g.rule, best, o, total, 0);
+    if (e == hipSuccess) e = hipMemcpy(&n, total, sizeof(n), hipMemcpyDeviceToHost);
+  }
+  if (e != hipSuccess) return e;
+  p->grid_candidates = n;
   uint8_t* cls = nullptr;
   if (g.closed) {
     // the counts and starts are done with: their memory takes the labels and roots
@@ -684,9 +689,9 @@ hipError_t build_grid(wos_problem* p, const HostGeometry& g, DevProblem<float>& 
   }
   auto point = [&](auto& h, const void* cells, auto* segs, auto* dc) {
     h.geom.cells = cells;
-    h.geom.cell_prim = o.prim;
+    h.geom.cell_prim = seg ? o.prim : nullptr;
     h.geom.cell_segs = seg ? segs : nullptr;
-    h.geom.cell_dc = dc;
+    h.geom.cell_dc = seg ? dc : nullptr;
     h.geom.cell_class = cls;
   };
   point(h32, o.cells32, o.segs32, o.dc32);

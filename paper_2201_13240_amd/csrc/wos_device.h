@@ -1376,53 +1376,61 @@ __device__ __forceinline__ T segment_dist2_pre(const T* x, PT s, T inv_len2) {
   return m_fma(dx, dx, dy * dy);
 }
 
+// x . y, its products added in the order 1, 0, 2 (one rounding each after the first).
+template <typename T>
+__device__ __forceinline__ T dot3(const T* x, const T* y) {
+  return m_fma(x[2], y[2], m_fma(x[0], y[0], x[1] * y[1]));
+}
+
 // Closest point of triangle (a, b, c) = (tri[0..2], tri[3..5], tri[6..8]) to p, by the
 // Voronoi regions of its vertices, edges and face (Ericson, Real-Time Collision
-// Detection, Sec. 5.1.5).
+// Detection, Sec. 5.1.5). Every region's point is a + s1 ab, rounded, plus s2 times ac (or
+// ac - ab on the edge bc), so the regions select numbers instead of branching: lanes of a
+// wave are spread over all of them, and as seven nested branches a triangle took twice as
+// long.
 template <typename T, typename PT>
 __device__ __forceinline__ void triangle_closest(const T* p, PT tri, T* q) {
-  const T a[3] = {tri[0], tri[1], tri[2]};
-  T ab[3], ac[3];
+  T a[3], ab[3], ac[3], ap[3], bp[3], cp[3];
+#pragma unroll
   for (int i = 0; i < 3; ++i) {
+    a[i] = tri[i];
     ab[i] = tri[3 + i] - a[i];
     ac[i] = tri[6 + i] - a[i];
+    ap[i] = p[i] - a[i];
+    bp[i] = ap[i] - ab[i];
+    cp[i] = ap[i] - ac[i];
   }
-  T ap[3];
-  for (int i = 0; i < 3; ++i) ap[i] = p[i] - a[i];
-  const T d1 = ab[0] * ap[0] + ab[1] * ap[1] + ab[2] * ap[2];
-  const T d2 = ac[0] * ap[0] + ac[1] * ap[1] + ac[2] * ap[2];
-  if (d1 <= (T)0 && d2 <= (T)0) { for (int i = 0; i < 3; ++i) q[i] = a[i]; return; }
-  T bp[3];
-  for (int i = 0; i < 3; ++i) bp[i] = ap[i] - ab[i];
-  const T d3 = ab[0] * bp[0] + ab[1] * bp[1] + ab[2] * bp[2];
-  const T d4 = ac[0] * bp[0] + ac[1] * bp[1] + ac[2] * bp[2];
-  if (d3 >= (T)0 && d4 <= d3) { for (int i = 0; i < 3; ++i) q[i] = a[i] + ab[i]; return; }
-  const T vc = d1 * d4 - d3 * d2;
-  if (vc <= (T)0 && d1 >= (T)0 && d3 <= (T)0) {
-    const T v = m_div(d1, d1 - d3);
-    for (int i = 0; i < 3; ++i) q[i] = a[i] + v * ab[i];
-    return;
-  }
-  T cp[3];
-  for (int i = 0; i < 3; ++i) cp[i] = ap[i] - ac[i];
-  const T d5 = ab[0] * cp[0] + ab[1] * cp[1] + ab[2] * cp[2];
-  const T d6 = ac[0] * cp[0] + ac[1] * cp[1] + ac[2] * cp[2];
-  if (d6 >= (T)0 && d5 <= d6) { for (int i = 0; i < 3; ++i) q[i] = a[i] + ac[i]; return; }
-  const T vb = d5 * d2 - d1 * d6;
-  if (vb <= (T)0 && d2 >= (T)0 && d6 <= (T)0) {
-    const T w = m_div(d2, d2 - d6);
-    for (int i = 0; i < 3; ++i) q[i] = a[i] + w * ac[i];
-    return;
-  }
-  const T va = d3 * d6 - d5 * d4;
-  if (va <= (T)0 && (d4 - d3) >= (T)0 && (d5 - d6) >= (T)0) {
-    const T w = m_div(d4 - d3, (d4 - d3) + (d5 - d6));
-    for (int i = 0; i < 3; ++i) q[i] = a[i] + ab[i] + w * (ac[i] - ab[i]);
-    return;
-  }
-  const T denom = m_rcp(va + vb + vc);
-  const T v = vb * denom, w = vc * denom;
-  for (int i = 0; i < 3; ++i) q[i] = a[i] + ab[i] * v + ac[i] * w;
+  const T d1 = dot3(ab, ap), d2 = dot3(ac, ap), d3 = dot3(ab, bp), d4 = dot3(ac, bp), d5 = dot3(ab, cp),
+          d6 = dot3(ac, cp);
+  const T vc = m_fma(d1, d4, -(d3 * d2)), vb = m_fma(d5, d2, -(d1 * d6)), va = m_fma(d3, d6, -(d5 * d4));
+  const T t1 = d4 - d3, t2 = d5 - d6;
+  // face, then the other regions from the last tested to the first: num / den is 1 / (va + vb +
+  // vc) on the face and the edge's parameter on an edge
+  T num = 1, den = va + vb + vc;
+  const bool bc = va <= (T)0 && t1 >= (T)0 && t2 >= (T)0;
+  num = bc ? t1 : num;
+  den = bc ? t1 + t2 : den;
+  const bool on_ac = vb <= (T)0 && d2 >= (T)0 && d6 <= (T)0;
+  num = on_ac ? d2 : num;
+  den = on_ac ? d2 - d6 : den;
+  const bool on_ab = vc <= (T)0 && d1 >= (T)0 && d3 <= (T)0;
+  num = on_ab ? d1 : num;
+  den = on_ab ? d1 - d3 : den;
+  const T r = m_div(num, den);
+  const bool at_a = d1 <= (T)0 && d2 <= (T)0, at_b = d3 >= (T)0 && d4 <= d3, at_c = d6 >= (T)0 && d5 <= d6;
+  T s1 = bc ? (T)1 : vb * r, s2 = bc ? r : vc * r;
+  s1 = on_ac ? (T)0 : s1;
+  s2 = on_ac ? r : s2;
+  s1 = at_c ? (T)0 : s1;
+  s2 = at_c ? (T)1 : s2;
+  s1 = on_ab ? r : s1;
+  s2 = on_ab ? (T)0 : s2;
+  s1 = at_b ? (T)1 : s1;
+  s2 = at_b ? (T)0 : s2;
+  s1 = at_a ? (T)0 : s1;
+  s2 = at_a ? (T)0 : s2;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) q[i] = m_fma(s2, bc ? ac[i] - ab[i] : ac[i], m_fma(s1, ab[i], a[i]));
 }
 
 template <typename T, typename PT>
@@ -1842,11 +1850,11 @@ __device__ __forceinline__ T boundary_distance(G<DevGeometry<T>>& g, const T* x,
           const int ix = (int)f[0], iy = (int)f[1], iz = (int)f[2];
           const WOS_GLOBAL MeshCell<T>* rec =
               (const WOS_GLOBAL MeshCell<T>*)g.cells + ((iz * g.grid_ny + iy) * g.grid_nx + ix);
-          const uint32_t n = rec->count, st = rec->start;
+          const uint32_t n = rec->count;
           const T tail = rec->tail;
           if (n > 0) {
-            const WOS_GLOBAL int32_t* cp = gptr(g.cell_prim) + st;
-            const WOS_GLOBAL T* dc = gptr(g.cell_dc) + st;
+            const WOS_GLOBAL int32_t* cp = rec->id;
+            const WOS_GLOBAL T* dc = rec->dc;
             const WOS_GLOBAL T* prims = gptr(g.prims);
             const T ox = x[0] - m_fma((T)ix + (T)0.5, g.grid_h, g.grid_lo[0]);
             const T oy = x[1] - m_fma((T)iy + (T)0.5, g.grid_h, g.grid_lo[1]);
@@ -1855,10 +1863,16 @@ __device__ __forceinline__ T boundary_distance(G<DevGeometry<T>>& g, const T* x,
             T best = Consts<T>::kInf;
             int bp = 0;
             uint32_t k = 0;
+            // the next entry is loaded (clamped to the list) while a triangle is tested
+            int pn = cp[0];
+            T cn = dc[0];
             for (; k < n; ++k) {
-              const T lim = dc[k] - r_pc;
+              const T lim = cn - r_pc;
               if (lim > (T)0 && lim * lim >= best) break;
-              const int pi = cp[k];
+              const int pi = pn;
+              const uint32_t kn = min(k + 1u, n - 1u);
+              pn = cp[kn];
+              cn = dc[kn];
               const T d2 = triangle_dist2<T>(x, prims + (size_t)pi * kPrimStride3);
               if (d2 < best) {
                 best = d2;

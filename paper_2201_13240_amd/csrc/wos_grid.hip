@@ -541,108 +541,113 @@ __device__ __forceinline__ int64_t block_cell(const GridShape& s, double* p) {
   return i < s.nx && j < s.ny && k < s.nz ? ((int64_t)k * s.ny + j) * s.nx + i : -1;
 }
 
-// Squared distance of each cell's centre (best), the nearest primitive and the length of its
-// list.
-template <int DIM, bool DEEP>
-__global__ void __launch_bounds__(64) grid_count_kernel(const DevProblem<double>* P, GridShape s, GridRule rule,
-                                                        double* best_out, int32_t* near_out, uint32_t* count) {
-  __shared__ int32_t s_node[DEEP ? 1 : kBuildStack * 64];
-  __shared__ double s_dist[DEEP ? 1 : kBuildStack * 64];
-  double p[3];
-  const int64_t c = block_cell<DIM>(s, p);
-  if (c < 0) return;
-  int32_t* sn = s_node + (DEEP ? 0 : threadIdx.x);
-  double* sd = s_dist + (DEEP ? 0 : threadIdx.x);
-  G<DevGeometry<double>>& g = gptr(P)->geom;
+// The traversal stacks of a block and the list being collected, a column per lane.
+template <bool DEEP, int KEEP>
+struct BuildScratch {
+  int32_t node[DEEP ? 1 : kBuildStack * 64];
+  double dist[DEEP ? 1 : kBuildStack * 64];
+  double d2[KEEP ? KEEP * 64 : 1];
+  int32_t id[KEEP ? KEEP * 64 : 1];
+};
+
+// Squared distance of p and the nearest primitive.
+template <int DIM, bool DEEP, typename S>
+__device__ __forceinline__ double build_nearest(G<DevGeometry<double>>& g, const double* p, S& sc, int32_t* nearest) {
+  const int t = DEEP ? 0 : (int)threadIdx.x;
   double best = 1e300;
-  int32_t nearest = 0;
-  build_traverse<DIM, DEEP>(g, p, best, sn, sd, [&](int32_t i, double d2) {
+  *nearest = 0;
+  build_traverse<DIM, DEEP>(g, p, best, sc.node + t, sc.dist + t, [&](int32_t i, double d2) {
     if (d2 < best) {
       best = d2;
-      nearest = i;
+      *nearest = i;
     }
   });
-  best_out[c] = best;
-  near_out[c] = nearest;
-  const double d = sqrt(best);
-  if (DIM == 3 && d >= rule.deep) {
-    count[c] = 1;
-    return;
-  }
-  const double r = d + 2 * rule.halfdiag + rule.margin, r2 = r * r;
-  const uint32_t most = (uint32_t)(DIM == 2 ? rule.max_list + 1 : rule.max_list);
-  uint32_t n = 0;
-  double bound = r2;
-  build_traverse<DIM, DEEP>(g, p, bound, sn, sd, [&](int32_t, double d2) {
-    if (d2 <= r2 && ++n >= most) bound = -1.0;   // enough is known
-  });
-  count[c] = DIM == 2 && n >= most ? (uint32_t)rule.deep_list : min(n, most);
+  return best;
 }
 
-// Writes every cell's list: primitives in leaf order of (distance, index), the distances in
-// both precisions less the rounding margin, and the records the walkers read.
-template <int DIM, bool DEEP>
-__global__ void __launch_bounds__(64) grid_fill_kernel(const DevProblem<double>* P, GridShape s, GridRule rule,
-                                                       const double* best_in, const int32_t* near_in,
-                                                       const uint32_t* start, GridOut o) {
-  // the nearest candidates found so far, in order; a polygon list over the limit keeps its
-  // deep_list nearest and the next one's distance
-  constexpr int kKeep = DIM == 2 ? kPolygonCellMax + 1 : kMeshCellList + 1;
-  __shared__ int32_t s_node[DEEP ? 1 : kBuildStack * 64];
-  __shared__ double s_dist[DEEP ? 1 : kBuildStack * 64];
-  __shared__ double s_d2[kKeep * 64];
-  __shared__ int32_t s_id[kKeep * 64];
+// Collects the primitives within r2 of p in the lane's column, in order of (distance, index):
+// the max_list + 1 nearest, or, for a polygon with more, the deep_list + 1 nearest. Returns
+// how many belong to the cell's list; *tail receives the distance of the next one, +inf where
+// the list is complete.
+template <int DIM, bool DEEP, typename S>
+__device__ __forceinline__ int build_list(G<DevGeometry<double>>& g, const double* p, double r2, const GridRule& rule,
+                                          S& sc, double* tail) {
+  const int t = DEEP ? 0 : (int)threadIdx.x;
+  double* ld = sc.d2 + threadIdx.x;
+  int32_t* li = sc.id + threadIdx.x;
+  double bound = r2;
+  int n = 0, cap = rule.max_list + 1;
+  bool over = false;
+  build_traverse<DIM, DEEP>(g, p, bound, sc.node + t, sc.dist + t, [&](int32_t i, double d2) {
+    if (!(d2 <= bound)) return;
+    if (n == cap) {
+      const double ed = ld[(n - 1) * 64];
+      if (d2 > ed || (d2 == ed && i > li[(n - 1) * 64])) return;
+      --n;
+    }
+    int k = n++;
+    for (; k > 0; --k) {
+      const double ed = ld[(k - 1) * 64];
+      const int32_t ei = li[(k - 1) * 64];
+      if (ed < d2 || (ed == d2 && ei < i)) break;
+      ld[k * 64] = ed;
+      li[k * 64] = ei;
+    }
+    ld[k * 64] = d2;
+    li[k * 64] = i;
+    if (n == cap) {
+      if (DIM == 2 && !over) {
+        over = true;
+        cap = n = rule.deep_list + 1;
+      }
+      bound = ld[(n - 1) * 64];
+    }
+  });
+  const int keep = DIM == 2 && over ? rule.deep_list : min(n, rule.max_list);
+  *tail = n > keep ? sqrt(ld[keep * 64]) : __builtin_huge_val();
+  return keep;
+}
+
+// Polygons: squared distance of each cell's centre and the length of its list.
+template <bool DEEP>
+__global__ void __launch_bounds__(64) segment_count_kernel(const DevProblem<double>* P, GridShape s, GridRule rule,
+                                                           double* best_out, uint32_t* count) {
+  __shared__ BuildScratch<DEEP, 0> sc;
   double p[3];
-  const int64_t c = block_cell<DIM>(s, p);
+  const int64_t c = block_cell<2>(s, p);
   if (c < 0) return;
-  int32_t* sn = s_node + (DEEP ? 0 : threadIdx.x);
-  double* sd = s_dist + (DEEP ? 0 : threadIdx.x);
-  double* ld = s_d2 + threadIdx.x;
-  int32_t* li = s_id + threadIdx.x;
   G<DevGeometry<double>>& g = gptr(P)->geom;
-  const double best = best_in[c], d = sqrt(best);
+  int32_t nearest;
+  const double best = build_nearest<2, DEEP>(g, p, sc, &nearest);
+  best_out[c] = best;
+  const double r = sqrt(best) + 2 * rule.halfdiag + rule.margin, r2 = r * r;
+  const uint32_t most = (uint32_t)rule.max_list + 1u;
+  uint32_t n = 0;
+  double bound = r2;
+  const int t = DEEP ? 0 : (int)threadIdx.x;
+  build_traverse<2, DEEP>(g, p, bound, sc.node + t, sc.dist + t, [&](int32_t, double d2) {
+    if (d2 <= r2 && ++n >= most) bound = -1.0;   // enough is known
+  });
+  count[c] = n >= most ? (uint32_t)rule.deep_list : n;
+}
+
+// Polygons: every cell's list from its start, and its record in both precisions; distances
+// are less the rounding margin.
+template <bool DEEP>
+__global__ void __launch_bounds__(64) segment_fill_kernel(const DevProblem<double>* P, GridShape s, GridRule rule,
+                                                          const double* best_in, const uint32_t* start, GridOut o) {
+  __shared__ BuildScratch<DEEP, kPolygonCellMax + 1> sc;
+  double p[3];
+  const int64_t c = block_cell<2>(s, p);
+  if (c < 0) return;
+  G<DevGeometry<double>>& g = gptr(P)->geom;
+  const double r = sqrt(best_in[c]) + 2 * rule.halfdiag + rule.margin;
+  double tail;
+  const int keep = build_list<2, DEEP>(g, p, r * r, rule, sc, &tail);
+  if (tail < __builtin_huge_val()) tail -= rule.margin;
+  const double* ld = sc.d2 + threadIdx.x;
+  const int32_t* li = sc.id + threadIdx.x;
   const uint32_t st = start[c];
-  int n = 0, keep = 0;
-  double tail = __builtin_huge_val();
-  if (DIM == 3 && d >= rule.deep) {
-    ld[0] = best;
-    li[0] = near_in[c];
-    keep = 1;
-    tail = d;
-  } else {
-    const double r = d + 2 * rule.halfdiag + rule.margin, r2 = r * r;
-    double bound = r2;
-    int cap = rule.max_list + 1;
-    bool over = false;
-    build_traverse<DIM, DEEP>(g, p, bound, sn, sd, [&](int32_t i, double d2) {
-      if (!(d2 <= bound)) return;
-      if (n == cap) {
-        const double ed = ld[(n - 1) * 64];
-        if (d2 > ed || (d2 == ed && i > li[(n - 1) * 64])) return;
-        --n;
-      }
-      int k = n++;
-      for (; k > 0; --k) {
-        const double ed = ld[(k - 1) * 64];
-        const int32_t ei = li[(k - 1) * 64];
-        if (ed < d2 || (ed == d2 && ei < i)) break;
-        ld[k * 64] = ed;
-        li[k * 64] = ei;
-      }
-      ld[k * 64] = d2;
-      li[k * 64] = i;
-      if (n == cap) {
-        if (DIM == 2 && !over) {
-          over = true;
-          cap = n = rule.deep_list + 1;
-        }
-        bound = ld[(n - 1) * 64];
-      }
-    });
-    keep = DIM == 2 ? (over ? rule.deep_list : n) : min(n, rule.max_list);
-    if (n > keep) tail = sqrt(ld[keep * 64]);
-  }
-  const double t = tail < __builtin_huge_val() ? tail - rule.margin : tail;
   const WOS_GLOBAL double* prims = gptr(g.prims);
   for (int k = 0; k < keep; ++k) {
     const int32_t id = li[k * 64];
@@ -650,48 +655,83 @@ __global__ void __launch_bounds__(64) grid_fill_kernel(const DevProblem<double>*
     o.prim[st + k] = id;
     o.dc32[st + k] = (float)dc;
     o.dc64[st + k] = dc;
-    if (DIM == 2) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const double v = prims[(size_t)id * kPrimStride2 + e];
-        o.segs32[(size_t)(st + k) * 4 + e] = (float)v;
-        o.segs64[(size_t)(st + k) * 4 + e] = v;
-      }
+    for (int e = 0; e < 4; ++e) {
+      const double v = prims[(size_t)id * kPrimStride2 + e];
+      o.segs32[(size_t)(st + k) * 4 + e] = (float)v;
+      o.segs64[(size_t)(st + k) * 4 + e] = v;
     }
   }
   auto record = [&](auto* rec) {
-    using R = typename std::remove_reference<decltype(*rec)>::type;
     using T = typename std::remove_reference<decltype(rec->tail)>::type;
     rec->count = (uint32_t)keep;
     rec->start = st;
-    rec->tail = (T)t;
-    if constexpr (std::is_same<R, CellRec<T>>::value) {
-      // inline entries beyond the list repeat its last candidate: their distance equals
-      // that candidate's, so they never replace it as the nearest (strict comparison)
-      for (int k = 0; k < kCellInline; ++k) {
-        T sg[4] = {0, 0, 0, 0}, inv = 0;
-        if (keep > 0) {
-          const WOS_GLOBAL double* q = prims + (size_t)li[min(k, keep - 1) * 64] * kPrimStride2;
-          sg[0] = (T)q[0];
-          sg[1] = (T)q[1];
-          sg[2] = (T)(q[2] - q[0]);
-          sg[3] = (T)(q[3] - q[1]);
-          const double ex = (double)sg[2], ey = (double)sg[3], l2 = ex * ex + ey * ey;
-          inv = l2 > 0 ? (T)(1.0 / l2) : (T)0;
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) rec->seg[k][e] = sg[e];
-        rec->inv_len2[k] = inv;
+    rec->tail = (T)tail;
+    // inline entries beyond the list repeat its last candidate: their distance equals
+    // that candidate's, so they never replace it as the nearest (strict comparison)
+    for (int k = 0; k < kCellInline; ++k) {
+      T sg[4] = {0, 0, 0, 0}, inv = 0;
+      if (keep > 0) {
+        const WOS_GLOBAL double* q = prims + (size_t)li[min(k, keep - 1) * 64] * kPrimStride2;
+        sg[0] = (T)q[0];
+        sg[1] = (T)q[1];
+        sg[2] = (T)(q[2] - q[0]);
+        sg[3] = (T)(q[3] - q[1]);
+        const double ex = (double)sg[2], ey = (double)sg[3], l2 = ex * ex + ey * ey;
+        inv = l2 > 0 ? (T)(1.0 / l2) : (T)0;
       }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) rec->seg[k][e] = sg[e];
+      rec->inv_len2[k] = inv;
     }
   };
-  if (DIM == 2) {
-    record((CellRec<float>*)o.cells32 + c);
-    record((CellRec<double>*)o.cells64 + c);
-  } else {
+  record((CellRec<float>*)o.cells32 + c);
+  record((CellRec<double>*)o.cells64 + c);
+}
+
+// Meshes: squared distance of each cell's centre, its record in both precisions, and the sum
+// of the list lengths. The search deep inside, where many triangles are nearly equidistant,
+// is most of the time; a list there would not decide anything, so the cell keeps the nearest
+// triangle alone, with its distance as the tail (no triangle is nearer to the centre).
+template <bool DEEP>
+__global__ void __launch_bounds__(64) mesh_cells_kernel(const DevProblem<double>* P, GridShape s, GridRule rule,
+                                                        double* best_out, GridOut o, uint32_t* total) {
+  __shared__ BuildScratch<DEEP, kMeshCellList + 1> sc;
+  double p[3];
+  const int64_t c = block_cell<3>(s, p);
+  int keep = 0;
+  if (c >= 0) {
+    G<DevGeometry<double>>& g = gptr(P)->geom;
+    double* ld = sc.d2 + threadIdx.x;
+    int32_t* li = sc.id + threadIdx.x;
+    int32_t nearest;
+    const double best = build_nearest<3, DEEP>(g, p, sc, &nearest), d = sqrt(best);
+    best_out[c] = best;
+    double tail = d;
+    keep = 1;
+    if (d >= rule.deep) {
+      ld[0] = best;
+      li[0] = nearest;
+    } else {
+      const double r = d + 2 * rule.halfdiag + rule.margin;
+      keep = build_list<3, DEEP>(g, p, r * r, rule, sc, &tail);
+    }
+    if (tail < __builtin_huge_val()) tail -= rule.margin;
+    auto record = [&](auto* rec) {
+      using T = typename std::remove_reference<decltype(rec->tail)>::type;
+      rec->count = (uint32_t)keep;
+      rec->tail = (T)tail;
+      for (int k = 0; k < kMeshCellList; ++k) {   // short lists repeat their last entry
+        const int e = min(k, keep - 1) * 64;
+        rec->id[k] = li[e];
+        rec->dc[k] = (T)(sqrt(ld[e]) - rule.margin);
+      }
+    };
     record((MeshCell<float>*)o.cells32 + c);
     record((MeshCell<double>*)o.cells64 + c);
   }
+  for (int off = 32; off > 0; off >>= 1) keep += __shfl_xor(keep, off);
+  if (threadIdx.x == 0) atomicAdd(total, (uint32_t)keep);
 }
 
 // ------------------------------------------------------------------ SDF cells
@@ -885,20 +925,13 @@ hipError_t launch_sigma_sample(int dim, int geom, const void* P64, const double*
                   : sigma_t<3>(geom, P64, lo, h, grid, first, n, nblocks, inside, out, st);
 }
 
-hipError_t launch_grid_count(int dim, int depth, const void* P64, const GridShape& s, const GridRule& rule, double* best,
-                             int32_t* near, uint32_t* count, uint32_t* sums, uint32_t* start, uint32_t* total,
-                             hipStream_t st) {
+hipError_t launch_segment_count(int depth, const void* P64, const GridShape& s, const GridRule& rule, double* best,
+                                uint32_t* count, uint32_t* sums, uint32_t* start, uint32_t* total, hipStream_t st) {
   const int64_t n = s.cells();
   const DevProblem<double>* P = (const DevProblem<double>*)P64;
-  const dim3 g((unsigned)(dim == 2 ? CellBlocks<2>::blocks(s) : CellBlocks<3>::blocks(s))), b(64);
-  const bool deep = depth > kBuildStack;
-  if (dim == 2) {
-    if (deep) hipLaunchKernelGGL((grid_count_kernel<2, true>), g, b, 0, st, P, s, rule, best, near, count);
-    else hipLaunchKernelGGL((grid_count_kernel<2, false>), g, b, 0, st, P, s, rule, best, near, count);
-  } else {
-    if (deep) hipLaunchKernelGGL((grid_count_kernel<3, true>), g, b, 0, st, P, s, rule, best, near, count);
-    else hipLaunchKernelGGL((grid_count_kernel<3, false>), g, b, 0, st, P, s, rule, best, near, count);
-  }
+  const dim3 g((unsigned)CellBlocks<2>::blocks(s)), b(64);
+  if (depth > kBuildStack) hipLaunchKernelGGL((segment_count_kernel<true>), g, b, 0, st, P, s, rule, best, count);
+  else hipLaunchKernelGGL((segment_count_kernel<false>), g, b, 0, st, P, s, rule, best, count);
   const unsigned nb = blocks_for(n, 256 * kScanItems);
   hipLaunchKernelGGL(scan_sums_kernel, dim3(nb), dim3(256), 0, st, count, n, sums);
   hipLaunchKernelGGL(scan_blocks_kernel, dim3(1), dim3(256), 0, st, sums, (int)nb, total);
@@ -906,19 +939,22 @@ hipError_t launch_grid_count(int dim, int depth, const void* P64, const GridShap
   return hipGetLastError();
 }
 
-hipError_t launch_grid_fill(int dim, int depth, const void* P64, const GridShape& s, const GridRule& rule,
-                            const double* best, const int32_t* near, const uint32_t* start, const GridOut& out,
-                            hipStream_t st) {
+hipError_t launch_segment_fill(int depth, const void* P64, const GridShape& s, const GridRule& rule, const double* best,
+                               const uint32_t* start, const GridOut& out, hipStream_t st) {
   const DevProblem<double>* P = (const DevProblem<double>*)P64;
-  const dim3 g((unsigned)(dim == 2 ? CellBlocks<2>::blocks(s) : CellBlocks<3>::blocks(s))), b(64);
-  const bool deep = depth > kBuildStack;
-  if (dim == 2) {
-    if (deep) hipLaunchKernelGGL((grid_fill_kernel<2, true>), g, b, 0, st, P, s, rule, best, near, start, out);
-    else hipLaunchKernelGGL((grid_fill_kernel<2, false>), g, b, 0, st, P, s, rule, best, near, start, out);
-  } else {
-    if (deep) hipLaunchKernelGGL((grid_fill_kernel<3, true>), g, b, 0, st, P, s, rule, best, near, start, out);
-    else hipLaunchKernelGGL((grid_fill_kernel<3, false>), g, b, 0, st, P, s, rule, best, near, start, out);
-  }
+  const dim3 g((unsigned)CellBlocks<2>::blocks(s)), b(64);
+  if (depth > kBuildStack) hipLaunchKernelGGL((segment_fill_kernel<true>), g, b, 0, st, P, s, rule, best, start, out);
+  else hipLaunchKernelGGL((segment_fill_kernel<false>), g, b, 0, st, P, s, rule, best, start, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_mesh_cells(int depth, const void* P64, const GridShape& s, const GridRule& rule, double* best,
+                             const GridOut& out, uint32_t* total, hipStream_t st) {
+  const DevProblem<double>* P = (const DevProblem<double>*)P64;
+  const dim3 g((unsigned)CellBlocks<3>::blocks(s)), b(64);
+  hipLaunchKernelGGL(scan_blocks_kernel, dim3(1), dim3(256), 0, st, (uint32_t*)nullptr, 0, total);   // total = 0
+  if (depth > kBuildStack) hipLaunchKernelGGL((mesh_cells_kernel<true>), g, b, 0, st, P, s, rule, best, out, total);
+  else hipLaunchKernelGGL((mesh_cells_kernel<false>), g, b, 0, st, P, s, rule, best, out, total);
   return hipGetLastError();
 }
 

@@ -85,18 +85,18 @@ hipError_t launch_classify(int dim, int geom, const void* P64, const double* pts
 // (`inside`: n bytes of scratch).
 hipError_t launch_sigma_sample(int dim, int geom, const void* P64, const double* lo, const double* h, int grid,
                                int64_t first, int64_t n, int nblocks, int8_t* inside, double* out, hipStream_t st);
-// Candidate grid of a polygon or mesh (P64: the problem on the device with its BVH): squared
-// centre distances, nearest primitives and list starts of the cells, and the total of the list lengths (depth:
-// of the BVH; sums: scan_sum_words(cells) words of scratch) ...
+// Candidate grid of a polygon (P64: the problem on the device with its BVH, of so many levels):
+// squared centre distances and list starts of the cells and the total of the list lengths
+// (sums: scan_sum_words(cells) words of scratch), then the lists and records.
 size_t scan_sum_words(int64_t cells);
-hipError_t launch_grid_count(int dim, int depth, const void* P64, const GridShape& s, const GridRule& rule, double* best,
-                             int32_t* near, uint32_t* count, uint32_t* sums, uint32_t* start, uint32_t* total,
-                             hipStream_t st);
-// ... the lists and records ...
-hipError_t launch_grid_fill(int dim, int depth, const void* P64, const GridShape& s, const GridRule& rule,
-                            const double* best, const int32_t* near, const uint32_t* start, const GridOut& out,
-                            hipStream_t st);
-// ... and the class of every cell of a closed boundary (reach: centre distance up to which a
+hipError_t launch_segment_count(int depth, const void* P64, const GridShape& s, const GridRule& rule, double* best,
+                                uint32_t* count, uint32_t* sums, uint32_t* start, uint32_t* total, hipStream_t st);
+hipError_t launch_segment_fill(int depth, const void* P64, const GridShape& s, const GridRule& rule, const double* best,
+                               const uint32_t* start, const GridOut& out, hipStream_t st);
+// The same for a mesh, whose records hold their lists.
+hipError_t launch_mesh_cells(int depth, const void* P64, const GridShape& s, const GridRule& rule, double* best,
+                             const GridOut& out, uint32_t* total, hipStream_t st);
+// The class of every cell of a closed boundary (reach: centre distance up to which a
 // primitive may touch the cell; label, roots: one word per cell of scratch).
 hipError_t launch_cell_classes(int dim, const void* P64, const GridShape& s, double reach, const double* best,
                                uint32_t* label, uint32_t* roots, uint32_t* n_roots, uint8_t* cls, hipStream_t st);
