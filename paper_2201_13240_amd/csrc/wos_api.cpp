@@ -660,14 +660,18 @@ hipError_t build_grid(wos_problem* p, const HostGeometry& g, DevProblem<float>& 
   uint32_t n = 0;
   if (seg) {
     e = launch_segment_count(p->depth, p->d64(), g.grid, g.rule, best, count, (uint32_t*)(b + o_sums), start, total, 0);
-    if (e == hipSuccess) e = hipMemcpy(&n, total, sizeof(n), hipMemcpyDeviceToHost);
+    uint32_t sizes[2] = {0, 0};   // candidates, truncated lists
+    if (e == hipSuccess) e = hipMemcpy(sizes, total, sizeof(sizes), hipMemcpyDeviceToHost);
     if (e != hipSuccess) return e;
+    n = sizes[0];
+    h32.geom.grid_bands = h64.geom.grid_bands = (uint64_t)sizes[1] * kBandCells > (uint64_t)nc;
   }
   off = 0;
+  const size_t n_list = (size_t)n + kListGroup;   // the last list is read in whole groups
   const size_t o_c32 = take(nc * (seg ? sizeof(CellRec<float>) : sizeof(MeshCell<float>))),
                o_c64 = take(nc * (seg ? sizeof(CellRec<double>) : sizeof(MeshCell<double>))), o_prim = take((size_t)n * 4),
-               o_s32 = take((size_t)n * 16), o_s64 = take((size_t)n * 32), o_d32 = take((size_t)n * 4),
-               o_d64 = take((size_t)n * 8), o_cls = take(nc);
+               o_s32 = take(n_list * 16), o_s64 = take(n_list * 32), o_d32 = take(n_list * 4),
+               o_d64 = take(n_list * 8), o_cls = take(nc);
   if ((e = hipMalloc(&p->grid_mem, off)) != hipSuccess) return e;
   b = (unsigned char*)p->grid_mem;
   const GridOut o{b + o_c32,           b + o_c64,           (int32_t*)(b + o_prim),

@@ -1747,7 +1747,7 @@ __device__ __forceinline__ T sdf_value(G<DevGeometry<T>>& g, const T* x, int* ac
 // (points deep inside, where many primitives are nearly equidistant): the ball of that
 // radius still lies inside the domain, which is all the walk's step needs, and a walk
 // never ends on such a value.
-template <typename T, int DIM, int GEOM, bool COUNT = false, bool BOUND = false>
+template <typename T, int DIM, int GEOM, bool COUNT = false, bool BOUND = false, int LIST = kListGroup>
 __device__ __forceinline__ T boundary_distance(G<DevGeometry<T>>& g, const T* x, int* prim, Tally* tally = nullptr,
                                                LdsStack<T> lds = LdsStack<T>{nullptr, nullptr, 0, 0}, int hint = -1) {
   if (GEOM == GK_BALL) {
@@ -1783,6 +1783,28 @@ __device__ __forceinline__ T boundary_distance(G<DevGeometry<T>>& g, const T* x,
           const int ix = (int)fx, iy = (int)fy;
           const WOS_GLOBAL CellRec<T>* rec = (const WOS_GLOBAL CellRec<T>*)g.cells + (iy * g.grid_nx + ix);
           const uint32_t n = rec->count, st = rec->start;
+          if constexpr (BOUND) {
+            // Cells with a truncated list are the deep ones, where `tail` bounds most walk
+            // steps in the end. Where the band around the list's segments lies beyond that
+            // bound, so do they, and the query needs none of them: two loads a lane instead
+            // of 7 inline and 9 listed candidates, whose lines come from beyond the L2 (the
+            // records of 4096 segments take 42 MB, their lists 100 MB).
+            if (g.grid_bands && rec->tail < Consts<T>::kInf) {
+              const WOS_GLOBAL ListBand<T>* band = (const WOS_GLOBAL ListBand<T>*)(gptr(g.cell_segs) + (size_t)st * 4);
+              const T ox = x[0] - m_fma((T)ix + (T)0.5, g.grid_h, g.grid_lo[0]);
+              const T oy = x[1] - m_fma((T)iy + (T)0.5, g.grid_h, g.grid_lo[1]);
+              const T lb = rec->tail - m_sqrt(m_fma(ox, ox, oy * oy));
+              const T reach = lb + band->radius;
+              if (lb >= g.grid_lb_min && segment_dist2_pre<T>(x, band->axis, band->inv_len2) > reach * reach) {
+                if constexpr (COUNT) {
+                  ++tally->cells;
+                  ++tally->prims;
+                }
+                *prim = kGridPrimTag | (int)st;
+                return lb;
+              }
+            }
+          }
           if (n > 0) {
             // the inline candidates are tested unconditionally (their loads do not wait
             // for the count); entries past a shorter list repeat its last candidate, which
@@ -1801,20 +1823,51 @@ __device__ __forceinline__ T boundary_distance(G<DevGeometry<T>>& g, const T* x,
             T lb = Consts<T>::kInf;
             if (n > (uint32_t)kCellInline) {
               // the rest of the list, nearest to the cell centre first: stop once a
-              // candidate's centre distance exceeds |x - centre| + best
+              // candidate's centre distance exceeds |x - centre| + best. The record tells for
+              // the first of them; the others are loaded a group at a time, so that a lane
+              // with a long list waits for one load in LIST candidates (lists of 25 deep
+              // inside large polygons kept whole waves waiting, one load after another)
+              constexpr int U = LIST;
               const WOS_GLOBAL T* segs = gptr(g.cell_segs) + (size_t)st * 4;
               const WOS_GLOBAL T* dc = gptr(g.cell_dc) + st;
               const T ox = x[0] - m_fma((T)ix + (T)0.5, g.grid_h, g.grid_lo[0]);
               const T oy = x[1] - m_fma((T)iy + (T)0.5, g.grid_h, g.grid_lo[1]);
               const T r_pc = m_sqrt(m_fma(ox, ox, oy * oy));
-              for (; k < n; ++k) {
-                const T lim = dc[k] - r_pc;
-                if (lim > (T)0 && lim * lim >= best) break;
-                T tp;
-                const T d2 = segment_dist2<T>(x, segs + (size_t)k * 4, &tp);
-                if (d2 < best) {
-                  best = d2;
-                  bk = k;
+              if constexpr (U == 1) {   // the walker's extras leave no registers for a group
+                for (; k < n; ++k) {
+                  const T lim = dc[k] - r_pc;
+                  if (lim > (T)0 && lim * lim >= best) break;
+                  T tp;
+                  const T d2 = segment_dist2<T>(x, segs + (size_t)k * 4, &tp);
+                  if (d2 < best) {
+                    best = d2;
+                    bk = k;
+                  }
+                }
+              } else {
+                const T lim0 = rec->next_dc - r_pc;
+                bool go = !(lim0 > (T)0 && lim0 * lim0 >= best);
+                while (go) {
+                  T sg[U][4], dk[U];   // past the end of the list: other cells' entries, or padding
+  #pragma unroll
+                  for (int u = 0; u < U; ++u) {
+                    dk[u] = dc[k + u];
+  #pragma unroll
+                    for (int e = 0; e < 4; ++e) sg[u][e] = segs[(size_t)(k + u) * 4 + e];
+                  }
+                  const uint32_t k0 = k;
+  #pragma unroll
+                  for (int u = 0; u < U; ++u) {
+                    const T lim = dk[u] - r_pc;
+                    go = go && k0 + u < n && !(lim > (T)0 && lim * lim >= best);
+                    T tp;
+                    const T d2 = segment_dist2<T>(x, (const T*)sg[u], &tp);
+                    if (go && d2 < best) {
+                      best = d2;
+                      bk = k0 + u;
+                    }
+                    k += go ? 1u : 0u;
+                  }
                 }
               }
               // a truncated list scanned to its end: the segments left off lie at

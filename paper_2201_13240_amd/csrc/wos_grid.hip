@@ -608,10 +608,11 @@ __device__ __forceinline__ int build_list(G<DevGeometry<double>>& g, const doubl
   return keep;
 }
 
-// Polygons: squared distance of each cell's centre and the length of its list.
+// Polygons: squared distance of each cell's centre, the length of its list, and how many lists
+// are truncated.
 template <bool DEEP>
 __global__ void __launch_bounds__(64) segment_count_kernel(const DevProblem<double>* P, GridShape s, GridRule rule,
-                                                           double* best_out, uint32_t* count) {
+                                                           double* best_out, uint32_t* count, uint32_t* truncated) {
   __shared__ BuildScratch<DEEP, 0> sc;
   double p[3];
   const int64_t c = block_cell<2>(s, p);
@@ -629,6 +630,8 @@ __global__ void __launch_bounds__(64) segment_count_kernel(const DevProblem<doub
     if (d2 <= r2 && ++n >= most) bound = -1.0;   // enough is known
   });
   count[c] = n >= most ? (uint32_t)rule.deep_list : n;
+  const uint64_t cut = __ballot(n >= most);
+  if (cut && (int)__lane_id() == __ffsll((unsigned long long)cut) - 1) atomicAdd(truncated, (uint32_t)__popcll(cut));
 }
 
 // Polygons: every cell's list from its start, and its record in both precisions; distances
@@ -662,6 +665,34 @@ __global__ void __launch_bounds__(64) segment_fill_kernel(const DevProblem<doubl
       o.segs64[(size_t)(st + k) * 4 + e] = v;
     }
   }
+  if (tail < __builtin_huge_val()) {
+    // the band of the list: its extent along the nearest segment and across it
+    const WOS_GLOBAL double* q = prims + (size_t)li[0] * kPrimStride2;
+    double ux = q[2] - q[0], uy = q[3] - q[1];
+    const double l = sqrt(ux * ux + uy * uy);
+    ux = l > 0 ? ux / l : 1.0;
+    uy = l > 0 ? uy / l : 0.0;
+    double t0 = 1e300, t1 = -1e300, w0 = 1e300, w1 = -1e300;
+    for (int k = 0; k < keep; ++k)
+      for (int v = 0; v < 4; v += 2) {
+        const WOS_GLOBAL double* e = prims + (size_t)li[k * 64] * kPrimStride2 + v;
+        const double t = (e[0] - q[0]) * ux + (e[1] - q[1]) * uy, w = (e[1] - q[1]) * ux - (e[0] - q[0]) * uy;
+        t0 = fmin(t0, t);
+        t1 = fmax(t1, t);
+        w0 = fmin(w0, w);
+        w1 = fmax(w1, w);
+      }
+    const double wm = 0.5 * (w0 + w1);
+    const double a[4] = {q[0] + t0 * ux - wm * uy, q[1] + t0 * uy + wm * ux, (t1 - t0) * ux, (t1 - t0) * uy};
+    auto band = [&](auto* b) {
+      using T = typename std::remove_reference<decltype(b->radius)>::type;
+      for (int e = 0; e < 4; ++e) b->axis[e] = (T)a[e];
+      b->inv_len2 = t1 > t0 ? (T)(1.0 / ((t1 - t0) * (t1 - t0))) : (T)0;
+      b->radius = (T)(0.5 * (w1 - w0) + 2 * rule.margin);   // the margin covers FP32 rounding here too
+    };
+    band((ListBand<float>*)(o.segs32 + (size_t)st * 4));
+    band((ListBand<double>*)(o.segs64 + (size_t)st * 4));
+  }
   auto record = [&](auto* rec) {
     using T = typename std::remove_reference<decltype(rec->tail)>::type;
     rec->count = (uint32_t)keep;
@@ -684,6 +715,7 @@ __global__ void __launch_bounds__(64) segment_fill_kernel(const DevProblem<doubl
       for (int e = 0; e < 4; ++e) rec->seg[k][e] = sg[e];
       rec->inv_len2[k] = inv;
     }
+    rec->next_dc = keep > kCellInline ? (T)(sqrt(ld[kCellInline * 64]) - rule.margin) : (T)0;
   };
   record((CellRec<float>*)o.cells32 + c);
   record((CellRec<double>*)o.cells64 + c);
@@ -930,8 +962,11 @@ hipError_t launch_segment_count(int depth, const void* P64, const GridShape& s, 
   const int64_t n = s.cells();
   const DevProblem<double>* P = (const DevProblem<double>*)P64;
   const dim3 g((unsigned)CellBlocks<2>::blocks(s)), b(64);
-  if (depth > kBuildStack) hipLaunchKernelGGL((segment_count_kernel<true>), g, b, 0, st, P, s, rule, best, count);
-  else hipLaunchKernelGGL((segment_count_kernel<false>), g, b, 0, st, P, s, rule, best, count);
+  hipLaunchKernelGGL(scan_blocks_kernel, dim3(1), dim3(256), 0, st, (uint32_t*)nullptr, 0, total + 1);   // = 0
+  if (depth > kBuildStack)
+    hipLaunchKernelGGL((segment_count_kernel<true>), g, b, 0, st, P, s, rule, best, count, total + 1);
+  else
+    hipLaunchKernelGGL((segment_count_kernel<false>), g, b, 0, st, P, s, rule, best, count, total + 1);
   const unsigned nb = blocks_for(n, 256 * kScanItems);
   hipLaunchKernelGGL(scan_sums_kernel, dim3(nb), dim3(256), 0, st, count, n, sums);
   hipLaunchKernelGGL(scan_blocks_kernel, dim3(1), dim3(256), 0, st, sums, (int)nb, total);

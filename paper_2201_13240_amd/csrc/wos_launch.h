@@ -86,8 +86,9 @@ hipError_t launch_classify(int dim, int geom, const void* P64, const double* pts
 hipError_t launch_sigma_sample(int dim, int geom, const void* P64, const double* lo, const double* h, int grid,
                                int64_t first, int64_t n, int nblocks, int8_t* inside, double* out, hipStream_t st);
 // Candidate grid of a polygon (P64: the problem on the device with its BVH, of so many levels):
-// squared centre distances and list starts of the cells and the total of the list lengths
-// (sums: scan_sum_words(cells) words of scratch), then the lists and records.
+// squared centre distances and list starts of the cells, the total of the list lengths
+// (total[0]) and the number of truncated lists (total[1]; sums: scan_sum_words(cells) words of
+// scratch), then the lists and records.
 size_t scan_sum_words(int64_t cells);
 hipError_t launch_segment_count(int depth, const void* P64, const GridShape& s, const GridRule& rule, double* best,
                                 uint32_t* count, uint32_t* sums, uint32_t* start, uint32_t* total, hipStream_t st);

@@ -489,6 +489,8 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
                             : sizeof(T) == 4 && GEOM == GK_POLYGON       ? 56
                             : sizeof(T) == 4 && GEOM == GK_TRIMESH       ? 22
                                                                          : 64;
+  // candidates of a polygon cell's list loaded at a time: the extras leave no registers for more
+  constexpr int kListLoads = EXTRA ? 1 : kListGroup;
   using Queue = EmitQueue<T, DIM, kQueueCap, EXTRA ? DIM : 0>;
   __shared__ __align__(16) unsigned char s_queue[4 * Queue::kBytes];
   Queue queue;
@@ -831,7 +833,8 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
             flag = kFlagCapped;
           } else {
             int prim;
-            const T d = boundary_distance<T, DIM, GEOM, COUNT, true>(P.geom, x, &prim, &tally, lds_stack(), last_prim);
+            const T d = boundary_distance<T, DIM, GEOM, COUNT, true, kListLoads>(P.geom, x, &prim, &tally, lds_stack(),
+                                                                                 last_prim);
             last_prim = prim;
             ++nsteps;
             if (!(d == d)) {

@@ -179,3 +179,38 @@ def test_sdf_cell_rows_decide_as_all_rows(W, dim, n):
             np.testing.assert_allclose(d.cpu().numpy(), ref, rtol=0, atol=tol)
         got = W.classify(h, dev(p)).cpu().numpy().astype(bool)
         assert np.array_equal(got, want > 0)
+
+
+def _fine_polygon(shape, n):
+    th = 2.0 * np.pi * np.arange(n) / n
+    if shape == "smooth":
+        return WL.star_polygon(np.random.default_rng(n), n)["vertices"]
+    if shape == "teeth":      # edges across the direction of the boundary
+        r = np.where(np.arange(n) % 2, 1.0, 0.97)
+        return np.c_[r * np.cos(th), r * np.sin(th)]
+    # a strip: lists deep inside hold edges of both long sides
+    m = n // 2
+    x = np.linspace(-1.0, 1.0, m)
+    return np.r_[np.c_[x, np.full(m, -0.15)], np.c_[x[::-1], np.full(m, 0.15)]]
+
+
+# more than a sixteenth of the cells hold truncated lists, whose band most queries stop at
+@pytest.mark.parametrize("shape,n", [("smooth", 2048), ("smooth", 4096), ("teeth", 3000), ("strip", 2600)])
+def test_walks_in_fine_polygons_match_the_oracle(W, shape, n):
+    """Estimates in polygons of many edges against the oracle's (exact distances), with bumps
+    on the boundary: a step that was too long would end walks at other places of it. 128
+    points, the parity criterion of all estimates."""
+    from oracle import oracle as O
+    from tests import parity as PR
+    from tests.gpu_common import gpu_solve
+    V = _fine_polygon(shape, n)
+    g = WL.geom_polygon(V)
+    rng = np.random.default_rng([n, 5])
+    boundary = WL.field_bumps(V[rng.integers(0, n, 12)], np.full(12, 0.25), rng.uniform(-1, 1, 12))
+    prob = WL.make_problem(2, g, ONE, ZERO, ZERO, ZERO, boundary)
+    pts = WL.sample_inside(rng, g, 2, 128)
+    ref = O.solve(prob, pts, 512, 20.0, seed=4, bvh=True)
+    h = W.Problem(prob, sigma_bar=20.0)
+    for precision, tol in (("fp32", 2e-6), ("fp64", 1e-12)):
+        r = gpu_solve(W, h, pts, 2048, precision, seed=3)
+        PR.assert_parity(r["mean"], r["se"], ref["mean"], ref["se"], f"{shape} {n} {precision}", tol)
