@@ -670,12 +670,10 @@ hipError_t build_grid(wos_problem* p, const HostGeometry& g, DevProblem<float>& 
   const size_t n_list = (size_t)n + kListGroup;   // the last list is read in whole groups
   const size_t o_c32 = take(nc * (seg ? sizeof(CellRec<float>) : sizeof(MeshCell<float>))),
                o_c64 = take(nc * (seg ? sizeof(CellRec<double>) : sizeof(MeshCell<double>))), o_prim = take((size_t)n * 4),
-               o_s32 = take(n_list * 16), o_s64 = take(n_list * 32), o_d32 = take(n_list * 4),
-               o_d64 = take(n_list * 8), o_cls = take(nc);
+               o_l32 = take(n_list * kListEntry * 4), o_l64 = take(n_list * kListEntry * 8), o_cls = take(nc);
   if ((e = hipMalloc(&p->grid_mem, off)) != hipSuccess) return e;
   b = (unsigned char*)p->grid_mem;
-  const GridOut o{b + o_c32,           b + o_c64,           (int32_t*)(b + o_prim),
-                  (float*)(b + o_s32), (float*)(b + o_d32), (double*)(b + o_s64), (double*)(b + o_d64)};
+  const GridOut o{b + o_c32, b + o_c64, (int32_t*)(b + o_prim), (float*)(b + o_l32), (double*)(b + o_l64)};
   if (seg) {
     e = launch_segment_fill(p->depth, p->d64(), g.grid, g.rule, best, start, o, 0);
   } else {
@@ -691,15 +689,14 @@ hipError_t build_grid(wos_problem* p, const HostGeometry& g, DevProblem<float>& 
     e = launch_cell_classes(p->dim, p->d64(), g.grid, g.rule.halfdiag + g.rule.margin, best, count, start, total, cls, 0);
     if (e != hipSuccess) return e;
   }
-  auto point = [&](auto& h, const void* cells, auto* segs, auto* dc) {
+  auto point = [&](auto& h, const void* cells, auto* list) {
     h.geom.cells = cells;
     h.geom.cell_prim = seg ? o.prim : nullptr;
-    h.geom.cell_segs = seg ? segs : nullptr;
-    h.geom.cell_dc = seg ? dc : nullptr;
+    h.geom.cell_list = seg ? list : nullptr;
     h.geom.cell_class = cls;
   };
-  point(h32, o.cells32, o.segs32, o.dc32);
-  point(h64, o.cells64, o.segs64, o.dc64);
+  point(h32, o.cells32, o.list32);
+  point(h64, o.cells64, o.list64);
   return hipSuccess;
 }
 

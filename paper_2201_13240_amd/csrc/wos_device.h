@@ -1790,7 +1790,7 @@ __device__ __forceinline__ T boundary_distance(G<DevGeometry<T>>& g, const T* x,
             // of 7 inline and 9 listed candidates, whose lines come from beyond the L2 (the
             // records of 4096 segments take 42 MB, their lists 100 MB).
             if (g.grid_bands && rec->tail < Consts<T>::kInf) {
-              const WOS_GLOBAL ListBand<T>* band = (const WOS_GLOBAL ListBand<T>*)(gptr(g.cell_segs) + (size_t)st * 4);
+              const WOS_GLOBAL ListBand<T>* band = (const WOS_GLOBAL ListBand<T>*)(gptr(g.cell_list) + (size_t)st * kListEntry);
               const T ox = x[0] - m_fma((T)ix + (T)0.5, g.grid_h, g.grid_lo[0]);
               const T oy = x[1] - m_fma((T)iy + (T)0.5, g.grid_h, g.grid_lo[1]);
               const T lb = rec->tail - m_sqrt(m_fma(ox, ox, oy * oy));
@@ -1828,17 +1828,17 @@ __device__ __forceinline__ T boundary_distance(G<DevGeometry<T>>& g, const T* x,
               // with a long list waits for one load in LIST candidates (lists of 25 deep
               // inside large polygons kept whole waves waiting, one load after another)
               constexpr int U = LIST;
-              const WOS_GLOBAL T* segs = gptr(g.cell_segs) + (size_t)st * 4;
-              const WOS_GLOBAL T* dc = gptr(g.cell_dc) + st;
+              const WOS_GLOBAL T* list = gptr(g.cell_list) + (size_t)st * kListEntry;
               const T ox = x[0] - m_fma((T)ix + (T)0.5, g.grid_h, g.grid_lo[0]);
               const T oy = x[1] - m_fma((T)iy + (T)0.5, g.grid_h, g.grid_lo[1]);
               const T r_pc = m_sqrt(m_fma(ox, ox, oy * oy));
               if constexpr (U == 1) {   // the walker's extras leave no registers for a group
                 for (; k < n; ++k) {
-                  const T lim = dc[k] - r_pc;
+                  const WOS_GLOBAL T* entry = list + (size_t)k * kListEntry;
+                  const T lim = entry[4] - r_pc;
                   if (lim > (T)0 && lim * lim >= best) break;
                   T tp;
-                  const T d2 = segment_dist2<T>(x, segs + (size_t)k * 4, &tp);
+                  const T d2 = segment_dist2<T>(x, entry, &tp);
                   if (d2 < best) {
                     best = d2;
                     bk = k;
@@ -1851,9 +1851,10 @@ __device__ __forceinline__ T boundary_distance(G<DevGeometry<T>>& g, const T* x,
                   T sg[U][4], dk[U];   // past the end of the list: other cells' entries, or padding
   #pragma unroll
                   for (int u = 0; u < U; ++u) {
-                    dk[u] = dc[k + u];
+                    const WOS_GLOBAL T* entry = list + (size_t)(k + u) * kListEntry;
+                    dk[u] = entry[4];
   #pragma unroll
-                    for (int e = 0; e < 4; ++e) sg[u][e] = segs[(size_t)(k + u) * 4 + e];
+                    for (int e = 0; e < 4; ++e) sg[u][e] = entry[e];
                   }
                   const uint32_t k0 = k;
   #pragma unroll

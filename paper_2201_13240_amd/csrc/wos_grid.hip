@@ -656,13 +656,15 @@ __global__ void __launch_bounds__(64) segment_fill_kernel(const DevProblem<doubl
     const int32_t id = li[k * 64];
     const double dc = sqrt(ld[k * 64]) - rule.margin;
     o.prim[st + k] = id;
-    o.dc32[st + k] = (float)dc;
-    o.dc64[st + k] = dc;
+    float* l32 = o.list32 + (size_t)(st + k) * kListEntry;
+    double* l64 = o.list64 + (size_t)(st + k) * kListEntry;
+    l32[4] = (float)dc;
+    l64[4] = dc;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const double v = prims[(size_t)id * kPrimStride2 + e];
-      o.segs32[(size_t)(st + k) * 4 + e] = (float)v;
-      o.segs64[(size_t)(st + k) * 4 + e] = v;
+      l32[e] = (float)v;
+      l64[e] = v;
     }
   }
   if (tail < __builtin_huge_val()) {
@@ -690,8 +692,8 @@ __global__ void __launch_bounds__(64) segment_fill_kernel(const DevProblem<doubl
       b->inv_len2 = t1 > t0 ? (T)(1.0 / ((t1 - t0) * (t1 - t0))) : (T)0;
       b->radius = (T)(0.5 * (w1 - w0) + 2 * rule.margin);   // the margin covers FP32 rounding here too
     };
-    band((ListBand<float>*)(o.segs32 + (size_t)st * 4));
-    band((ListBand<double>*)(o.segs64 + (size_t)st * 4));
+    band((ListBand<float>*)(o.list32 + (size_t)st * kListEntry));
+    band((ListBand<double>*)(o.list64 + (size_t)st * kListEntry));
   }
   auto record = [&](auto* rec) {
     using T = typename std::remove_reference<decltype(rec->tail)>::type;

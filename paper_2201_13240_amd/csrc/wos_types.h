@@ -39,6 +39,9 @@ constexpr int kCellInline = 7;
 // arrays end in as many entries of padding): star polygon FP32 66.1 -> 62.9 ms, FP64
 // 19.3 -> 18.7 ms, distances of 123,000 points 30.4 -> 26.2 us against one at a time.
 constexpr int kListGroup = 4;
+// Numbers of a list entry: the segment's ends and a lower bound of its distance from the cell's
+// centre, side by side, so that a group of them is a line or two and not two to four.
+constexpr int kListEntry = 5;
 // Length of the candidate lists of the triangle-mesh grid, and of the truncated lists
 // of polygon grid cells with more than kPolygonCellMax candidates.
 constexpr int kMeshCellList = 6;
@@ -78,12 +81,12 @@ struct GridRule {
 struct GridOut {
   void *cells32, *cells64;
   int32_t* prim;
-  float *segs32, *dc32;
-  double *segs64, *dc64;
+  float* list32;
+  double* list64;
 };
 
-// One cell of the polygon candidate grid: `count` candidates at cell_prim / cell_segs /
-// cell_dc [start, start + count), the first kCellInline also held here as start point,
+// One cell of the polygon candidate grid: `count` candidates at cell_prim and cell_list
+// [start, start + count), the first kCellInline also held here as start point,
 // edge vector and reciprocal squared length (x0, y0, ex, ey), 1/|e|^2, so that their
 // distance needs no division (a shorter list is padded with copies of its last
 // candidate). `tail` bounds from below the centre distance of every segment left off a
@@ -98,12 +101,12 @@ struct __attribute__((aligned(16))) CellRec {
   };
   T seg[kCellInline][4];
   T inv_len2[kCellInline];
-  T next_dc;   // cell_dc of the first candidate that is not held here (lists longer than that)
+  T next_dc;   // centre distance bound of the first candidate that is not held here (lists longer than that)
 };
 
 // A band that covers the segments of a truncated list: every one of them lies within `radius`
 // of the axis segment (start, edge vector, 1 / |e|^2). It takes the place of the list's first
-// two segments in cell_segs, which are read from the record instead.
+// two entries in cell_list, which are read from the record instead.
 template <typename T>
 struct ListBand {
   T axis[4];
@@ -111,7 +114,7 @@ struct ListBand {
   T radius;
   T pad[2];
 };
-static_assert(sizeof(ListBand<float>) == 8 * sizeof(float) && kCellInline >= 2, "two entries of cell_segs");
+static_assert(sizeof(ListBand<float>) <= 2 * kListEntry * sizeof(float) && kCellInline >= 2, "two entries of the list");
 
 // One cell of the triangle-mesh candidate grid: `count` candidates (triangles nearest to the
 // cell centre first) with lower bounds of their centre distances, and `tail`, a lower bound of
@@ -161,11 +164,11 @@ struct DevGeometry {
   // Uniform candidate grid of polygons and triangle meshes (grid_nx = 0: none). Cell
   // (i, j[, k]) covers [grid_lo + (i, j, k) h, grid_lo + (i + 1, j + 1, k + 1) h]; its
   // candidates are cell_prim[start .. start + count), nearest to the cell centre first;
-  // cell_dc holds a lower bound of each one's distance from the centre (the distance
-  // minus the rounding margin).
+  // with each one goes a lower bound of its distance from the centre (the distance minus the
+  // rounding margin).
   // Polygons: cells[c] is a CellRec with the list's length and start and a copy of its
-  // first kCellInline segments, so most queries read one record; cell_segs holds the
-  // segments of the whole list. Meshes: cells[c] is a MeshCell, cell (i, j, k) at
+  // first kCellInline segments, so most queries read one record; cell_list holds the
+  // whole list (kListEntry numbers each). Meshes: cells[c] is a MeshCell, cell (i, j, k) at
   // (k ny + j) nx + i, which holds its list.
   int32_t grid_nx, grid_ny, grid_nz;
   int32_t grid_bands;    // polygons: a good part of the cells holds a ListBand
@@ -176,8 +179,7 @@ struct DevGeometry {
   const void* cells;     // CellRec<T>[nx * ny], MeshCell<T>[nx * ny * nz] or, for SDF rows,
                          // uint64_t[nx * ny (* nz)] (kSdfCellRows)
   const int32_t* cell_prim;
-  const T* cell_segs;
-  const T* cell_dc;
+  const T* cell_list;
   const uint8_t* cell_class;   // per cell: 0 outside, 1 inside, kCellMixed on the boundary; null:
                                // the mesh is not closed
 };
