@@ -17,7 +17,7 @@ ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 SOURCES = ["wos_walker_f64_3d.hip", "wos_walker_f64_2d.hip", "wos_walker_f32_3d.hip", "wos_walker_f32_2d.hip",
            "wos_kernels.hip", "wos_grid.hip", "wos_api.cpp", "bvh.cpp"]
 HEADERS = ["wos_walker.h", "wos_device.h", "wos_types.h", "wos_launch.h", "bvh.h", "bessel_tables.h",
-           "proposal_bound.h"]
+           "proposal_bound.h", "triangle.h"]
 
 # Packed FP32 instructions are disabled for all device code (the compiler forms them
 # from scalar float code on its own otherwise).
