@@ -241,6 +241,7 @@ typedef struct {
  *  points:   device double [n_points][dim] (caller-owned).
  *  sum, sum_sq, n_walks, n_steps: device [n_points] accumulators; every call ADDS the new
  *            walks' sum of estimates, sum of squares, walk count and distance-query count.
+ *            Items may share them, in whole or in part: they are added in the items' order.
  *  counters: device uint64 [4] or NULL, also accumulated: [0] query points outside the
  *            domain or non-finite (their sum becomes NaN), [1] walks cut at max_steps,
  *            [2] walks ended by Russian roulette, [3] radius proposals drawn by the

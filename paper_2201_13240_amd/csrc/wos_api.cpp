@@ -1343,6 +1343,39 @@ wos_status prep_job(const wos_batch_item* items, int n_items, const Schedule& s,
   return WOS_OK;
 }
 
+// Whether any two of the items' output arrays share memory (two items of a batch may add into
+// one set of accumulators, or into overlapping parts of a larger one).
+bool outputs_overlap(const std::vector<DevItem>& d, int grad_dim) {
+  std::vector<std::pair<uintptr_t, uintptr_t>> r;
+  for (const DevItem& x : d) {
+    if (x.n_points == 0) continue;
+    const uintptr_t n = (uintptr_t)x.n_points * 8;   // every output is 8 bytes wide
+    for (const void* p : {(const void*)x.sum, (const void*)x.sum_sq, (const void*)x.n_walks, (const void*)x.n_steps})
+      r.emplace_back((uintptr_t)p, (uintptr_t)p + n);
+    for (const void* p : {(const void*)x.grad_sum, (const void*)x.grad_sum_sq})
+      if (grad_dim && p) r.emplace_back((uintptr_t)p, (uintptr_t)p + n * grad_dim);
+  }
+  std::sort(r.begin(), r.end());
+  for (size_t k = 1; k < r.size(); ++k)
+    if (r[k].first < r[k - 1].second) return true;
+  return false;
+}
+
+// Adds every item's sums into its outputs, in one launch; items that share outputs are added
+// one after another, as their blocks would race on them.
+hipError_t reduce_items(const std::vector<DevItem>& d, const Schedule& s, const DevItem* table, const uint64_t* slots,
+                        hipStream_t st) {
+  auto blocks = [](const DevItem& x) { return ((uint64_t)x.n_points + kReducePoints - 1) / kReducePoints; };
+  if (d.size() == 1 || !outputs_overlap(d, s.grad_dim))
+    return launch_reduce(s.grad_dim, table, (int)d.size(), 0, d.back().reduce_block + blocks(d.back()), slots,
+                         s.slot_words, st);
+  for (size_t k = 0; k < d.size(); ++k) {
+    const hipError_t e = launch_reduce(s.grad_dim, table + k, 1, d[k].reduce_block, blocks(d[k]), slots, s.slot_words, st);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 // Enqueues [clear, walker, reduce] for every launch of the schedule (`cleared`: the first one
 // finds its slots and counters cleared). With `marks`, an event pair is recorded around each
 // walker launch (eager timing only: a captured job takes none).
@@ -1359,9 +1392,7 @@ wos_status enqueue_job(int n_items, const wos_options* opt, const Schedule& s, c
     if (marks) WOS_HIP(hipEventRecord((*marks)[2 * c], st));
     WOS_HIP(launch_walker(L, st));
     if (marks) WOS_HIP(hipEventRecord((*marks)[2 * c + 1], st));
-    const DevItem& last = dit[c].back();
-    const uint64_t blocks = last.reduce_block + ((uint64_t)last.n_points + kReducePoints - 1) / kReducePoints;
-    WOS_HIP(launch_reduce(s.grad_dim, table, n_items, blocks, w.slots, s.slot_words, st));
+    WOS_HIP(reduce_items(dit[c], s, table, w.slots, st));
   }
   return WOS_OK;
 }

@@ -51,16 +51,18 @@ __device__ __forceinline__ void fx_accumulate(int64_t* L, const uint64_t* words)
 // of the gradient components (supplemental Sec. 2).
 template <int GD>
 __global__ void __launch_bounds__(kReducePoints) reduce_kernel(const DevItem* __restrict__ items, int n_items,
-                                                               const uint64_t* __restrict__ slots, int slot_words) {
+                                                               uint64_t block0, const uint64_t* __restrict__ slots,
+                                                               int slot_words) {
+  const uint64_t block = block0 + blockIdx.x;
   // the block's item: the last one that starts at or before it
   int lo = 0;
   for (int hi = n_items; hi - lo > 1;) {
     const int mid = (lo + hi) / 2;
-    if (gptr(items)[mid].reduce_block <= blockIdx.x) lo = mid;
+    if (gptr(items)[mid].reduce_block <= block) lo = mid;
     else hi = mid;
   }
   G<DevItem>& it = gptr(items)[lo];
-  const int64_t p = (int64_t)(blockIdx.x - it.reduce_block) * blockDim.x + threadIdx.x;
+  const int64_t p = (int64_t)(block - it.reduce_block) * blockDim.x + threadIdx.x;
   uint64_t capped = 0, killed = 0;
   if (p < it.n_points) {
     const uint32_t spp = it.tiles_per_point > 0u ? it.tiles_per_point : 1u;
@@ -312,13 +314,13 @@ const void* walker_symbol(int fp64, int dim, int geom, int mode) {
   return dim == 2 ? walker_symbol_f32_2d(geom, mode) : walker_symbol_f32_3d(geom, mode);
 }
 
-hipError_t launch_reduce(int grad_dim, const DevItem* items, int n_items, uint64_t n_blocks, const uint64_t* slots,
-                         int slot_words, hipStream_t st) {
+hipError_t launch_reduce(int grad_dim, const DevItem* items, int n_items, uint64_t block0, uint64_t n_blocks,
+                         const uint64_t* slots, int slot_words, hipStream_t st) {
   if (n_blocks == 0) return hipSuccess;
   const dim3 g((unsigned)n_blocks), b(kReducePoints);
-  if (grad_dim == 2) hipLaunchKernelGGL(reduce_kernel<2>, g, b, 0, st, items, n_items, slots, slot_words);
-  else if (grad_dim == 3) hipLaunchKernelGGL(reduce_kernel<3>, g, b, 0, st, items, n_items, slots, slot_words);
-  else hipLaunchKernelGGL(reduce_kernel<0>, g, b, 0, st, items, n_items, slots, slot_words);
+  if (grad_dim == 2) hipLaunchKernelGGL(reduce_kernel<2>, g, b, 0, st, items, n_items, block0, slots, slot_words);
+  else if (grad_dim == 3) hipLaunchKernelGGL(reduce_kernel<3>, g, b, 0, st, items, n_items, block0, slots, slot_words);
+  else hipLaunchKernelGGL(reduce_kernel<0>, g, b, 0, st, items, n_items, block0, slots, slot_words);
   return hipGetLastError();
 }
 

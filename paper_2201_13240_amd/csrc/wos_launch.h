@@ -69,11 +69,11 @@ hipError_t static_scratch(int device, void** ptr);
 // 0 delta tracking, 1 delta tracking with splitting or gradient records, 2 next flight
 int walker_mode(int variant, bool grad, bool split);
 const void* walker_symbol(int fp64, int dim, int geom, int mode);
-// Per-point sums of every item from its slots, added into the item's outputs (n_blocks: blocks
-// of kReducePoints points, each item its own).
+// Per-point sums of the items from their slots, added into the items' outputs (n_blocks: blocks
+// of kReducePoints points from block0 on, each item its own; no two items share outputs).
 constexpr int kReducePoints = 256;
-hipError_t launch_reduce(int grad_dim, const DevItem* items, int n_items, uint64_t n_blocks, const uint64_t* slots,
-                         int slot_words, hipStream_t st);
+hipError_t launch_reduce(int grad_dim, const DevItem* items, int n_items, uint64_t block0, uint64_t n_blocks,
+                         const uint64_t* slots, int slot_words, hipStream_t st);
 // Zeroes n words at p and the tile counters (a kernel, so that it can sit in a captured graph).
 hipError_t launch_clear(uint64_t* p, uint64_t n, uint32_t* counters, hipStream_t st);
 hipError_t launch_finalize_components(const double* sum, const double* sum_sq, const uint64_t* nw, int64_t n, int dim,
