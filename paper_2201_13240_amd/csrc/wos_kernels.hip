@@ -48,7 +48,7 @@ __device__ __forceinline__ void fx_accumulate(int64_t* L, const uint64_t* words)
 
 // Per point: the exact sums of its slots (one per tile it was cut into), converted to
 // double once and added into the caller's accumulators. With grad_dim > 0 also the sums
-// of the gradient components (supplemental Sec. 2).
+// of the gradient components (supplemental Sec. 2), for the items that ask for them.
 template <int GD>
 __global__ void __launch_bounds__(kReducePoints) reduce_kernel(const DevItem* __restrict__ items, int n_items,
                                                                uint64_t block0, const uint64_t* __restrict__ slots,
@@ -63,6 +63,7 @@ __global__ void __launch_bounds__(kReducePoints) reduce_kernel(const DevItem* __
   }
   G<DevItem>& it = gptr(items)[lo];
   const int64_t p = (int64_t)(block - it.reduce_block) * blockDim.x + threadIdx.x;
+  const bool grad = GD > 0 && it.grad_sum != nullptr;
   uint64_t capped = 0, killed = 0;
   if (p < it.n_points) {
     const uint32_t spp = it.tiles_per_point > 0u ? it.tiles_per_point : 1u;
@@ -71,7 +72,7 @@ __global__ void __launch_bounds__(kReducePoints) reduce_kernel(const DevItem* __
       it.sum[p] += nan;
       it.sum_sq[p] += nan;
 #pragma unroll
-      for (int c = 0; c < GD; ++c) {
+      for (int c = 0; grad && c < GD; ++c) {
         it.grad_sum[p * GD + c] += nan;
         it.grad_sum_sq[p * GD + c] += nan;
       }
@@ -102,7 +103,7 @@ __global__ void __launch_bounds__(kReducePoints) reduce_kernel(const DevItem* __
       it.sum[p] += bad ? nan : fx_value(S);
       it.sum_sq[p] += bad ? nan : fx_value(Q);
 #pragma unroll
-      for (int c = 0; c < GD; ++c) {
+      for (int c = 0; grad && c < GD; ++c) {
         it.grad_sum[p * GD + c] += bad ? nan : fx_value(GS[c]);
         it.grad_sum_sq[p * GD + c] += bad ? nan : fx_value(GQ[c]);
       }
