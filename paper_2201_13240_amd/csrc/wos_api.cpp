@@ -1111,14 +1111,21 @@ wos_status pick_shape(const wos_options* opt, Schedule& s) {
   wos_status r = grid_for_block(s, block);
   if (r != WOS_OK) return r;
   const uint64_t lanes = (uint64_t)s.grid * s.block, walks = s.total_points * opt->walks_per_point;
-  if (opt->tile_walks > 0) tile = (uint32_t)opt->tile_walks;
-  else if (!tuned || walks < tune_walks(lanes)) tile = std::min(tile, tile_for(walks, lanes));
-  s.tile_walks = tile;
   const uint64_t cap = opt->workspace_bytes ? opt->workspace_bytes : (4ull << 30);
   const uint64_t slot_bytes = (uint64_t)s.slot_words * 8u;
   const uint64_t N = opt->walks_per_point;
+  auto fits = [&](uint32_t t) { return slots_for(s.total_points, N, t) * slot_bytes <= cap; };
+  if (opt->tile_walks > 0) {
+    tile = (uint32_t)opt->tile_walks;
+  } else if (!tuned || walks < tune_walks(lanes)) {
+    // shorter tiles take more slots: none so short that the job would need more launches
+    uint32_t t = std::min(tile, tile_for(walks, lanes));
+    while (t < tile && !fits(t)) t = std::min(2 * t, tile);
+    tile = t;
+  }
+  s.tile_walks = tile;
   uint64_t nc = N;
-  if (s.total_points > 0 && slots_for(s.total_points, N, tile) * slot_bytes > cap) {
+  if (s.total_points > 0 && !fits(tile)) {
     const uint64_t tiles_per_point = std::max<uint64_t>(1, cap / slot_bytes / s.total_points);
     nc = std::min<uint64_t>(N, tiles_per_point * tile);
   }
