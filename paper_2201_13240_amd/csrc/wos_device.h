@@ -1636,12 +1636,12 @@ __device__ __forceinline__ void sdf_fold(int op, int k, T fk, T& f, int& act) {
 }
 
 // Combined field f of the operation list (from f = +inf). Where the domain has a grid, the
-// lane's cell names the rows that can decide f in it (SdfCell), which leaves 1 to 4 of the 33
+// lane's cell names the rows that can decide f in it (kSdfCellRows), which leaves 1 to 4 of the 33
 // rows of a scattered scene; the rows are read per lane. Cells with more of them, points
 // outside the grid and short lists take every row: those sit at wave-uniform addresses
 // (scalar loads), at about 470 cycles a row.
-template <typename T, int DIM>
-__device__ __forceinline__ T sdf_value(G<DevGeometry<T>>& g, const T* x, int* active) {
+template <typename T, int DIM, bool COUNT = false>
+__device__ __forceinline__ T sdf_value(G<DevGeometry<T>>& g, const T* x, int* active, Tally* tally = nullptr) {
   const WOS_GLOBAL T* rows = gptr(g.prims);
   T f = Consts<T>::kInf;
   int act = 0;
@@ -1659,8 +1659,10 @@ __device__ __forceinline__ T sdf_value(G<DevGeometry<T>>& g, const T* x, int* ac
     if (in) {
       const uint64_t list = ((const WOS_GLOBAL uint64_t*)g.cells)[c];
       const int n = (int)(list & 0xFFu);
+      if constexpr (COUNT) ++tally->cells;
       if (n <= kSdfCellRows) {
         all = false;
+        if constexpr (COUNT) tally->prims += n;
         for (int j = 0; j < n; ++j) {
           const int k = (int)(list >> (8 * j + 8) & 0xFFu);
           const WOS_GLOBAL T* p = rows + (size_t)k * kSdfStride;
@@ -1680,6 +1682,7 @@ __device__ __forceinline__ T sdf_value(G<DevGeometry<T>>& g, const T* x, int* ac
     }
   }
   if (all) {
+    if constexpr (COUNT) tally->prims += g.n_prims;
     for (int k = 0; k < g.n_prims; ++k) {
       const WOS_GLOBAL T* r = rows + (size_t)k * kSdfStride;
       sdf_fold((int)r[0], k, sdf_shape<T, DIM, false>(r, x, nullptr), f, act);
@@ -1721,8 +1724,7 @@ __device__ __forceinline__ T boundary_distance(G<DevGeometry<T>>& g, const T* x,
     *prim = best;
     return d;
   } else if (GEOM == GK_SDF) {
-    if constexpr (COUNT) tally->prims += g.n_prims;
-    return -sdf_value<T, DIM>(g, x, prim);
+    return -sdf_value<T, DIM, COUNT>(g, x, prim, tally);
   } else {
     if constexpr (GEOM == GK_POLYGON) {
       if (g.grid_nx > 0) {
