@@ -1393,27 +1393,29 @@ __device__ __forceinline__ T triangle_dist2(const T* p, PT tri) {
 
 constexpr int kPrimStride2 = 4;    // segment: x0 y0 x1 y1
 constexpr int kPrimStride3 = 12;   // triangle: a, b, c, (pad)
-constexpr int kStackDepth = 48;     // private (scratch) stack: any tree the host accepts
+constexpr int kStackDepth = 48;     // levels of any tree the host accepts
 // LDS stack depths of the walker. The walker's LDS must leave room for five 256-thread
 // blocks per CU beside the queue of finished walks: the mesh walker takes trees of depth
 // <= 13 (26 KB in FP32; up to 32,768 triangles), the polygon walker, whose candidate grid
-// answers most queries, trees of depth <= 11 (22 KB; up to 8192 edges). Deeper trees use the
-// private stack.
+// answers most queries, trees of depth <= 11 (22 KB; up to 8192 edges). Searches of deeper
+// trees use private memory (StackPlace).
 constexpr int kLdsStackDepth = 13;
 constexpr int kLdsStackDepthPolygon = 11;
 
-// Traversal stack of far children with their box distances, either in LDS (one column
-// per lane: entry k of lane t at k * stride + t, conflict-free) for trees of depth <= depth,
-// or in private memory.
+// Traversal stack of far children with their box distances in LDS, one column per lane: entry
+// k of lane t at k * stride + t, conflict-free, for k < depth.
 template <typename T>
 struct LdsStack {
-  int32_t* node;   // null: use the private stack
+  int32_t* node;
   T* dist;
   int stride;
   int depth;
 };
 
-// Nearest primitive by BVH traversal; returns squared distance and primitive index.
+// Where the waiting nodes of a search are: in the LDS column, in private memory, or in the column
+// first and beyond it in private memory.
+enum StackPlace { STACK_LDS, STACK_PRIVATE, STACK_BOTH };
+
 template <typename T, int DIM>
 __device__ __forceinline__ T prim_dist2(const WOS_GLOBAL T* prims, const T* x, int pi) {
   if (DIM == 2) {
@@ -1428,75 +1430,21 @@ __device__ __forceinline__ T prim_dist2(const WOS_GLOBAL T* prims, const T* x, i
 // the previous distance per step, so the previous closest primitive is usually still
 // closest or nearly so, and the traversal then prunes all but a few nodes. The result
 // is the exact nearest distance either way.
-template <typename T, int DIM, bool COUNT = false>
-__device__ __forceinline__ T bvh_nearest(G<DevGeometry<T>>& g, const T* x, int* best_prim, Tally* tally = nullptr,
-                                         LdsStack<T> lds = LdsStack<T>{nullptr, nullptr, 0, 0}, int hint = -1) {
-  if (lds.node && g.depth <= lds.depth) {
-    const WOS_GLOBAL BvhNode<T, DIM>* nodes = (const WOS_GLOBAL BvhNode<T, DIM>*)g.nodes;
-    const WOS_GLOBAL T* prims = gptr(g.prims);
-    T best = Consts<T>::kInf;
-    int bp = -1;
-    if (hint >= 0) {
-      best = prim_dist2<T, DIM>(prims, x, hint);
-      bp = hint;
-      if constexpr (COUNT) ++tally->prims;
-    }
-    int sp = 0;
-    int cur = g.root;
-    T cur_d = 0;
-    for (;;) {
-      if (cur_d < best) {
-        if (cur < 0) {
-          const int code = -1 - cur;
-          const int first = code >> 3, cnt = code & 7;
-          if constexpr (COUNT) tally->prims += cnt;
-          for (int k = 0; k < cnt; ++k) {
-            const int pi = first + k;
-            T d2;
-            if (DIM == 2) {
-              T tp;
-              d2 = segment_dist2<T>(x, prims + (size_t)pi * kPrimStride2, &tp);
-            } else {
-              d2 = triangle_dist2<T>(x, prims + (size_t)pi * kPrimStride3);
-            }
-            if (d2 < best) {
-              best = d2;
-              bp = pi;
-            }
-          }
-        } else {
-          G<BvhNode<T, DIM>>& n = nodes[cur];
-          if constexpr (COUNT) ++tally->nodes;
-          const T da = box_dist2<T, DIM>(x, n.lo[0], n.hi[0]);
-          const T db = box_dist2<T, DIM>(x, n.lo[1], n.hi[1]);
-          const int ca = n.child[0], cb = n.child[1];
-          const bool a_first = da <= db;
-          const int near_c = a_first ? ca : cb, far_c = a_first ? cb : ca;
-          const T near_d = a_first ? da : db, far_d = a_first ? db : da;
-          if (far_d < best) {  // at most one entry per level above the current node
-            lds.node[sp * lds.stride] = far_c;
-            lds.dist[sp * lds.stride] = far_d;
-            ++sp;
-          }
-          cur = near_c;
-          cur_d = near_d;
-          continue;
-        }
-      }
-      if (sp == 0) break;
-      --sp;
-      cur = lds.node[sp * lds.stride];
-      cur_d = lds.dist[sp * lds.stride];
-    }
-    *best_prim = bp;
-    return best;
-  }
+template <typename T, int DIM, bool COUNT, StackPlace PLACE>
+__device__ __forceinline__ T bvh_search(G<DevGeometry<T>>& g, const T* x, int* best_prim, Tally* tally,
+                                        LdsStack<T> lds, int hint) {
   const WOS_GLOBAL BvhNode<T, DIM>* nodes = (const WOS_GLOBAL BvhNode<T, DIM>*)g.nodes;
   const WOS_GLOBAL T* prims = gptr(g.prims);
+  constexpr int kFirst = PLACE == STACK_BOTH ? kLdsStackDepth : 0;   // first entry in private memory
+  int32_t own_node[PLACE == STACK_LDS ? 1 : kStackDepth - kFirst];
+  T own_dist[PLACE == STACK_LDS ? 1 : kStackDepth - kFirst];
   T best = Consts<T>::kInf;
   int bp = -1;
-  int stack[kStackDepth];
-  T stack_d[kStackDepth];
+  if (hint >= 0) {
+    best = prim_dist2<T, DIM>(prims, x, hint);
+    bp = hint;
+    if constexpr (COUNT) ++tally->prims;
+  }
   int sp = 0;
   int cur = g.root;
   T cur_d = 0;
@@ -1529,9 +1477,14 @@ __device__ __forceinline__ T bvh_nearest(G<DevGeometry<T>>& g, const T* x, int* 
         const bool a_first = da <= db;
         const int near_c = a_first ? ca : cb, far_c = a_first ? cb : ca;
         const T near_d = a_first ? da : db, far_d = a_first ? db : da;
-        if (far_d < best && sp < kStackDepth) {
-          stack[sp] = far_c;
-          stack_d[sp] = far_d;
+        if (far_d < best) {  // at most one entry per level above the current node
+          if (PLACE == STACK_LDS || (PLACE == STACK_BOTH && sp < kFirst)) {
+            lds.node[sp * lds.stride] = far_c;
+            lds.dist[sp * lds.stride] = far_d;
+          } else {
+            own_node[sp - kFirst] = far_c;
+            own_dist[sp - kFirst] = far_d;
+          }
           ++sp;
         }
         cur = near_c;
@@ -1541,11 +1494,30 @@ __device__ __forceinline__ T bvh_nearest(G<DevGeometry<T>>& g, const T* x, int* 
     }
     if (sp == 0) break;
     --sp;
-    cur = stack[sp];
-    cur_d = stack_d[sp];
+    if (PLACE == STACK_LDS || (PLACE == STACK_BOTH && sp < kFirst)) {
+      cur = lds.node[sp * lds.stride];
+      cur_d = lds.dist[sp * lds.stride];
+    } else {
+      cur = own_node[sp - kFirst];
+      cur_d = own_dist[sp - kFirst];
+    }
   }
   *best_prim = bp;
   return best;
+}
+
+// Meshes search with the stack in both places, whatever the tree's depth: 81,920 triangles (depth
+// 15) 19.4 ms, with a loop of its own for deep trees in private memory alone 20.7, and without the
+// hint there 25.9; 20,480 triangles 7.8 ms with one loop or two. Polygons have the two loops: the
+// walker with gradients is at the limit of its registers, and the place of an entry in one loop
+// cost it 2% (2.89 and 2.96 ms for 7,700 points x 256 walks in 256 edges), where 12,000 edges
+// with the widest epsilon shells (0.03) would run 16.4 instead of 19.8 ms.
+template <typename T, int DIM, bool COUNT = false>
+__device__ __forceinline__ T bvh_nearest(G<DevGeometry<T>>& g, const T* x, int* best_prim, Tally* tally,
+                                         LdsStack<T> lds, int hint) {
+  if constexpr (DIM == 3) return bvh_search<T, DIM, COUNT, STACK_BOTH>(g, x, best_prim, tally, lds, hint);
+  if (g.depth <= lds.depth) return bvh_search<T, DIM, COUNT, STACK_LDS>(g, x, best_prim, tally, lds, hint);
+  return bvh_search<T, DIM, COUNT, STACK_PRIVATE>(g, x, best_prim, tally, lds, hint);
 }
 
 // A polygon grid query returns its candidate list position tagged with kGridPrimTag

@@ -471,11 +471,12 @@ __device__ __forceinline__ void walker_body(WalkerArgs<T> a, uint32_t* __restric
   __shared__ int32_t s_node[kHasStack ? kStack * 256 : 1];
   __shared__ T s_dist[kHasStack ? kStack * 256 : 1];
   const int wave = uniform_int((int)(threadIdx.x >> 6));
-  // the lane's column of the stack
+  // the lane's column of the stack, 256 apart whatever the block (a number to multiply with
+  // would take a scalar register through the whole loop)
   auto lds_stack = [&]() {
     if constexpr (!kHasStack) return LdsStack<T>{nullptr, nullptr, 0, 0};
     const uint32_t c = (uint32_t)wave * 64u + lane_here();
-    return LdsStack<T>{s_node + c, s_dist + c, (int)blockDim.x, kStack};
+    return LdsStack<T>{s_node + c, s_dist + c, 256, kStack};
   };
   // LDS cache of accumulation slots: gradient slots are larger, so fewer entries
   constexpr int kCacheWords = EXTRA ? 64 : 16;
