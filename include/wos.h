@@ -227,7 +227,7 @@ typedef struct {
                                  problem_index < 2^16 (branch streams use the top half
                                  of that counter word) and ww_hi > ww_lo with roulette. */
   uint64_t max_steps;         /* distance queries per walk before it is cut (0: 10^6) */
-  int32_t block_size;         /* 0: autotuned/default; else 64..1024, multiple of 64 */
+  int32_t block_size;         /* 0: autotuned/default; else 64, 128, 192 or 256 */
   int32_t tile_walks;         /* 0: default; walks of one point per work tile taken by a
                                  wavefront (a tile holds whole points when a point has
                                  fewer walks), at most 65536 */
@@ -328,7 +328,8 @@ wos_status wos_finalize_grad(const double* grad_sum, const double* grad_sum_sq, 
  * walks (eight per resident lane; the per-walk buffers of the plan's workspace only, the
  * caller's outputs are not touched), keeps the fastest for that variant, and builds with
  * it. Later plans and wos_solve of the same variant reuse it. Jobs with fewer walks than
- * the prefix are not timed: they take tiles of 64 to 256 walks, shorter for smaller jobs.
+ * the prefix are not timed: they take tiles of 64 to 256 walks, shorter for smaller jobs as
+ * far as the workspace cap allows without further launches.
  * Explicit values are used as given. Synchronous; the caller's stream is used for the
  * timing runs. */
 typedef struct wos_plan wos_plan;

@@ -60,8 +60,9 @@ double deep_distance(const GridShape& s);
 // fingerprint of the signed edges, which is zero for a closed set.
 bool closed_mesh(const int32_t* triangles, int64_t n);
 
-// Reference construction of the grids on the host: what the device builds (grid_count_kernel,
-// grid_fill_kernel) is held against it.
+// Reference construction of the grids on the host. Nothing in the library calls it: the lists
+// that the device builds (segment_count_kernel, segment_fill_kernel, mesh_cells_kernel) are held
+// against it entry by entry by the tests, and a scan of its lists against brute force.
 //
 // segs: [n][4] in leaf order; topo/bounds: the BVH over them (child bounds as produced
 // by bvh_child_bounds<double>). target_cells bounds the grid size. Each list is sorted by

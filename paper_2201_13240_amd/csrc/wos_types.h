@@ -48,6 +48,8 @@ constexpr int kMeshCellList = 6;
 constexpr int kPolygonCellMax = 32;
 constexpr int kPolygonDeepList = 16;
 
+// Class of a cell that the boundary may touch, and the label of such a cell while the classes
+// of the others are found.
 constexpr int kCellMixed = 2;
 constexpr uint32_t kNoLabel = 0xFFFFFFFFu;
 
@@ -118,10 +120,11 @@ static_assert(sizeof(ListBand<float>) <= 2 * kListEntry * sizeof(float) && kCell
 
 // One cell of the triangle-mesh candidate grid: `count` candidates (triangles nearest to the
 // cell centre first) with lower bounds of their centre distances, and `tail`, a lower bound of
-// the centre distance of every triangle left off the list (+inf: none was). A record is one
-// cache line: with the lists in arrays of their own, a query waited for three lines one after
-// another, from far beyond the L2 (92 MB for 20,480 triangles): 33.0 ms for a slice of 131,072
-// points x 64 walks, 21.3 ms with the records.
+// the centre distance of every triangle left off the list (+inf: none was). In FP32 a record is
+// half a cache line (64 bytes); in FP64 (96 bytes) every other one lies across two. With the lists
+// in arrays of their own, a query waited for three lines one after another, from far beyond the
+// L2 (92 MB for 20,480 triangles): 33.0 ms for a slice of 131,072 points x 64 walks in FP32,
+// 21.3 ms with the records.
 template <typename T>
 struct __attribute__((aligned(32))) MeshCell {
   uint32_t count;
