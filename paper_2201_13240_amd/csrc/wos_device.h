@@ -1506,18 +1506,18 @@ __device__ __forceinline__ T bvh_search(G<DevGeometry<T>>& g, const T* x, int* b
   return best;
 }
 
-// Meshes search with the stack in both places, whatever the tree's depth: 81,920 triangles (depth
-// 15) 19.4 ms, with a loop of its own for deep trees in private memory alone 20.7, and without the
-// hint there 25.9; 20,480 triangles 7.8 ms with one loop or two. Polygons have the two loops: the
-// walker with gradients is at the limit of its registers, and the place of an entry in one loop
-// cost it 2% (2.89 and 2.96 ms for 7,700 points x 256 walks in 256 edges), where 12,000 edges
-// with the widest epsilon shells (0.03) would run 16.4 instead of 19.8 ms.
+// Trees within the LDS column have a loop of their own (one loop with the entry's place to decide
+// cost small meshes 1 to 3%, and the polygon walker with gradients, at the limit of its registers,
+// 2%). Deeper meshes keep the column's part of their stack there: 81,920 triangles (depth 15)
+// 19.4 ms, all in private memory 20.7. Deeper polygons search in private memory: 12,000 edges run
+// 10.0 ms either way, and 19.8 instead of 16.4 with the widest epsilon shells (0.03), but the
+// second place in their loop, too, cost the walker with gradients 2%.
 template <typename T, int DIM, bool COUNT = false>
 __device__ __forceinline__ T bvh_nearest(G<DevGeometry<T>>& g, const T* x, int* best_prim, Tally* tally,
                                          LdsStack<T> lds, int hint) {
-  if constexpr (DIM == 3) return bvh_search<T, DIM, COUNT, STACK_BOTH>(g, x, best_prim, tally, lds, hint);
   if (g.depth <= lds.depth) return bvh_search<T, DIM, COUNT, STACK_LDS>(g, x, best_prim, tally, lds, hint);
-  return bvh_search<T, DIM, COUNT, STACK_PRIVATE>(g, x, best_prim, tally, lds, hint);
+  constexpr StackPlace kDeep = DIM == 3 ? STACK_BOTH : STACK_PRIVATE;
+  return bvh_search<T, DIM, COUNT, kDeep>(g, x, best_prim, tally, lds, hint);
 }
 
 // A polygon grid query returns its candidate list position tagged with kGridPrimTag
