@@ -410,7 +410,8 @@ wos_status wos_eval_offcentred(int32_t which, int32_t dim, int32_t precision, do
                                const double* u, const double* v, int64_t n, double* out, void* stream);
 
 /* 1 if points[i] lies strictly inside the domain, else 0 (harness helper; not on the
- * walk's path). inside: device int8 [n]. */
+ * walk's path). On the surface itself rounding decides, as it does for query points of a
+ * solve. inside: device int8 [n]. */
 wos_status wos_classify(const wos_problem* p, const double* points, int64_t n, int8_t* inside, void* stream);
 
 #ifdef __cplusplus

@@ -61,15 +61,17 @@ __device__ __forceinline__ double inside_term(G<DevGeometry<double>>& g, const d
     b[i] = t[3 + i] - x[i];
     c[i] = t[6 + i] - x[i];
   }
-  const double la = sqrt(a[0] * a[0] + a[1] * a[1] + a[2] * a[2]);
-  const double lb = sqrt(b[0] * b[0] + b[1] * b[1] + b[2] * b[2]);
-  const double lc = sqrt(c[0] * c[0] + c[1] * c[1] + c[2] * c[2]);
-  const double det = a[0] * (b[1] * c[2] - b[2] * c[1]) - a[1] * (b[0] * c[2] - b[2] * c[0]) +
-                     a[2] * (b[0] * c[1] - b[1] * c[0]);
-  const double ab = a[0] * b[0] + a[1] * b[1] + a[2] * b[2];
-  const double ac = a[0] * c[0] + a[1] * c[1] + a[2] * c[2];
-  const double bc = b[0] * c[0] + b[1] * c[1] + b[2] * c[2];
-  return 2.0 * atan2(det, la * lb * lc + ab * lc + ac * lb + bc * la);
+  // every rounding is written out: on the surface the sum's last bits decide, and left to the
+  // compiler they depend on the kernel around it
+  auto dot = [](const double* u, const double* v) {
+    return __builtin_fma(u[2], v[2], __builtin_fma(u[0], v[0], u[1] * v[1]));
+  };
+  auto minor = [&](int i, int j) { return __builtin_fma(b[i], c[j], -(c[i] * b[j])); };
+  const double la = sqrt(dot(a, a)), lb = sqrt(dot(b, b)), lc = sqrt(dot(c, c));
+  const double det = __builtin_fma(a[2], minor(0, 1), __builtin_fma(a[0], minor(1, 2), -(a[1] * minor(0, 2))));
+  const double ab = dot(a, b), ac = dot(a, c), bc = dot(b, c);
+  const double den = __builtin_fma(bc, la, __builtin_fma(ac, lb, __builtin_fma(la * lb, lc, ab * lc)));
+  return 2.0 * atan2(det, den);
 }
 
 template <int GEOM>
@@ -77,12 +79,24 @@ __device__ __forceinline__ bool inside_sum(double w) {
   return GEOM == GK_POLYGON ? ((int64_t)w & 1) != 0 : fabs(w) > 2.0 * M_PI;
 }
 
-// Inside test of one finite point by a whole wave, over every primitive.
+// Inside test of one finite point by a whole wave, over every primitive. On the surface of a mesh
+// the angles add up to 2 pi, the threshold, and rounding decides: sums that close to it (n
+// roundings of angles below 2 pi) are taken again in the primitives' order, so that the answer
+// does not depend on how the lanes share them.
 template <int GEOM>
 __device__ __forceinline__ bool inside_wave(G<DevGeometry<double>>& g, const double* x) {
+  const int lane = (int)__lane_id();
   double w = 0;
-  for (int j = (int)__lane_id(); j < g.n_prims; j += 64) w += inside_term<GEOM>(g, x, j);
+  for (int j = lane; j < g.n_prims; j += 64) w += inside_term<GEOM>(g, x, j);
   for (int off = 32; off > 0; off >>= 1) w += __shfl_xor(w, off);
+  if (GEOM == GK_TRIMESH && fabs(fabs(w) - 2.0 * M_PI) <= 1e-13 * (double)(g.n_prims + 64)) {
+    w = 0;
+    for (int j0 = 0; j0 < g.n_prims; j0 += 64) {
+      const int n = min(64, g.n_prims - j0);
+      const double t = lane < n ? inside_term<GEOM>(g, x, j0 + lane) : 0.0;
+      for (int k = 0; k < n; ++k) w += __shfl(t, k);
+    }
+  }
   return inside_sum<GEOM>(w);
 }
 
