@@ -960,7 +960,31 @@ struct Schedule {
   int n_launches = 0;
   int slot_words = 16;        // words per accumulation slot
   int grad_dim = 0;           // dim when gradient sums are asked for, else 0
+  bool shared_outputs = false;   // items add into the same memory: reduced one after another
 };
+
+// Whether any two of the items' output arrays share memory (two items of a batch may add into
+// one set of accumulators, or into overlapping parts of a larger one).
+bool outputs_overlap(const wos_batch_item* items, int n_items, int dim) {
+  std::vector<std::pair<uintptr_t, uintptr_t>> r;
+  auto add = [&](const void* p, uintptr_t n) {   // every output is 8 bytes wide
+    if (p && n) r.emplace_back((uintptr_t)p, (uintptr_t)p + 8 * n);
+  };
+  for (int k = 0; k < n_items; ++k) {
+    const wos_batch_item& x = items[k];
+    const uintptr_t n = (uintptr_t)x.n_points;
+    add(x.sum, n);
+    add(x.sum_sq, n);
+    add(x.n_walks, n);
+    add(x.n_steps, n);
+    add(x.grad_sum, n * dim);
+    add(x.grad_sum_sq, n * dim);
+  }
+  std::sort(r.begin(), r.end());
+  for (size_t k = 1; k < r.size(); ++k)
+    if (r[k].first < r[k - 1].second) return true;
+  return false;
+}
 
 wos_status check_items(const wos_batch_item* items, int n_items, const wos_options* opt, Schedule& s) {
   if (!items || n_items <= 0 || !opt) return fail(WOS_ERR_INVALID_ARG, "null or empty batch");
@@ -1013,6 +1037,7 @@ wos_status check_items(const wos_batch_item* items, int n_items, const wos_optio
   s.mode = walker_mode(s.variant, s.grad != 0, opt->ww_hi > 0);
   s.grad_dim = s.grad ? s.dim : 0;
   s.slot_words = slot_words(s.grad_dim);
+  s.shared_outputs = n_items > 1 && outputs_overlap(items, n_items, s.dim);
   return WOS_OK;
 }
 
@@ -1350,30 +1375,12 @@ wos_status prep_job(const wos_batch_item* items, int n_items, const Schedule& s,
   return WOS_OK;
 }
 
-// Whether any two of the items' output arrays share memory (two items of a batch may add into
-// one set of accumulators, or into overlapping parts of a larger one).
-bool outputs_overlap(const std::vector<DevItem>& d, int grad_dim) {
-  std::vector<std::pair<uintptr_t, uintptr_t>> r;
-  for (const DevItem& x : d) {
-    if (x.n_points == 0) continue;
-    const uintptr_t n = (uintptr_t)x.n_points * 8;   // every output is 8 bytes wide
-    for (const void* p : {(const void*)x.sum, (const void*)x.sum_sq, (const void*)x.n_walks, (const void*)x.n_steps})
-      r.emplace_back((uintptr_t)p, (uintptr_t)p + n);
-    for (const void* p : {(const void*)x.grad_sum, (const void*)x.grad_sum_sq})
-      if (grad_dim && p) r.emplace_back((uintptr_t)p, (uintptr_t)p + n * grad_dim);
-  }
-  std::sort(r.begin(), r.end());
-  for (size_t k = 1; k < r.size(); ++k)
-    if (r[k].first < r[k - 1].second) return true;
-  return false;
-}
-
 // Adds every item's sums into its outputs, in one launch; items that share outputs are added
 // one after another, as their blocks would race on them.
 hipError_t reduce_items(const std::vector<DevItem>& d, const Schedule& s, const DevItem* table, const uint64_t* slots,
                         hipStream_t st) {
   auto blocks = [](const DevItem& x) { return ((uint64_t)x.n_points + kReducePoints - 1) / kReducePoints; };
-  if (d.size() == 1 || !outputs_overlap(d, s.grad_dim))
+  if (!s.shared_outputs)
     return launch_reduce(s.grad_dim, table, (int)d.size(), 0, d.back().reduce_block + blocks(d.back()), slots,
                          s.slot_words, st);
   for (size_t k = 0; k < d.size(); ++k) {
@@ -1902,8 +1909,8 @@ wos_status wos_plan_create(const wos_batch_item* items, int32_t n_items, const w
   return guarded([&] { return plan_create_impl(items, n_items, opt, stream, out); });
 }
 
-wos_status wos_plan_time(wos_plan* P, uint64_t seed, uint64_t walk_offset_add, void* stream, double* walker_ms,
-                         double* total_ms) {
+static wos_status plan_time_impl(wos_plan* P, uint64_t seed, uint64_t walk_offset_add, void* stream, double* walker_ms,
+                                 double* total_ms) {
   if (!P || !walker_ms) return fail(WOS_ERR_INVALID_ARG, "null plan or output");
   if (P->opt.walk_offset + walk_offset_add + P->opt.walks_per_point > (1ull << 32))
     return fail(WOS_ERR_INVALID_ARG, "walk indices exceed 32 bits");
@@ -1945,6 +1952,11 @@ wos_status wos_plan_time(wos_plan* P, uint64_t seed, uint64_t walk_offset_add, v
   for (auto& m : marks)
     if (m) (void)hipEventDestroy(m);
   return r;
+}
+
+wos_status wos_plan_time(wos_plan* P, uint64_t seed, uint64_t walk_offset_add, void* stream, double* walker_ms,
+                         double* total_ms) {
+  return guarded([&] { return plan_time_impl(P, seed, walk_offset_add, stream, walker_ms, total_ms); });
 }
 
 wos_status wos_plan_launch(wos_plan* P, uint64_t seed, uint64_t walk_offset_add, void* stream) {
